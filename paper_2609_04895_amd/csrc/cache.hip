@@ -1,7 +1,7 @@
 // cache.hip - the per-(stream, layer) cache state machine of the decode step.
 //
-// cache_step_kernel: one wavefront per stream; expert e of the layer lives in
-// lane e % 64, register e / 64.  For the accessed layer l it
+// cache_step_kernel: one wavefront per (stream, layer) of a batch of layers;
+// expert e of the layer lives in lane e % 64, register e / 64.  For layer l it
 //   - finishes the router logits (adds the split-K partials in ascending
 //     order, adds the native bias, rounds once to fp32),
 //   - computes p^R, p^T (router policy) and p^S (modes with a Spatio
@@ -19,14 +19,13 @@
 //   - stores the next token's a-score (Section 3.3: s^T in the full mode;
 //     p^R in the Spatio-only ablation of Section 5 / Appendix B.4) and p^S
 //     as the prediction for the causal successor.
-// In the modes with a Spatio Router it then refines the successor layer's
-// cache before that layer is accessed (Algorithm 2): candidates Top_R(s^ST),
-// s^ST = a + p^S of the causal predecessor, examined in descending order; a
-// non-resident candidate fills free room, else replaces the lowest-s^ST
-// resident when its score is strictly higher (an inserted expert takes the
-// LRU time of the refinement).  The first layer of a token is refined by a
-// refine-only launch at the start of the token, from the previous token's
-// last-layer p^S (the wrap-around of the causal predecessor).
+// In the modes with a Spatio Router each layer is refined before its access
+// (Algorithm 2): candidates Top_R(s^ST), s^ST = a + p^S of the causal
+// predecessor, examined in descending order; a non-resident candidate fills
+// free room, else replaces the lowest-s^ST resident when its score is strictly
+// higher (an inserted expert takes the LRU time of the refinement).  The first
+// layer of a token takes the previous token's last-layer p^S (the wrap-around
+// of the causal predecessor).
 //
 // The same kernel groups the layer's (stream, k) selections by expert for the
 // FFN (fixed-capacity buckets filled with integer atomics) and counts the
@@ -45,7 +44,6 @@
 #include <math.h>
 
 #include "cmoe_internal.h"
-#include "combine.h"
 
 namespace cmoe {
 
@@ -291,10 +289,12 @@ __device__ inline void clear_bit(unsigned long long (&w)[NPL], int e) {
         if (j == (e >> 6)) w[j] &= ~(1ull << (e & 63));
 }
 
-// Pre-access refinement of one (stream, layer) cache (Algorithm 2).
+// Pre-access refinement of one (stream, layer) cache (Algorithm 2), in
+// registers: cw is updated, ins gets the experts inserted here; returns their
+// number (an expert inserted and replaced again counts).
 template <int NPL>
-__device__ void refine_one(const Layout& lo, int s, int rl, int R, int t, bool counted, const float (&pred)[NPL],
-                           const float (&aTv)[NPL], const unsigned long long (&cw_in)[NPL], int64_t ctr_p, int lane) {
+__device__ int refine_one(const Layout& lo, int R, const float (&pred)[NPL], const float (&aTv)[NPL],
+                          unsigned long long (&cw)[NPL], unsigned long long (&ins)[NPL], int lane) {
     const int N = lo.N;
     float sST[NPL];
     uint32_t cand[NPL];  // ordered scores; 0 = not a candidate (no real score maps to 0)
@@ -309,18 +309,12 @@ __device__ void refine_one(const Layout& lo, int s, int rl, int R, int t, bool c
             cand[j] = 0u;
         }
     }
-    unsigned long long* cptr = lo.cache + ((int64_t)s * lo.L + rl) * lo.NW;
-    unsigned long long cw[NPL];
-    int count = 0;
+    int count = 0, nP = 0;
 #pragma unroll
     for (int j = 0; j < NPL; ++j) {
-        cw[j] = j < lo.NW ? cw_in[j] : 0ull;
         count += __popcll(cw[j]);
+        ins[j] = 0ull;
     }
-    int nP = 0;
-    unsigned long long ins[NPL];  // experts inserted here
-#pragma unroll
-    for (int j = 0; j < NPL; ++j) ins[j] = 0ull;
     const int Rn = R < N ? R : N;
     for (int i = 0; i < Rn; ++i) {
         uint32_t ord_e;
@@ -347,289 +341,276 @@ __device__ void refine_one(const Layout& lo, int s, int rl, int R, int t, bool c
             }
         }
     }
-    if (lo.policy == kPolicyLRU) {  // inserted as the most recently used, at 2t + 1
-#pragma unroll
-        for (int j = 0; j < NPL; ++j) {
-            const int e = j * 64 + lane;
-            if (e < N && ((ins[j] >> lane) & 1ull)) lo.pol[((int64_t)s * lo.L + rl) * N + e] = (float)(2 * t + 1);
-        }
-    }
-    if (lane == 0) {
-        for (int j = 0; j < lo.NW; ++j) cptr[j] = cw[j];
-        lo.events[((int64_t)rl * lo.S + s) * 4 + 2] = nP;
-        if (counted) lo.ctr[((int64_t)s * lo.L + rl) * kNctr + kCtrP] = ctr_p + nP;
-    }
+    return nP;
 }
 
-template <int NPL, int NR, bool INJECT, int ZS>
-__device__ void stream_step(const Layout& lo, const StepArgs& a, int s, int lane) {
-    const int N = lo.N, L = lo.L, K = lo.K;
-    const bool spatio = lo.iS > 0;           // a Spatio Router: stores a-score and p^S
+// One (stream, layer) of a batch: refinement (REF) and access.  bl is the
+// layer's index in its batch.
+template <int NPL, int NR, bool INJECT, int ZS, bool REF>
+__device__ void stream_step(const Layout& lo, const StepArgs& a, int s, int bl, int lane) {
+    const int N = lo.N, L = lo.L, K = lo.K, l = a.l0 + bl;
+    const bool spatio = lo.iS > 0;           // a Spatio Router (always the last slot)
     const bool classical = lo.policy != kPolicyRouter;
     const bool counted = (a.flags & kFlagCount) != 0;
-    float pred[NPL];
+    const int64_t sl = (int64_t)s * L + l;
 
-    // Loads that do not depend on this token's scores are issued first so
-    // that their latencies overlap: the refined layer's a^T and cache words,
-    // the accessed layer's cache words and classical priorities, and the
-    // counters.  They are issued whatever the flags (rows clamped into range,
-    // words and experts past the end masked where they are used): a load
-    // under a branch of its own makes the compiler wait for it where the
-    // branches join, before the router partials below are even requested.
-    const bool refine = (a.flags & kFlagRefine) != 0;
-    const int64_t row_a = (int64_t)s * L + a.l, row_r = (int64_t)s * L + min(a.rl, L - 1);
-    float aTv[NPL], polv[NPL], pS_st[NPL];
-    unsigned long long cw_r[NPL], cw_a[NPL];
+    // Every load is issued before the first use, so that their latencies
+    // overlap: the a-scores, cache words, classical priorities and counters
+    // of this (stream, layer), the native bias, and the logits (router split
+    // partials, up to ZS per logit, or the injected logits).  Rows and splits
+    // are clamped into range and words, experts and splits past the end masked
+    // where they are used: a load under a branch of its own makes the compiler
+    // wait for it where the branches join.
+    float aTv[NPL], polv[NPL], pS_st[NPL], bz[NPL];
+    unsigned long long cw[NPL];
+    const float* brow = lo.bias ? lo.bias + (int64_t)l * N : lo.pol;  // without a bias: any N readable floats
 #pragma unroll
     for (int j = 0; j < NPL; ++j) {
         const int ec = min(j * 64 + lane, N - 1), jw = min(j, lo.NW - 1);
-        pS_st[j] = lo.pS[(int64_t)s * N + ec];  // the stored prediction, for a refine-only launch
-        aTv[j] = lo.aT[row_r * N + ec];
-        cw_r[j] = lo.cache[row_r * lo.NW + jw];
-        cw_a[j] = lo.cache[row_a * lo.NW + jw];
-        polv[j] = lo.pol[row_a * N + ec];
+        cw[j] = lo.cache[sl * lo.NW + jw];
+        polv[j] = lo.pol[sl * N + ec];
+        bz[j] = brow[ec];
+        if (REF) {
+            pS_st[j] = lo.pS[((int64_t)(a.psw ^ 1) * lo.S + s) * N + ec];
+            aTv[j] = lo.aT[sl * N + ec];
+        }
     }
-    // counters this wavefront updates (lane 0 owns them)
-    int64_t ctr_a[kNctr];
+    int64_t ctr_a[kNctr];  // counters this wavefront updates (lane 0 owns them)
 #pragma unroll
-    for (int c = 0; c < kNctr; ++c) ctr_a[c] = lo.ctr[row_a * kNctr + c];
-    const int64_t ctr_rp = lo.ctr[row_r * kNctr + kCtrP];
-    int64_t bucket = 0;  // lane k < K: bucket of its selection and position in it
-    int bucket_pos = 0;
-
-    if (a.flags & kFlagAccess) {
-        const int l = a.l;
-        const int64_t sl = (int64_t)s * L + l;
-        // logits: every load is issued first (router split partials, ZS slots
-        // per logit, or the injected logits; the native bias, a zero row when
-        // there is none), then the splits are added in ascending order and
-        // rounded once
-        const float* brow = lo.bias ? lo.bias + (int64_t)l * N : lo.zero_row;
-        double2 pv[NR][NPL][ZS / 2];
-        float zin[NR][NPL], bz[NPL];
+    for (int c = 0; c < kNctr; ++c) ctr_a[c] = lo.ctr[sl * kNctr + c];
+    // slot r < NR: this layer's logits; slot NR (REF): the Spatio logits of
+    // the causal predecessor, when that layer is in this batch
+    constexpr int NZ = NR + (REF ? 1 : 0);
+    double pv[NZ][NPL][ZS];
+    float zin[NZ][NPL];
 #pragma unroll
-        for (int j = 0; j < NPL; ++j) {
-            const int e = j * 64 + lane;
-            const int ec = e < N ? e : N - 1;  // lanes past N read a valid address and discard it
-            bz[j] = brow[ec];
+    for (int j = 0; j < NPL; ++j) {
+        const int ec = min(j * 64 + lane, N - 1);  // lanes past N read a valid address and discard it
 #pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                if (INJECT) {
-                    zin[r][j] = a.z[r][sl * N + ec];
-                } else {
-                    const double2* zp =
-                        reinterpret_cast<const double2*>(lo.zpart + (((int64_t)s * NR + r) * N + ec) * ZS);
+        for (int r = 0; r < NZ; ++r) {
+            const int rr = r < NR ? r : NR - 1, lb = r < NR ? bl : max(bl - 1, 0);
+            if (INJECT) {
+                zin[r][j] = a.z[rr][((int64_t)s * L + a.l0 + lb) * N + ec];
+            } else {
+                const double* zp = lo.zpart + (((int64_t)lb * lo.S + s) * NR + rr) * lo.nsplit * N + ec;
 #pragma unroll
-                    for (int u = 0; u < ZS / 2; ++u) pv[r][j][u] = zp[u];
-                }
+                for (int u = 0; u < ZS; ++u) pv[r][j][u] = zp[(int64_t)min(u, lo.nsplit - 1) * N];
             }
         }
-        float z[3][NPL];
+    }
+
+    // logits: the splits added in ascending order, the native bias, rounded once
+    float z[3][NPL], zp[NPL];
 #pragma unroll
-        for (int r = NR; r < 3; ++r)
+    for (int r = NR; r < 3; ++r)
 #pragma unroll
-            for (int j = 0; j < NPL; ++j) z[r][j] = 0.0f;
+        for (int j = 0; j < NPL; ++j) z[r][j] = 0.0f;
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
+    for (int r = 0; r < NZ; ++r) {
 #pragma unroll
-            for (int j = 0; j < NPL; ++j) {
-                float v;
-                if (INJECT) {
-                    v = zin[r][j];
-                } else {
-                    double acc = 0.0;
+        for (int j = 0; j < NPL; ++j) {
+            float v;
+            if (INJECT) {
+                v = zin[r][j];
+            } else {
+                double acc = 0.0;
 #pragma unroll
-                    for (int p = 0; p < ZS; ++p)
-                        if (p < lo.nsplit) acc += (p & 1) ? pv[r][j][p >> 1].y : pv[r][j][p >> 1].x;
-                    if (r == 0) acc += (double)bz[j];
-                    v = (float)acc;
-                }
-                const int e = j * 64 + lane;
+                for (int p = 0; p < ZS; ++p)
+                    if (p < lo.nsplit) acc += pv[r][j][p];
+                if (r == 0 && lo.bias) acc += (double)bz[j];
+                v = (float)acc;
+            }
+            const int e = j * 64 + lane;
+            if (r < NR) {
                 if (e < N) lo.logits[(((int64_t)l * lo.S + s) * NR + r) * N + e] = v;
                 z[r][j] = e < N ? v : 0.0f;
+            } else {
+                zp[j] = e < N ? v : 0.0f;
             }
         }
-        // router slots: 0 native, then temporal (router policy), then spatio;
-        // every slot is in use, so the NR softmaxes run together
-        float pz[3][NPL];
-        softmax_fixed<NPL, NR>(z, N, lane, pz);
-        float pR[NPL], pT[NPL];
-#pragma unroll
-        for (int j = 0; j < NPL; ++j) {
-            pR[j] = pz[0][j];
-            pT[j] = (NR >= 2 && !classical) ? pz[1][j] : 0.0f;
-            if (NR >= 2 && spatio) pred[j] = pz[NR - 1][j];
-        }
-
-        // Top-K by native logit, lower index first on ties
-        uint32_t key[NPL];  // ordered native logits; 0 = taken or past N (no real logit maps to 0)
-#pragma unroll
-        for (int j = 0; j < NPL; ++j) {
-            const int e = j * 64 + lane;
-            key[j] = e < N ? ord32(z[0][j]) : 0u;
-        }
-        unsigned long long sw[NPL];
-#pragma unroll
-        for (int j = 0; j < NPL; ++j) sw[j] = 0ull;
-        float gsum = 0.0f, my_p = 0.0f;
-        int my_sel = 0;
-        for (int k = 0; k < K; ++k) {
-            uint32_t kmax;
-            const int e = argmax_lowest(key, kmax);  // highest logit, lower index on ties
-            float pv = 0.0f;
-#pragma unroll
-            for (int j = 0; j < NPL; ++j) {
-                if (j == (e >> 6) && lane == (e & 63)) {
-                    key[j] = 0u;
-                    pv = pR[j];
-                }
-            }
-            pv = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(pv), e & 63));
-            gsum = gsum + pv;
-            set_bit(sw, e);
-            if (lane == k) {
-                my_p = pv;
-                my_sel = e;
-            }
-        }
-        if (lane < K) {
-            const int64_t o = ((int64_t)l * lo.S + s) * K + lane;
-            lo.sel[o] = my_sel;
-            lo.gates[o] = my_p / gsum;
-            // token (s, k) joins the bucket of its expert; the position inside
-            // the bucket does not affect any result (each token is its own
-            // column of the expert's matrix products).  The position is used
-            // at the end of the step, so the atomic's round trip overlaps the
-            // rest of it.
-            bucket = (int64_t)a.bbuf * N + my_sel;
-            bucket_pos = atomicAdd(&lo.bcount[bucket], 1);
-            if (counted) atomicAdd(&lo.selcount[(int64_t)l * N + my_sel], 1ull);
-        }
-        // retention priority of Algorithm 1
-        float sT[NPL];
-        if (!classical) {
-#pragma unroll
-            for (int j = 0; j < NPL; ++j) sT[j] = pR[j] + pT[j];
-        } else {
-#pragma unroll
-            for (int j = 0; j < NPL; ++j) {
-                const bool used = (sw[j] >> lane) & 1ull;
-                float v = j * 64 + lane < N ? polv[j] : 0.0f;
-                if (lo.policy == kPolicyLRU) {
-                    if (used) v = (float)(2 * a.t + 2);
-                } else if (lo.policy == kPolicyLFU) {
-                    if (used) v = v + 1.0f;
-                } else {
-                    v = v * lo.lrfu_w;
-                    if (used) v = v + 1.0f;
-                }
-                sT[j] = v;
-                const int e = j * 64 + lane;
-                if (e < N) lo.pol[sl * N + e] = v;
-            }
-        }
-
-        // access
-        unsigned long long* cptr = lo.cache + sl * lo.NW;
-        unsigned long long cw[NPL];
-        int count = 0, hits = 0;
-#pragma unroll
-        for (int j = 0; j < NPL; ++j) {
-            cw[j] = j < lo.NW ? cw_a[j] : 0ull;
-            count += __popcll(cw[j]);
-            hits += __popcll(cw[j] & sw[j]);
-        }
-        const int nD = K - hits;
-        // Algorithm 1 with the demand set D = S \ C taken before any insertion
-#pragma unroll
-        for (int j = 0; j < NPL; ++j) {
-            unsigned long long dw = sw[j] & ~cw[j];
-            while (dw) {
-                const int b = __builtin_ctzll(dw);
-                dw &= dw - 1;
-                if (count < lo.C) {
-                    cw[j] |= 1ull << b;
-                    ++count;
-                } else {
-                    unsigned long long vict[NPL];
-#pragma unroll
-                    for (int jj = 0; jj < NPL; ++jj) vict[jj] = cw[jj] & ~sw[jj];
-                    const unsigned long long mn = argmin_member(sT, vict, N, lane);
-                    clear_bit(cw, (int)(mn & 0xFFFFFFFFull));
-                    cw[j] |= 1ull << b;
-                }
-            }
-        }
-        if (lane == 0) {
-            for (int j = 0; j < lo.NW; ++j) cptr[j] = cw[j];
-            int32_t* ev = lo.events + ((int64_t)l * lo.S + s) * 4;
-            ev[0] = hits;
-            ev[1] = nD;
-            if (!(a.flags & kFlagRefinedHere)) ev[2] = 0;
-            ev[3] = 0;
-            if (counted) {
-                int64_t* c = lo.ctr + sl * kNctr;
-                c[kCtrA] = ctr_a[kCtrA] + K;
-                c[kCtrHits] = ctr_a[kCtrHits] + hits;
-                c[kCtrD] = ctr_a[kCtrD] + nD;
-                c[kCtrT] = ctr_a[kCtrT] + 1;
-            }
-        }
-        if (spatio) {  // the next token's a-score of this layer, and p^S for the successor
-            const bool spatio_only = lo.iT < 0;
-#pragma unroll
-            for (int j = 0; j < NPL; ++j) {
-                const int e = j * 64 + lane;
-                if (e < N) {
-                    lo.aT[sl * N + e] = spatio_only ? pR[j] : sT[j];
-                    lo.pS[(int64_t)s * N + e] = pred[j];
-                }
-            }
-        }
-        // The refinement is called on each side of the branch: after a join
-        // with the refine-only side, whose prediction loads may still be in
-        // flight there, the compiler waits for every outstanding memory
-        // operation, and with it for the bucket atomic issued above, whose
-        // round trip the refinement is meant to hide.
-        if (refine) refine_one<NPL>(lo, s, a.rl, a.R, a.t, counted, pred, aTv, cw_r, ctr_rp, lane);
-    } else {
-        // refine-only launch: the predecessor's prediction is the stored one
-#pragma unroll
-        for (int j = 0; j < NPL; ++j) {
-            const int e = j * 64 + lane;
-            pred[j] = e < N ? pS_st[j] : 0.0f;
-        }
-        if (refine) refine_one<NPL>(lo, s, a.rl, a.R, a.t, counted, pred, aTv, cw_r, ctr_rp, lane);
     }
-    if ((a.flags & kFlagAccess) && lane < K) {
+    // router slots: 0 native, then temporal (router policy), then spatio.  The
+    // NR softmaxes run together; with refinement the Spatio slot holds the
+    // predecessor's logits, the prediction for this layer.
+    float zz[3][NPL], pz[3][NPL], pR[NPL], pT[NPL], pred[NPL];
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int j = 0; j < NPL; ++j) zz[r][j] = (REF && r == NR - 1) ? zp[j] : z[r][j];
+    softmax_fixed<NPL, NR>(zz, N, lane, pz);
+#pragma unroll
+    for (int j = 0; j < NPL; ++j) {
+        pR[j] = pz[0][j];
+        pT[j] = (NR >= 2 && !classical) ? pz[1][j] : 0.0f;
+        // the first layer of a batch is predicted by the previous batch's last
+        // layer (for layer 0: the previous token's)
+        if (REF) pred[j] = bl > 0 ? pz[NR - 1][j] : (j * 64 + lane < N ? pS_st[j] : 0.0f);
+    }
+
+    // Top-K by native logit, lower index first on ties
+    uint32_t key[NPL];  // ordered native logits; 0 = taken or past N (no real logit maps to 0)
+#pragma unroll
+    for (int j = 0; j < NPL; ++j) {
+        const int e = j * 64 + lane;
+        key[j] = e < N ? ord32(z[0][j]) : 0u;
+    }
+    unsigned long long sw[NPL];
+#pragma unroll
+    for (int j = 0; j < NPL; ++j) sw[j] = 0ull;
+    float gsum = 0.0f, my_p = 0.0f;
+    int my_sel = 0;
+    for (int k = 0; k < K; ++k) {
+        uint32_t kmax;
+        const int e = argmax_lowest(key, kmax);  // highest logit, lower index on ties
+        float pv = 0.0f;
+#pragma unroll
+        for (int j = 0; j < NPL; ++j) {
+            if (j == (e >> 6) && lane == (e & 63)) {
+                key[j] = 0u;
+                pv = pR[j];
+            }
+        }
+        pv = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(pv), e & 63));
+        gsum = gsum + pv;
+        set_bit(sw, e);
+        if (lane == k) {
+            my_p = pv;
+            my_sel = e;
+        }
+    }
+    int64_t bucket = 0;  // lane k < K: bucket of its selection and position in it
+    int bucket_pos = 0;
+    if (lane < K) {
+        const int64_t o = ((int64_t)l * lo.S + s) * K + lane;
+        lo.sel[o] = my_sel;
+        lo.gates[o] = my_p / gsum;
+        // token (s, k) joins the bucket of its expert; the position inside
+        // the bucket does not affect any result (each token is its own
+        // column of the expert's matrix products).  The position is used
+        // at the end of the step, so the atomic's round trip overlaps the
+        // rest of it.
+        bucket = (int64_t)bl * N + my_sel;
+        bucket_pos = atomicAdd(&lo.bcount[bucket], 1);
+        if (counted) atomicAdd(&lo.selcount[(int64_t)l * N + my_sel], 1ull);
+    }
+
+#pragma unroll
+    for (int j = 0; j < NPL; ++j)
+        if (j >= lo.NW) cw[j] = 0ull;
+    int nP = 0;
+    if (REF) {
+        unsigned long long ins[NPL];
+        nP = refine_one<NPL>(lo, a.R, pred, aTv, cw, ins, lane);
+        if (lane == 0)  // what the proactive residency event of this layer sees
+            for (int j = 0; j < lo.NW; ++j) lo.mid[((int64_t)l * lo.S + s) * lo.NW + j] = cw[j];
+        if (lo.policy == kPolicyLRU) {  // inserted as the most recently used, at 2t + 1
+#pragma unroll
+            for (int j = 0; j < NPL; ++j)
+                if ((ins[j] >> lane) & 1ull) polv[j] = (float)(2 * a.t + 1);
+        }
+    }
+
+    // retention priority of Algorithm 1
+    float sT[NPL];
+    if (!classical) {
+#pragma unroll
+        for (int j = 0; j < NPL; ++j) sT[j] = pR[j] + pT[j];
+    } else {
+#pragma unroll
+        for (int j = 0; j < NPL; ++j) {
+            const bool used = (sw[j] >> lane) & 1ull;
+            float v = j * 64 + lane < N ? polv[j] : 0.0f;
+            if (lo.policy == kPolicyLRU) {
+                if (used) v = (float)(2 * a.t + 2);
+            } else if (lo.policy == kPolicyLFU) {
+                if (used) v = v + 1.0f;
+            } else {
+                v = v * lo.lrfu_w;
+                if (used) v = v + 1.0f;
+            }
+            sT[j] = v;
+            const int e = j * 64 + lane;
+            if (e < N) lo.pol[sl * N + e] = v;
+        }
+    }
+
+    // access
+    int count = 0, hits = 0;
+#pragma unroll
+    for (int j = 0; j < NPL; ++j) {
+        count += __popcll(cw[j]);
+        hits += __popcll(cw[j] & sw[j]);
+    }
+    const int nD = K - hits;
+    // Algorithm 1 with the demand set D = S \ C taken before any insertion
+#pragma unroll
+    for (int j = 0; j < NPL; ++j) {
+        unsigned long long dw = sw[j] & ~cw[j];
+        while (dw) {
+            const int b = __builtin_ctzll(dw);
+            dw &= dw - 1;
+            if (count < lo.C) {
+                cw[j] |= 1ull << b;
+                ++count;
+            } else {
+                unsigned long long vict[NPL];
+#pragma unroll
+                for (int jj = 0; jj < NPL; ++jj) vict[jj] = cw[jj] & ~sw[jj];
+                const unsigned long long mn = argmin_member(sT, vict, N, lane);
+                clear_bit(cw, (int)(mn & 0xFFFFFFFFull));
+                cw[j] |= 1ull << b;
+            }
+        }
+    }
+    if (lane == 0) {
+        for (int j = 0; j < lo.NW; ++j) lo.cache[sl * lo.NW + j] = cw[j];
+        *reinterpret_cast<int4*>(lo.events + ((int64_t)l * lo.S + s) * 4) = int4{hits, nD, nP, 0};
+        if (counted) {
+            int64_t* c = lo.ctr + sl * kNctr;
+            c[kCtrA] = ctr_a[kCtrA] + K;
+            c[kCtrHits] = ctr_a[kCtrHits] + hits;
+            c[kCtrD] = ctr_a[kCtrD] + nD;
+            c[kCtrP] = ctr_a[kCtrP] + nP;
+            c[kCtrT] = ctr_a[kCtrT] + 1;
+        }
+    }
+    if (spatio) {  // the next token's a-score of this layer
+        const bool spatio_only = lo.iT < 0;
+#pragma unroll
+        for (int j = 0; j < NPL; ++j) {
+            const int e = j * 64 + lane;
+            if (e < N) lo.aT[sl * N + e] = spatio_only ? pR[j] : sT[j];
+        }
+        if (bl == a.nl - 1) {  // p^S of the batch's last layer, for its successor
+            float own[3][NPL], po[3][NPL];
+            if (REF) {
+#pragma unroll
+                for (int j = 0; j < NPL; ++j) own[0][j] = z[NR - 1][j];
+                softmax_fixed<NPL, 1>(own, N, lane, po);
+            }
+#pragma unroll
+            for (int j = 0; j < NPL; ++j) {
+                const int e = j * 64 + lane;
+                if (e < N) lo.pS[((int64_t)a.psw * lo.S + s) * N + e] = REF ? po[0][j] : pz[NR - 1][j];
+            }
+        }
+    }
+    if (lane < K) {
         lo.pairs[bucket * lo.S + bucket_pos] = (s << 8) | lane;
-        if (counted && bucket_pos == 0) atomicAdd(&lo.active_sum[a.l], 1ull);
+        if (counted && bucket_pos == 0) atomicAdd(&lo.active_sum[l], 1ull);
     }
 }
 
-// grid: the stream workgroups, then (a.y non-NULL) the workgroups of the
-// previous layer's combine.  The combine's only input, the gated expert
-// outputs, is complete once the previous layer's FFN has run, and no step of
-// this launch reads its output, so it runs here on the compute units that the
-// stream wavefronts leave idle, in place of a launch of its own; its
-// workgroups come after the streams' in dispatch order, so the streams'
-// prologue loads are issued first.
-template <int NPL, int NR, bool INJECT, int ZS>
-__global__ __launch_bounds__(64 * kStreamsPerBlock) void cache_step_kernel(Layout lo, StepArgs a) {
-    constexpr int kThreads = 64 * kStreamsPerBlock;
-    const int nsb = (lo.S + kStreamsPerBlock - 1) / kStreamsPerBlock;
-    if ((int)blockIdx.x >= nsb) {
-        combine_quad(lo, a.cl, a.y, (int64_t)(blockIdx.x - nsb) * kThreads + threadIdx.x);
-        return;
-    }
-    const int lane = threadIdx.x & 63;
-    const int s = blockIdx.x * kStreamsPerBlock + (threadIdx.x >> 6);
-    if ((a.flags & kFlagAccess) && blockIdx.x == 0) {
-        // the other bucket buffer was used by the previous layer step (its FFN
-        // has completed) and is filled by the next one
-        for (int i = threadIdx.x; i < lo.N; i += kThreads) lo.bcount[(int64_t)(a.bbuf ^ 1) * lo.N + i] = 0;
-    }
-    if (s < lo.S) stream_step<NPL, NR, INJECT, ZS>(lo, a, s, lane);  // wave-uniform branch
+// grid: x = streams, y = layers of the batch; one wavefront per (stream,
+// layer).  No step depends on another: a layer's refinement needs the previous
+// token's state of that layer and the predecessor's Spatio logits of this
+// token, which the router launch has left for every layer of the batch, so
+// one launch takes a batch of layers.  A wavefront is a chain of dependent
+// wave reductions (about 4 us); only the number of them in flight hides it.
+// At 64 streams and 24 layers one launch replaces 24 of 5.9 us.
+template <int NPL, int NR, bool INJECT, int ZS, bool REF>
+__global__ __launch_bounds__(64) void cache_step_kernel(Layout lo, StepArgs a) {
+    stream_step<NPL, NR, INJECT, ZS, REF>(lo, a, blockIdx.x, blockIdx.y, threadIdx.x);
 }
 
 // ---------------------------------------------------------------- init
@@ -643,7 +624,7 @@ __global__ void init_kernel(Layout lo) {
         lo.aT[i] = 0.0f;
         lo.pol[i] = 0.0f;
     }
-    for (int64_t i = gid; i < (int64_t)lo.S * lo.N; i += gs) lo.pS[i] = 0.0f;
+    for (int64_t i = gid; i < (int64_t)2 * lo.S * lo.N; i += gs) lo.pS[i] = 0.0f;
     for (int64_t i = gid; i < (int64_t)lo.S * lo.L * kNctr; i += gs) lo.ctr[i] = 0;
     for (int64_t i = gid; i < (int64_t)lo.L * 2; i += gs) lo.phys[i] = 0;
     for (int64_t i = gid; i < lo.L; i += gs) lo.active_sum[i] = 0ull;
@@ -656,15 +637,13 @@ __global__ void init_kernel(Layout lo) {
     if (lo.events == nullptr) return;  // no workspace bound (kernel-uniform)
     for (int64_t i = gid; i < (int64_t)lo.L * 2; i += gs) lo.step_fills[i] = 0;
     for (int64_t i = gid; i < (int64_t)lo.L * lo.S * 4; i += gs) lo.events[i] = 0;
-    for (int64_t i = gid; i < (int64_t)2 * lo.N; i += gs) lo.bcount[i] = 0;
-    for (int64_t i = gid; i < lo.N; i += gs) lo.zero_row[i] = 0.0f;
 }
 
-// What a token's first layer step needs zero in a workspace that other calls
-// may have left behind: both bucket-count buffers and the zero bias row.
-__global__ __launch_bounds__(256) void prep_workspace_kernel(Layout lo) {
-    for (int i = threadIdx.x; i < 2 * lo.N; i += blockDim.x) lo.bcount[i] = 0;
-    for (int i = threadIdx.x; i < lo.N; i += blockDim.x) lo.zero_row[i] = 0.0f;
+// Bucket counts of a batch whose logits are injected (otherwise the router
+// launch clears them).
+__global__ __launch_bounds__(256) void clear_buckets_kernel(Layout lo, int n) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) lo.bcount[i] = 0;
 }
 
 }  // namespace
@@ -674,23 +653,31 @@ hipError_t launch_init(const Layout& lo, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_prep_workspace(const Layout& lo, hipStream_t st) {
-    hipLaunchKernelGGL(prep_workspace_kernel, dim3(1), dim3(256), 0, st, lo);
+hipError_t launch_clear_buckets(const Layout& lo, int nl, hipStream_t st) {
+    hipLaunchKernelGGL(clear_buckets_kernel, dim3((nl * lo.N + 255) / 256), dim3(256), 0, st, lo, nl * lo.N);
     return hipGetLastError();
+}
+
+template <int NPL, int NR, bool REF>
+void launch_step_ref(const Layout& lo, const StepArgs& a, hipStream_t st, const Timing& tm) {
+    const dim3 grid(lo.S, a.nl), block(64);
+    if (a.flags & kFlagInject)
+        launch_kernel(cache_step_kernel<NPL, NR, true, 1, REF>, grid, block, st, tm, lo, a);
+    else if (lo.nsplit <= 2)
+        launch_kernel(cache_step_kernel<NPL, NR, false, 2, REF>, grid, block, st, tm, lo, a);
+    else
+        launch_kernel(cache_step_kernel<NPL, NR, false, kMaxSplit, REF>, grid, block, st, tm, lo, a);
 }
 
 template <int NPL, int NR>
 hipError_t launch_step_nr(const Layout& lo, const StepArgs& a, hipStream_t st, const Timing& tm) {
-    const int64_t nsb = (lo.S + kStreamsPerBlock - 1) / kStreamsPerBlock;
-    const int64_t quads = a.y ? (int64_t)lo.S * (lo.d / 4) : 0;  // combine threads
-    const dim3 grid((unsigned)(nsb + (quads + 64 * kStreamsPerBlock - 1) / (64 * kStreamsPerBlock)));
-    const dim3 block(64 * kStreamsPerBlock);
-    if (a.flags & kFlagInject)
-        launch_kernel(cache_step_kernel<NPL, NR, true, 2>, grid, block, st, tm, lo, a);
-    else if (lo.zstride == 4)
-        launch_kernel(cache_step_kernel<NPL, NR, false, 4>, grid, block, st, tm, lo, a);
-    else
-        launch_kernel(cache_step_kernel<NPL, NR, false, kMaxSplit>, grid, block, st, tm, lo, a);
+    if constexpr (NR > 1) {  // refinement needs a Spatio Router
+        if (a.flags & kFlagRefine) {
+            launch_step_ref<NPL, NR, true>(lo, a, st, tm);
+            return hipGetLastError();
+        }
+    }
+    launch_step_ref<NPL, NR, false>(lo, a, st, tm);
     return hipGetLastError();
 }
 

@@ -2,17 +2,18 @@
 // buffer carving, the per-token launch sequence on the main and side streams,
 // counters, inspection and kernel timing.
 //
-// Launch sequence of one token (layers in causal order; "refining modes" are
-// the full and Spatio-only modes, which have a Spatio Router):
-//   [refining mode, t >= 1, R > 0] main: cache step refining layer 0 from the
-//       previous token's last-layer Spatio prediction; side: fill (proactive)
-//   for each layer l:
-//     main: router GEMV(l)
-//     main: [wait for the proactive fill of l] cache step(l): access, retention,
-//           counters, buckets; in a refining mode also refinement of layer l + 1
-//     main: fill(l, demand)  -- gates the FFN of this layer
-//     side: [refining mode] fill(l + 1, proactive), overlapping the FFN of l
-//     main: expert gate/up(l), expert down(l), combine(l)
+// Launch sequence of one token: the layers run in batches of up to G, in
+// causal order ("refining" is a mode with a Spatio Router at t >= 1, R > 0).
+// Every hidden state of the token is an input of the call, so a layer's logits
+// and cache step wait for no other layer's FFN:
+//   for each batch of layers:
+//     main: router GEMV (batch)
+//     main: cache step (batch): refinement, access, retention, counters, buckets
+//     for each layer l:
+//       main: fill(l, demand)  -- gates the FFN of this layer
+//       [refining] main or side: fill(l, proactive), before it
+//       main: expert gate/up(l), expert down(l)
+//     main: combine (batch)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -36,6 +37,9 @@ using cmoe::StepArgs;
 // device memory: the device address comes from hipGetSymbolAddress, taken once
 // per device at cmoe_init with that device current.
 constexpr size_t kScratchBytes = size_t(64) << 20;
+// The workspace asked for holds the per-step buffers of as many layers (a
+// batch) as stay within this, and of one layer at least.
+constexpr size_t kBatchBytes = size_t(192) << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
@@ -70,13 +74,41 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 enum KernelId { KID_ROUTER = 0, KID_CACHE = 1, KID_FILL = 2, KID_UP = 3, KID_DOWN = 4, KID_COMBINE = 5 };
 
 struct Derived {
-    int NW, n_r, n_slots, nsplit, rdk, zstride;
+    int NW, n_r, n_slots, nsplit, rdk;
     int rounds;        // FFN rounds per layer step: more than one only for an arena smaller than the union
     int iT, iS;        // router slots of the Temporal / Spatio Router, -1 if not used
     int ffn_waves;     // wavefronts per bf16 FFN workgroup (1 or 4)
     int xcd_units;     // 1: each FFN work unit's workgroups on one XCD
     size_t esz, expert_bytes;
 };
+
+// Router split-K: each wavefront of a router workgroup sums a 32-aligned k
+// range of rdk; a workgroup covers kRouterWaves ranges and writes one partial
+// per logit.
+int router_splits(const cmoe_config* c, int64_t rdk) {
+    const int64_t W = cmoe::kRouterWaves;
+    return (int)((c->d + W * rdk - 1) / (W * rdk));
+}
+
+// rdk for at most max_split partials per logit, with ranges as long as still
+// give about a thousand wavefronts per layer.
+int router_range(const cmoe_config* c, int n_r, int max_split) {
+    const int64_t tiles = (int64_t)n_r * ((c->N + 15) / 16) * ((c->S + 15) / 16);
+    const int W = cmoe::kRouterWaves;
+    auto splits = [c](int64_t k) { return router_splits(c, k); };
+    int rdk = 32;
+    while (splits(rdk) > max_split) rdk *= 2;
+    while (W * 2 * rdk <= c->d && tiles * W * splits(2 * rdk) >= 1024) rdk *= 2;
+    // a single partial per logit leaves big layers (many streams, three
+    // routers) with under two wavefronts per SIMD: take two
+    if (splits(rdk) == 1 && tiles * W < 2048 && rdk >= 64) rdk /= 2;
+    // up to four partials per logit while the grid stays under ~8K wavefronts:
+    // shorter wavefronts hide more of the loads' latency under the fp64 matrix
+    // work (measured on MI355X, 256 streams with three routers: 11.3 against
+    // 12.2 us per launch at d = 2048, 19.7 against 20.3 us at d = 4096)
+    while (splits(rdk) < 4 && rdk >= 64 && splits(rdk / 2) <= 4 && tiles * W * splits(rdk / 2) <= 8192) rdk /= 2;
+    return rdk;
+}
 
 bool has_spatio(int mode) { return mode == CMOE_MODE_SPATIO_TEMPORAL || mode == CMOE_MODE_SPATIO_ONLY; }
 
@@ -133,35 +165,16 @@ cmoe_status validate(const cmoe_config* c, Derived* dv) {
     dv->rounds = dv->n_slots < max_slots ? (int)((max_exec + dv->n_slots - 1) / dv->n_slots) : 1;
     dv->esz = c->dtype == CMOE_BF16 ? 2 : 4;
     dv->expert_bytes = (size_t)3 * c->d * c->F * dv->esz;
-    // router split-K: each wavefront of a router workgroup sums a 32-aligned
-    // k range of rdk; a workgroup covers kRouterWaves ranges and writes one
-    // partial; at most kMaxSplit partials per logit, and ranges as long as
-    // still give about a thousand wavefronts
-    const int64_t tiles = (int64_t)dv->n_r * ((c->N + 15) / 16) * ((c->S + 15) / 16);
-    const int W = cmoe::kRouterWaves;
-    auto splits = [&](int64_t k) { return (c->d + W * k - 1) / (W * k); };
-    int rdk = 32;
-    while (splits(rdk) > cmoe::kMaxSplit) rdk *= 2;
-    while (W * 2 * rdk <= c->d && tiles * W * splits(2 * rdk) >= 1024) rdk *= 2;
-    // a single partial per logit leaves big layers (many streams, three
-    // routers) with under two wavefronts per SIMD: take two
-    if (splits(rdk) == 1 && tiles * W < 2048 && rdk >= 64) rdk /= 2;
-    // up to four partials per logit (one slot group of the cache step's
-    // loads) while the grid stays under ~8K wavefronts: shorter wavefronts
-    // hide more of the loads' latency under the fp64 matrix work (measured on
-    // MI355X, 256 streams with three routers: 11.3 against 12.2 us per launch
-    // at d = 2048, 19.7 against 20.3 us at d = 4096)
-    while (splits(rdk) < 4 && rdk >= 64 && splits(rdk / 2) <= 4 && tiles * W * splits(rdk / 2) <= 8192) rdk /= 2;
-    dv->rdk = rdk;
-    dv->nsplit = (int)splits(rdk);
-    dv->zstride = dv->nsplit <= 4 ? 4 : cmoe::kMaxSplit;  // partial slots per logit
+    dv->rdk = router_range(c, dv->n_r, cmoe::kMaxSplit);
+    dv->nsplit = router_splits(c, dv->rdk);
     return CMOE_OK;
 }
 
 // Offsets of every sub-buffer; used both for sizing and for carving.
 struct Plan {
-    size_t cache, aT, pol, pS, ctr, phys, active_sum, selcount, slot_of, slot_exp, slot_stamp, state_total;
-    size_t zpart, logits, sel, gates, events, step_fills, bcount, pairs, act, yp, zero_row, units, round_of, ws_total;
+    int G;  // layers per batch
+    size_t cache, aT, pol, pS, mid, ctr, phys, active_sum, selcount, slot_of, slot_exp, slot_stamp, state_total;
+    size_t zpart, logits, sel, gates, events, step_fills, bcount, pairs, act, yp, units, round_of, ws_total;
     size_t arena;
 };
 
@@ -169,8 +182,10 @@ int max_units(const cmoe_config* c) {
     return c->N + (int)(((int64_t)c->S * c->K + cmoe::kUnitTokens - 1) / cmoe::kUnitTokens);
 }
 
-Plan make_plan(const cmoe_config* c, const Derived& dv) {
+// The plan with G layers per batch (the state does not depend on G).
+Plan make_plan(const cmoe_config* c, const Derived& dv, int G) {
     Plan p{};
+    p.G = G;
     const size_t S = c->S, L = c->L, N = c->N, K = c->K;
     size_t o = 0;
     auto take = [&o](size_t bytes) {
@@ -181,7 +196,8 @@ Plan make_plan(const cmoe_config* c, const Derived& dv) {
     p.cache = take(S * L * dv.NW * 8);
     p.aT = take(S * L * N * 4);
     p.pol = take(S * L * N * 4);
-    p.pS = take(S * N * 4);
+    p.pS = take(2 * S * N * 4);
+    p.mid = take(L * S * dv.NW * 8);
     p.ctr = take(S * L * cmoe::kNctr * 8);
     p.phys = take(L * 2 * 8);
     p.active_sum = take(L * 8);
@@ -191,17 +207,16 @@ Plan make_plan(const cmoe_config* c, const Derived& dv) {
     p.slot_stamp = take(2 * L * (size_t)dv.n_slots * 4);
     p.state_total = o;
     o = 0;
-    p.zpart = take(S * dv.n_r * N * (size_t)dv.zstride * 8);
+    p.zpart = take(G * S * dv.n_r * N * (size_t)dv.nsplit * 8);
     p.logits = take(L * S * dv.n_r * N * 4);
     p.sel = take(L * S * K * 4);
     p.gates = take(L * S * K * 4);
     p.events = take(L * S * 4 * 4);
     p.step_fills = take(L * 2 * 4);
-    p.bcount = take(2 * N * 4);
-    p.pairs = take(2 * N * S * 4);
+    p.bcount = take(G * N * 4);
+    p.pairs = take(G * N * S * 4);
     p.act = take(S * K * (size_t)c->F * dv.esz);
-    p.yp = take(S * K * (size_t)c->d * dv.esz);
-    p.zero_row = take(N * 4);
+    p.yp = take(G * S * K * (size_t)c->d * dv.esz);
     p.units = take((size_t)max_units(c) * 16);
     p.round_of = take(N * 4);
     p.ws_total = o;
@@ -209,8 +224,38 @@ Plan make_plan(const cmoe_config* c, const Derived& dv) {
     return p;
 }
 
+// The plan with the most layers per batch whose workspace stays within limit
+// bytes (one layer if none does).
+Plan batch_plan(const cmoe_config* c, const Derived& dv, size_t limit) {
+    int lo = 1, hi = std::min(c->L, cmoe::kMaxBatch);
+    while (lo < hi) {  // the workspace grows with G
+        const int m = (lo + hi + 1) / 2;
+        if (make_plan(c, dv, m).ws_total <= limit)
+            lo = m;
+        else
+            hi = m - 1;
+    }
+    return make_plan(c, dv, lo);
+}
+
+// What decides whether a configuration may run on the scratch array: the
+// per-step buffers of one layer at a time with two bucket buffers and 4 or 16
+// partial sums per logit.  The plan of one layer per batch needs no more than
+// this, so a configuration within the limit always has a plan that fits.
+size_t scratch_need(const cmoe_config* c, const Derived& dv) {
+    const size_t S = c->S, L = c->L, N = c->N, K = c->K;
+    const size_t slots = router_splits(c, router_range(c, dv.n_r, 16)) <= 4 ? 4 : 16;
+    size_t o = 0;
+    for (size_t bytes : {S * dv.n_r * N * slots * 8, L * S * dv.n_r * N * 4, L * S * K * 4, L * S * K * 4,
+                         L * S * 16, L * 8, 2 * N * 4, 2 * N * S * 4, S * K * (size_t)c->F * dv.esz,
+                         S * K * (size_t)c->d * dv.esz, N * 4, (size_t)max_units(c) * 16, N * 4})
+        o += align256(bytes);
+    return o;
+}
+
 // Points the workspace members of lo into the buffer wb (nullptr: none).
 void bind_workspace(Layout& lo, char* wb, const Plan& p) {
+    lo.G = p.G;
     auto at = [wb](size_t off) -> char* { return wb ? wb + off : nullptr; };
     lo.zpart = reinterpret_cast<double*>(at(p.zpart));
     lo.logits = reinterpret_cast<float*>(at(p.logits));
@@ -222,7 +267,6 @@ void bind_workspace(Layout& lo, char* wb, const Plan& p) {
     lo.pairs = reinterpret_cast<int32_t*>(at(p.pairs));
     lo.act = at(p.act);
     lo.yp = at(p.yp);
-    lo.zero_row = reinterpret_cast<float*>(at(p.zero_row));
     lo.units = reinterpret_cast<int32_t*>(at(p.units));
     lo.round_of = reinterpret_cast<int32_t*>(at(p.round_of));
 }
@@ -232,19 +276,21 @@ void bind_workspace(Layout& lo, char* wb, const Plan& p) {
 struct cmoe_handle {
     cmoe_config cfg;
     Derived dv;
-    Plan plan;
+    Plan plan;                  // of the caller's workspace
     Layout lo;                  // workspace pointers into the caller's workspace (null if none was given)
     Layout lo_static;           // the same with workspace pointers into the device's scratch array
     const Layout* cur = nullptr;  // the layout of the token being launched
     bool has_ws = false;        // the caller bound a workspace
-    bool scratch_fits = false;  // the workspace plan fits the scratch array
-    bool last_static = false;   // the last token ran on the scratch array
+    size_t scratch_bytes = 0;   // what the scratch array's limit is compared with
+    bool scratch_fits = false;  // the per-step buffers fit the scratch array
+    bool last_static = false;   // the last token ran on the scratch array (views read it)
     int device = 0;
     hipStream_t main = nullptr, side = nullptr;
     bool side_is_main = true;
-    std::vector<hipEvent_t> ev_access, ev_pro;
+    hipEvent_t ev_access = nullptr;  // the batch's cache step (side-stream fills)
+    std::vector<hipEvent_t> ev_pro;  // each layer's proactive fill
     int32_t t = 0;            // next token
-    int64_t g = 0;            // layer steps accessed so far (bucket buffer parity)
+    int64_t g = 0;            // batches run so far (p^S buffer parity)
     std::vector<int> ver;     // current slot-map version of each layer
     std::vector<int32_t> clk; // arena clock of each layer: advances once per fill launch
     int32_t R = 0;
@@ -253,7 +299,11 @@ struct cmoe_handle {
     int32_t prof_left = 0;
     uint32_t prof_mask = 0;
     std::vector<hipEvent_t> prof_pool;
-    std::vector<std::pair<int, size_t>> prof_rec;  // kernel id, index of start event (stop = +1)
+    struct ProfRec {
+        int kid, layers;  // kernel id, layer steps the launch counts for
+        size_t ev;        // index of the start event (stop = +1)
+    };
+    std::vector<ProfRec> prof_rec;
     size_t prof_next = 0;
 };
 
@@ -278,13 +328,14 @@ cmoe_status usable(cmoe_handle* hd) {
 
 // Runs launch(timing): when this kernel is being profiled, timing holds the
 // next start/stop event pair, which the launch attaches to the kernel itself.
+// layers: layer steps the launch counts for.
 template <typename F>
-hipError_t timed(cmoe_handle* hd, int kid, F&& launch) {
+hipError_t timed(cmoe_handle* hd, int kid, int layers, F&& launch) {
     cmoe::Timing tm;
     if (hd->prof_left > 0 && ((hd->prof_mask >> kid) & 1u) && hd->prof_next + 2 <= hd->prof_pool.size()) {
         const size_t i = hd->prof_next;
         hd->prof_next += 2;
-        hd->prof_rec.emplace_back(kid, i);
+        hd->prof_rec.push_back({kid, layers, i});
         tm.start = hd->prof_pool[i];
         tm.stop = hd->prof_pool[i + 1];
     }
@@ -293,17 +344,18 @@ hipError_t timed(cmoe_handle* hd, int kid, F&& launch) {
 
 // The arguments of one residency event of `layer` (or one FFN round of it);
 // advances the layer's slot-map version and arena clock.
-FillArgs event(cmoe_handle* hd, int layer, int kind, bool counted, bool zero_pre, int bbuf = 0, bool units = false,
+FillArgs event(cmoe_handle* hd, int layer, int kind, bool counted, bool zero_pre, int bl = 0, bool units = false,
                int round = 0) {
-    FillArgs f{layer, kind, hd->ver[layer], counted ? 1 : 0, zero_pre ? 1 : 0, bbuf, units ? 1 : 0, round,
+    FillArgs f{layer, kind, hd->ver[layer], counted ? 1 : 0, zero_pre ? 1 : 0, bl, units ? 1 : 0, round,
                ++hd->clk[layer]};
     hd->ver[layer] ^= 1;
     return f;
 }
 
-// One fill launch on stream st: event f, and event g of another layer if given.
-hipError_t fill(cmoe_handle* hd, const FillArgs& f, hipStream_t st, const FillArgs* g = nullptr) {
-    return timed(hd, KID_FILL, [&](const cmoe::Timing& tm) { return cmoe::launch_fill(*hd->cur, f, g, st, tm); });
+// One fill launch on stream st.
+hipError_t fill(cmoe_handle* hd, const FillArgs& f, hipStream_t st) {
+    return timed(hd, KID_FILL, f.kind == 0 ? 1 : 0,
+                 [&](const cmoe::Timing& tm) { return cmoe::launch_fill(*hd->cur, f, nullptr, st, tm); });
 }
 
 // One decode token.  h == nullptr selects injected logits (no router, no FFN).
@@ -315,87 +367,62 @@ cmoe_status run_token(cmoe_handle* hd, const void* h, float* y, const float* zR,
     hd->cur = on_scratch ? &hd->lo_static : &hd->lo;
     const Layout& lo = *hd->cur;
     const bool inject = h == nullptr;
-    const bool refine_on = has_spatio(c.mode) && hd->t >= 1 && hd->R > 0;
+    const bool refine = has_spatio(c.mode) && hd->t >= 1 && hd->R > 0;
     const bool counted = hd->t >= c.warmup_tokens;
-    const uint32_t count = counted ? cmoe::kFlagCount : 0u;
     hipStream_t M = hd->main, Sd = hd->side;
-
-    // A workspace that other calls used last may hold nonzero bucket counts:
-    // the scratch array always (other handles share it), the caller's
-    // workspace after tokens that ran on the scratch array.
-    if (on_scratch || hd->last_static) HIPCHK(cmoe::launch_prep_workspace(lo, M), "workspace preparation");
     hd->last_static = on_scratch;
 
-    if (refine_on) {  // layer 0: refined from the previous token's last-layer prediction
-        StepArgs a{0, 0, hd->R, 0, cmoe::kFlagRefine | count, hd->t, {nullptr, nullptr, nullptr}};
-        HIPCHK(timed(hd, KID_CACHE, [&](const cmoe::Timing& tm) { return cmoe::launch_cache_step(lo, a, M, tm); }),
-               "refine layer 0");
-        if (!hd->side_is_main) {
-            HIPCHK(hipEventRecord(hd->ev_access[0], M), "event record");
-            HIPCHK(hipStreamWaitEvent(Sd, hd->ev_access[0], 0), "stream wait");
-        }
-        HIPCHK(fill(hd, event(hd, 0, 1, counted, false), Sd), "fill");
-        if (!hd->side_is_main) HIPCHK(hipEventRecord(hd->ev_pro[0], Sd), "event record");
-    }
-    for (int l = 0; l < c.L; ++l) {
-        if (!inject)
-            HIPCHK(timed(hd, KID_ROUTER, [&](const cmoe::Timing& tm) { return cmoe::launch_router(lo, l, h, M, tm); }),
+    for (int l0 = 0; l0 < c.L; l0 += lo.G) {
+        const int nl = std::min(lo.G, c.L - l0);
+        if (inject)
+            HIPCHK(cmoe::launch_clear_buckets(lo, nl, M), "bucket counts");
+        else
+            HIPCHK(timed(hd, KID_ROUTER, nl,
+                         [&](const cmoe::Timing& tm) { return cmoe::launch_router(lo, l0, nl, h, M, tm); }),
                    "router");
-        // the proactive fill of this layer reads its refined caches: it must end
-        // before the access below changes them
-        if (refine_on && !hd->side_is_main) HIPCHK(hipStreamWaitEvent(M, hd->ev_pro[l], 0), "stream wait");
-        const bool refine_next = refine_on && l + 1 < c.L;
-        uint32_t flags = cmoe::kFlagAccess | count;
-        if (inject) flags |= cmoe::kFlagInject;
-        if (refine_on) flags |= cmoe::kFlagRefinedHere;
-        if (refine_next) flags |= cmoe::kFlagRefine;
-        const int bbuf = (int)(hd->g & 1);
-        StepArgs a{l, l + 1, hd->R, bbuf, flags, hd->t, {zR, nullptr, nullptr}};
+        StepArgs a{l0, nl, hd->R, (int)(hd->g & 1), 0, hd->t, {zR, nullptr, nullptr}};
+        a.flags = (inject ? cmoe::kFlagInject : 0u) | (refine ? cmoe::kFlagRefine : 0u) | (counted ? cmoe::kFlagCount : 0u);
         if (hd->dv.iT > 0) a.z[hd->dv.iT] = zT;
         if (hd->dv.iS > 0) a.z[hd->dv.iS] = zS;
-        if (!inject && l > 0) {  // the same launch combines layer l - 1's expert outputs
-            a.y = y;
-            a.cl = l - 1;
-        }
-        HIPCHK(timed(hd, KID_CACHE, [&](const cmoe::Timing& tm) { return cmoe::launch_cache_step(lo, a, M, tm); }),
+        HIPCHK(timed(hd, KID_CACHE, nl, [&](const cmoe::Timing& tm) { return cmoe::launch_cache_step(lo, a, M, tm); }),
                "cache step");
         hd->g += 1;
-        // Demand loads gate this layer's FFN; the same launch lays out the FFN
-        // work units.  An arena smaller than the union of the caches runs the
-        // FFN in rounds, each after the fill that brings its experts in.  The
-        // proactive loads of layer l + 1 follow the same cache step: on the
-        // main stream they join the first demand launch; on the side stream
-        // they overlap this layer's FFN.
-        for (int r = 0; r < hd->dv.rounds; ++r) {
-            const FillArgs dem = event(hd, l, 0, counted, r == 0 && !refine_on, bbuf, !inject, r);
-            if (r == 0 && refine_next && hd->side_is_main) {
-                const FillArgs pro = event(hd, l + 1, 1, counted, false);
-                HIPCHK(fill(hd, dem, M, &pro), "fill");
-            } else {
-                HIPCHK(fill(hd, dem, M), "fill");
+        // Proactive loads (what the refinement inserted) come before the
+        // layer's demand loads; on the side stream they overlap the FFNs of
+        // the layers before.
+        if (refine && !hd->side_is_main) {
+            HIPCHK(hipEventRecord(hd->ev_access, M), "event record");
+            HIPCHK(hipStreamWaitEvent(Sd, hd->ev_access, 0), "stream wait");
+            for (int l = l0; l < l0 + nl; ++l) {
+                HIPCHK(fill(hd, event(hd, l, 1, counted, false), Sd), "fill");
+                HIPCHK(hipEventRecord(hd->ev_pro[l], Sd), "event record");
             }
-            if (r == 0 && refine_next && !hd->side_is_main) {
-                HIPCHK(hipEventRecord(hd->ev_access[l], M), "event record");
-                HIPCHK(hipStreamWaitEvent(Sd, hd->ev_access[l], 0), "stream wait");
-                HIPCHK(fill(hd, event(hd, l + 1, 1, counted, false), Sd), "fill");
-                HIPCHK(hipEventRecord(hd->ev_pro[l + 1], Sd), "event record");
-            }
-            if (!inject) {
+        }
+        for (int l = l0; l < l0 + nl; ++l) {
+            const int bl = l - l0;
+            if (refine && hd->side_is_main) HIPCHK(fill(hd, event(hd, l, 1, counted, false), M), "fill");
+            if (refine && !hd->side_is_main) HIPCHK(hipStreamWaitEvent(M, hd->ev_pro[l], 0), "stream wait");
+            // Demand loads gate this layer's FFN; the same launch lays out the
+            // FFN work units.  An arena smaller than the union of the caches
+            // runs the FFN in rounds, each after the fill that brings its
+            // experts in.
+            for (int r = 0; r < hd->dv.rounds; ++r) {
+                HIPCHK(fill(hd, event(hd, l, 0, counted, r == 0 && !refine, bl, !inject, r), M), "fill");
+                if (inject) continue;
                 const int sv = hd->ver[l];
-                HIPCHK(timed(hd, KID_UP,
-                             [&](const cmoe::Timing& tm) {
-                                 return cmoe::launch_ffn_up(lo, l, bbuf, sv, r, h, M, tm);
-                             }),
+                HIPCHK(timed(hd, KID_UP, 1,
+                             [&](const cmoe::Timing& tm) { return cmoe::launch_ffn_up(lo, l, bl, sv, r, h, M, tm); }),
                        "ffn up");
-                HIPCHK(timed(hd, KID_DOWN,
-                             [&](const cmoe::Timing& tm) { return cmoe::launch_ffn_down(lo, l, bbuf, sv, r, M, tm); }),
+                HIPCHK(timed(hd, KID_DOWN, 1,
+                             [&](const cmoe::Timing& tm) { return cmoe::launch_ffn_down(lo, l, bl, sv, r, M, tm); }),
                        "ffn down");
             }
         }
+        if (!inject)
+            HIPCHK(timed(hd, KID_COMBINE, l0 + nl == c.L ? 1 : 0,
+                         [&](const cmoe::Timing& tm) { return cmoe::launch_combine(lo, l0, nl, y, M, tm); }),
+                   "combine");
     }
-    if (!inject)
-        HIPCHK(timed(hd, KID_COMBINE, [&](const cmoe::Timing& tm) { return cmoe::launch_combine(lo, c.L - 1, y, M, tm); }),
-               "combine");
     hd->t += 1;
     if (hd->prof_left > 0) hd->prof_left -= 1;
     return CMOE_OK;
@@ -416,7 +443,7 @@ cmoe_status cmoe_query(const cmoe_config* cfg, cmoe_sizes* out) {
     cmoe_status st = validate(cfg, &dv);
     if (st != CMOE_OK) return st;
     if (!out) return fail(CMOE_ERR_INVALID_ARG, "sizes output is NULL");
-    const Plan p = make_plan(cfg, dv);
+    const Plan p = batch_plan(cfg, dv, kBatchBytes);
     out->arena_bytes = p.arena;
     out->state_bytes = p.state_total;
     out->workspace_bytes = p.ws_total;
@@ -438,10 +465,11 @@ cmoe_status cmoe_init(const cmoe_config* cfg, const cmoe_weights* w, const cmoe_
     if (!buf->arena || !buf->state) return fail(CMOE_ERR_INVALID_ARG, "arena and state buffers are required");
     for (const void* p : {buf->arena, buf->state, buf->workspace})
         if (reinterpret_cast<uintptr_t>(p) & 255) return fail(CMOE_ERR_INVALID_ARG, "buffers must be 256-byte aligned");
-    const Plan plan = make_plan(cfg, dv);
-    if (!buf->workspace && plan.ws_total > kScratchBytes)
+    const Plan plan = batch_plan(cfg, dv, kBatchBytes);
+    const size_t need = scratch_need(cfg, dv);
+    if (!buf->workspace && need > kScratchBytes)
         return fail(CMOE_ERR_UNSUPPORTED, "no workspace given and the per-step buffers (" +
-                                              std::to_string(plan.ws_total) + " bytes) exceed the " +
+                                              std::to_string(need) + " bytes) exceed the " +
                                               std::to_string(kScratchBytes) + "-byte scratch array");
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) {
@@ -482,7 +510,8 @@ cmoe_status cmoe_init(const cmoe_config* cfg, const cmoe_weights* w, const cmoe_
     hd->plan = plan;
     hd->device = device;
     hd->has_ws = buf->workspace != nullptr;
-    hd->scratch_fits = plan.ws_total <= kScratchBytes;
+    hd->scratch_bytes = need;
+    hd->scratch_fits = need <= kScratchBytes;
     hd->R = has_spatio(cfg->mode) ? cfg->R : 0;
     hd->ver.assign(cfg->L, 0);
     hd->clk.assign(cfg->L, 0);
@@ -497,7 +526,7 @@ cmoe_status cmoe_init(const cmoe_config* cfg, const cmoe_weights* w, const cmoe_
     const Plan& p = hd->plan;
     lo.L = cfg->L; lo.N = cfg->N; lo.K = cfg->K; lo.d = cfg->d; lo.F = cfg->F; lo.C = cfg->C; lo.S = cfg->S;
     lo.mode = cfg->mode; lo.dtype = cfg->dtype; lo.NW = dv.NW; lo.n_slots = dv.n_slots; lo.n_r = dv.n_r;
-    lo.nsplit = dv.nsplit; lo.rdk = dv.rdk; lo.zstride = dv.zstride; lo.warmup = cfg->warmup_tokens;
+    lo.nsplit = dv.nsplit; lo.rdk = dv.rdk; lo.warmup = cfg->warmup_tokens;
     lo.iT = dv.iT; lo.iS = dv.iS; lo.policy = cfg->policy;
     lo.lrfu_w = (float)std::pow(2.0, -(double)cfg->lrfu_lambda);
     lo.expert_elems = (int64_t)3 * cfg->d * cfg->F;
@@ -512,6 +541,7 @@ cmoe_status cmoe_init(const cmoe_config* cfg, const cmoe_weights* w, const cmoe_
     lo.aT = reinterpret_cast<float*>(sb + p.aT);
     lo.pol = reinterpret_cast<float*>(sb + p.pol);
     lo.pS = reinterpret_cast<float*>(sb + p.pS);
+    lo.mid = reinterpret_cast<unsigned long long*>(sb + p.mid);
     lo.ctr = reinterpret_cast<int64_t*>(sb + p.ctr);
     lo.phys = reinterpret_cast<int64_t*>(sb + p.phys);
     lo.active_sum = reinterpret_cast<unsigned long long*>(sb + p.active_sum);
@@ -525,17 +555,14 @@ cmoe_status cmoe_init(const cmoe_config* cfg, const cmoe_weights* w, const cmoe_
     lo.unit_tokens = dv.ffn_waves > 1 ? cmoe::kUnitTokensGrouped : cmoe::kUnitTokens;
     hd->lo_static = lo;
     bind_workspace(lo, static_cast<char*>(buf->workspace), p);
-    bind_workspace(hd->lo_static, hd->scratch_fits ? static_cast<char*>(scratch_dev) : nullptr, p);
+    bind_workspace(hd->lo_static, hd->scratch_fits ? static_cast<char*>(scratch_dev) : nullptr,
+                   batch_plan(cfg, dv, kScratchBytes));
     hd->cur = &hd->lo;
 
     auto mk = [&](hipEvent_t* e) { return hipEventCreateWithFlags(e, hipEventDisableTiming); };
-    hd->ev_access.resize(cfg->L);
     hd->ev_pro.resize(cfg->L);
-    hipError_t e = hipSuccess;
-    for (int l = 0; l < cfg->L && e == hipSuccess; ++l) {
-        e = mk(&hd->ev_access[l]);
-        if (e == hipSuccess) e = mk(&hd->ev_pro[l]);
-    }
+    hipError_t e = mk(&hd->ev_access);
+    for (int l = 0; l < cfg->L && e == hipSuccess; ++l) e = mk(&hd->ev_pro[l]);
     if (e == hipSuccess) e = cmoe::launch_init(lo, hd->main);
     if (e == hipSuccess) e = hipStreamSynchronize(hd->main);
     if (e != hipSuccess) {
@@ -559,7 +586,7 @@ cmoe_status cmoe_step_noalloc(cmoe_handle* hd, const void* h, float* y) {
     if (st != CMOE_OK) return st;
     if (!h || !y) return fail(CMOE_ERR_INVALID_ARG, "h and y are required");
     if (!hd->scratch_fits)
-        return fail(CMOE_ERR_UNSUPPORTED, "the per-step buffers (" + std::to_string(hd->plan.ws_total) +
+        return fail(CMOE_ERR_UNSUPPORTED, "the per-step buffers (" + std::to_string(hd->scratch_bytes) +
                                               " bytes) exceed the " + std::to_string(kScratchBytes) +
                                               "-byte scratch array: use cmoe_step with a workspace");
     int device = -1;
@@ -685,7 +712,7 @@ cmoe_status cmoe_destroy(cmoe_handle* hd) {
     auto rm = [](hipEvent_t e) {
         if (e) (void)hipEventDestroy(e);
     };
-    for (auto e : hd->ev_access) rm(e);
+    rm(hd->ev_access);
     for (auto e : hd->ev_pro) rm(e);
     for (auto e : hd->prof_pool) rm(e);
     delete hd;
@@ -778,9 +805,9 @@ cmoe_status cmoe_profile_end(cmoe_handle* hd, double* ms_out, int64_t* launches_
     std::vector<int64_t> n(CMOE_KERNEL_COUNT, 0);
     for (const auto& r : hd->prof_rec) {
         float v = 0.0f;
-        HIPCHK(hipEventElapsedTime(&v, hd->prof_pool[r.second], hd->prof_pool[r.second + 1]), "event elapsed");
-        ms[r.first] += v;
-        n[r.first] += 1;
+        HIPCHK(hipEventElapsedTime(&v, hd->prof_pool[r.ev], hd->prof_pool[r.ev + 1]), "event elapsed");
+        ms[r.kid] += v;
+        n[r.kid] += r.layers;
     }
     if (ms_out) std::memcpy(ms_out, ms.data(), ms.size() * sizeof(double));
     if (launches_out) std::memcpy(launches_out, n.data(), n.size() * sizeof(int64_t));

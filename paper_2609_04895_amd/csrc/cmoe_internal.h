@@ -12,9 +12,9 @@ constexpr int kNctr = 5;          // per (stream, layer) counters: A, hits, D, P
 constexpr int kCtrA = 0, kCtrHits = 1, kCtrD = 2, kCtrP = 3, kCtrT = 4;
 constexpr int kMaxN = 256;        // experts per layer handled by the kernels
 constexpr int kMaxK = 64;         // Top-K handled by the kernels (one lane per selected expert)
-constexpr int kMaxSplit = 16;        // router split-K partials per logit, at most
+constexpr int kMaxSplit = 4;         // router split-K partials per logit, at most
 constexpr int kRouterWaves = 4;      // router: wavefronts per workgroup, one k sub-range each
-constexpr int kStreamsPerBlock = 1;   // cache-step kernel: one wavefront per stream
+constexpr int kMaxBatch = 64;        // layers of one batch (one launch of each phase), at most
 // fill kernel workgroups: copies out of an HBM pool want many loads in
 // flight (512 workgroups copy 2.7 times faster than 128); reads over the
 // host link peak with fewer (128: 56 GB/s, 1024: 47 GB/s)
@@ -26,7 +26,8 @@ constexpr int kUnitTokens = 64, kUnitTokensGrouped = 128;
 
 // Every pointer the kernels use, carved out of the caller's buffers.
 struct Layout {
-    int32_t L, N, K, d, F, C, S, mode, dtype, NW, n_slots, n_r, nsplit, rdk, zstride, warmup;
+    int32_t L, N, K, d, F, C, S, mode, dtype, NW, n_slots, n_r, nsplit, rdk, warmup;
+    int32_t G;             // layers per batch: the per-batch buffers below hold G layers
     int32_t iT, iS;        // router slot of the Temporal / Spatio Router, -1 if not used
     int32_t max_units;     // FFN work units per layer step, at most N + ceil(S K / kUnitTokens)
     int32_t unit_tokens;   // tokens per work unit: kUnitTokens, or kUnitTokensGrouped (grouped launch)
@@ -49,7 +50,9 @@ struct Layout {
     float* aT;                  // [S][L][N]   previous token's a-score: s^T (full mode),
                                 //             p^R (Spatio-only mode)
     float* pol;                 // [S][L][N]   classical retention priority
-    float* pS;                  // [S][N]      latest Spatio Router distribution
+    float* pS;                  // [2][S][N]   Spatio Router distribution of the last layer of the
+                                //             latest two batches (by batch parity)
+    unsigned long long* mid;    // [L][S][NW]  cache membership after the token's refinement
     int64_t* ctr;               // [S][L][kNctr]
     int64_t* phys;              // [L][2]      physical fills: demand, proactive
     unsigned long long* active_sum;  // [L]    distinct experts executed (counted tokens)
@@ -58,17 +61,16 @@ struct Layout {
     int32_t* slot_exp;          // [2][L][n_slots] expert in each slot, -1 free
     int32_t* slot_stamp;        // [2][L][n_slots] arena clock at the last use of each slot's expert
     // workspace
-    double* zpart;              // [S][n_r][N][zstride] router partial sums
+    double* zpart;              // [G][S][n_r][nsplit][N] router partial sums
     float* logits;              // [L][S][n_r][N]
     int32_t* sel;               // [L][S][K]
     float* gates;               // [L][S][K]
     int32_t* events;            // [L][S][4]   hits, D, P, 0 of the last token
     int32_t* step_fills;        // [L][2]      physical fills of the last token
-    int32_t* bcount;            // [2][N]      tokens per expert (two buffers)
-    int32_t* pairs;             // [2][N][S]   (stream << 8) | k of each token of an expert
+    int32_t* bcount;            // [G][N]      tokens per expert
+    int32_t* pairs;             // [G][N][S]   (stream << 8) | k of each token of an expert
     void* act;                  // [S][K][F]   SwiGLU intermediate (dtype)
-    void* yp;                   // [S][K][d]   gated expert outputs (dtype)
-    float* zero_row;            // [N]         zeros (native bias when there is none)
+    void* yp;                   // [G][S][K][d] gated expert outputs (dtype)
     int32_t* units;             // [max_units][4] FFN work units of the current round, heaviest
                                 //             first: {(pass << 8) | expert, slot, tokens, 0},
                                 //             {-1, -1, 0, 0} past the end
@@ -77,22 +79,18 @@ struct Layout {
 };
 
 // cache-step kernel flags
-constexpr uint32_t kFlagAccess = 1u;       // route, access, retention for layer l
-constexpr uint32_t kFlagInject = 2u;       // logits come from the caller
-constexpr uint32_t kFlagRefine = 4u;       // refine layer `rl` (modes with a Spatio Router)
-constexpr uint32_t kFlagRefinedHere = 8u;  // layer l was refined earlier this token
-constexpr uint32_t kFlagCount = 16u;       // this token is counted
+constexpr uint32_t kFlagInject = 1u;  // logits come from the caller
+constexpr uint32_t kFlagRefine = 2u;  // refine each layer before its access (modes with a Spatio Router)
+constexpr uint32_t kFlagCount = 4u;   // this token is counted
 
+// The cache step of layers l0 .. l0 + nl - 1 (one batch).
 struct StepArgs {
-    int32_t l;          // layer accessed (kFlagAccess)
-    int32_t rl;         // layer refined (kFlagRefine)
+    int32_t l0, nl;
     int32_t R;          // refinement budget
-    int32_t bbuf;       // bucket buffer of this layer step (the other one is cleared)
+    int32_t psw;        // pS buffer this batch writes (it reads the other one)
     uint32_t flags;
     int32_t t;          // token index (LRU clock)
     const float* z[3];  // injected logits [S][L][N] per router slot (kFlagInject)
-    float* y;           // non-NULL: the launch also combines layer cl's expert outputs into y
-    int32_t cl;
 };
 
 // One residency event of layer `layer` (or one round of it): the arena must
@@ -105,7 +103,7 @@ struct FillArgs {
     int32_t rv;
     int32_t counted;
     int32_t zero_pre;    // kind 0: no refinement happened this token, clear its fill count
-    int32_t bbuf;        // kind 0: bucket buffer of the layer step (its counts give the executed experts)
+    int32_t bl;          // the layer's index in its batch
     int32_t units;       // kind 0: lay out the FFN work units of this round
     int32_t round;       // kind 0: FFN round of the layer step (0 plans the rounds)
     int32_t clk;         // arena clock of this launch: the last use it stamps
@@ -128,17 +126,19 @@ inline void launch_kernel(void (*kernel)(KArgs...), dim3 grid, dim3 block, hipSt
 }
 
 hipError_t launch_init(const Layout& lo, hipStream_t st);  // state, and the workspace if bound
-hipError_t launch_prep_workspace(const Layout& lo, hipStream_t st);
-hipError_t launch_router(const Layout& lo, int l, const void* h, hipStream_t st, const Timing& tm = {});
+hipError_t launch_clear_buckets(const Layout& lo, int nl, hipStream_t st);
+// router logits of layers l0 .. l0 + nl - 1; also zeroes the batch's bucket counts
+hipError_t launch_router(const Layout& lo, int l0, int nl, const void* h, hipStream_t st, const Timing& tm = {});
 hipError_t launch_cache_step(const Layout& lo, const StepArgs& a, hipStream_t st, const Timing& tm = {});
 // g (or NULL): a second event of another layer in the same launch
 hipError_t launch_fill(const Layout& lo, const FillArgs& f, const FillArgs* g, hipStream_t st,
                        const Timing& tm = {});
-hipError_t launch_ffn_up(const Layout& lo, int l, int bbuf, int sv, int round, const void* h, hipStream_t st,
+hipError_t launch_ffn_up(const Layout& lo, int l, int bl, int sv, int round, const void* h, hipStream_t st,
                          const Timing& tm = {});
-hipError_t launch_ffn_down(const Layout& lo, int l, int bbuf, int sv, int round, hipStream_t st,
+hipError_t launch_ffn_down(const Layout& lo, int l, int bl, int sv, int round, hipStream_t st,
                            const Timing& tm = {});
-hipError_t launch_combine(const Layout& lo, int l, float* y, hipStream_t st, const Timing& tm = {});
+// the combine of layers l0 .. l0 + nl - 1
+hipError_t launch_combine(const Layout& lo, int l0, int nl, float* y, hipStream_t st, const Timing& tm = {});
 // streaming read of per_wave 16-byte units by each wavefront of the probe
 // grid; read_probe_units_per_wave gives the largest per_wave that fits in
 // `bytes` and the bytes the grid then reads

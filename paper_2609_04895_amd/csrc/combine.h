@@ -1,8 +1,6 @@
-// combine.h - the gated combine of one layer's expert outputs, as a device
-// function: y[s][l] = sum over k of the gated outputs yp[s][k] (the gates
-// are already applied by the down projection), added in k order in fp32.
-// Used by the stand-alone combine kernel and by the cache-step launch of the
-// next layer, which runs it in workgroups of its own.
+// combine.h - the gated combine of expert outputs, as a device function:
+// y[s][l] = sum over k of the gated outputs yp[s][k] (the gates are already
+// applied by the down projection), added in k order in fp32.
 #pragma once
 
 #include <type_traits>
@@ -27,10 +25,10 @@ struct Quad {
 };
 
 template <bool BF16>
-__device__ inline void combine_quad_t(const Layout& lo, int l, float* __restrict__ y, int s, int c) {
+__device__ inline void combine_quad_t(const Layout& lo, int l, int bl, float* __restrict__ y, int s, int c) {
     using Raw = typename Quad<BF16>::Raw;
     const int n4 = lo.d / 4;
-    const Raw* yp = reinterpret_cast<const Raw*>(lo.yp) + (int64_t)s * lo.K * n4 + c;
+    const Raw* yp = reinterpret_cast<const Raw*>(lo.yp) + ((int64_t)bl * lo.S + s) * lo.K * n4 + c;
     // Batches of 8 outputs: every load of a batch (indices clamped to K - 1;
     // a clamped re-read is not added) is issued before the adds, which run
     // in k order, in fp32.
@@ -57,20 +55,20 @@ __device__ inline void combine_quad_t(const Layout& lo, int l, float* __restrict
     reinterpret_cast<float4*>(y + ((int64_t)s * lo.L + l) * lo.d)[c] = acc;
 }
 
-// Thread `idx` of the combine grid: four consecutive outputs of one stream.
+// Thread `idx` of layer l (number bl of its batch): four consecutive outputs of one stream.
 // Threads past S d / 4 do nothing.  The gated outputs are stored in the
 // compute dtype (bf16 or fp32).
-__device__ inline void combine_quad(const Layout& lo, int l, float* __restrict__ y, int64_t idx) {
+__device__ inline void combine_quad(const Layout& lo, int l, int bl, float* __restrict__ y, int64_t idx) {
     const int n4 = lo.d / 4;
     if (idx >= (int64_t)lo.S * n4) return;
     const int s = (int)(idx / n4), c = (int)(idx - (int64_t)s * n4);
     if (lo.dtype == 1)
-        combine_quad_t<true>(lo, l, y, s, c);
+        combine_quad_t<true>(lo, l, bl, y, s, c);
     else
-        combine_quad_t<false>(lo, l, y, s, c);
+        combine_quad_t<false>(lo, l, bl, y, s, c);
 }
 
-// Workgroups of the combine grid: S d / 4 threads, kCombineThreads each.
+// Workgroups of one layer: S d / 4 threads, kCombineThreads each.
 inline int64_t combine_groups(const Layout& lo) {
     return ((int64_t)lo.S * (lo.d / 4) + kCombineThreads - 1) / kCombineThreads;
 }

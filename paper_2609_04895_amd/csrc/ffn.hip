@@ -80,8 +80,8 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
 // Gated output of (stream s, slot k) at d-rows j .. j + 3 (c0) and
 // j + 16 .. j + 19 (c1), rounded to bf16 like the SwiGLU intermediate: the
 // combine adds them in fp32.
-__device__ inline void store_gated(const Layout& lo, int s, int k, int j, float gk, const f32x4& c0, const f32x4& c1) {
-    uint16_t* dst = reinterpret_cast<uint16_t*>(lo.yp) + ((int64_t)s * lo.K + k) * lo.d + j;
+__device__ inline void store_gated(const Layout& lo, int bl, int s, int k, int j, float gk, const f32x4& c0, const f32x4& c1) {
+    uint16_t* dst = reinterpret_cast<uint16_t*>(lo.yp) + (((int64_t)bl * lo.S + s) * lo.K + k) * lo.d + j;
     *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16x2(gk * c0[0], gk * c0[1]), pack_bf16x2(gk * c0[2], gk * c0[3]));
     *reinterpret_cast<uint2*>(dst + 16) =
         make_uint2(pack_bf16x2(gk * c1[0], gk * c1[1]), pack_bf16x2(gk * c1[2], gk * c1[3]));
@@ -441,7 +441,7 @@ __device__ __forceinline__ void up_heavy_wide(const Layout& lo, int l, int ft, c
 // multiple of 64, so every wavefront has a tile).  W = 1: every wavefront
 // on its own; W = kWaves: grouped.
 template <int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void ffn_up_bf16(Layout lo, int l, int bbuf, int /*sv: slots come with the units*/,
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void ffn_up_bf16(Layout lo, int l, int bl, int /*sv: slots come with the units*/,
                                                       const uint16_t* __restrict__ h) {
     const int wgn = lo.F / (16 * W);
     int u, j;
@@ -453,7 +453,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
     if (ui.x < 0) return;
     const int e = ui.x & 255, t0 = lo.unit_tokens * (ui.x >> 8), slot = ui.y, m = ui.z;
     if (m <= 0 || slot < 0 || slot >= lo.n_slots) return;
-    const int32_t* bk = lo.pairs + ((int64_t)bbuf * lo.N + e) * lo.S + t0;
+    const int32_t* bk = lo.pairs + ((int64_t)bl * lo.N + e) * lo.S + t0;
     // packed slot layout: chunk c of this row tile is 256 units of 16 bytes,
     // gate half 0, gate half 1, up half 0, up half 1, each 64 units
     const uint4* tileA =
@@ -472,7 +472,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
 }
 
 template <int NG, int U>
-__device__ inline void down_passes(const Layout& lo, int l, int dt, const int32_t* __restrict__ bk, int m,
+__device__ inline void down_passes(const Layout& lo, int l, int bl, int dt, const int32_t* __restrict__ bk, int m,
                                    const uint4* __restrict__ tileB, int lane) {
     const int r = lane & 15, g = lane >> 4;
     const int F = lo.F;
@@ -494,7 +494,7 @@ __device__ inline void down_passes(const Layout& lo, int l, int dt, const int32_
             if (tok < m) {
                 const int s = pr[q] >> 8, k = pr[q] & 255;
                 const float gk = lo.gates[((int64_t)l * lo.S + s) * lo.K + k];
-                store_gated(lo, s, k, dt * 32 + 4 * g, gk, c0[q], c1[q]);
+                store_gated(lo, bl, s, k, dt * 32 + 4 * g, gk, c0[q], c1[q]);
             }
         }
     }
@@ -504,7 +504,7 @@ __device__ inline void down_passes(const Layout& lo, int l, int dt, const int32_
 // the SwiGLU intermediate shared by the workgroup.  Wavefronts past the last
 // d-tile (d not a multiple of 32 W) take part in the staging and barriers
 // only.
-__device__ inline void down_heavy(const Layout& lo, int l, int dt, bool active, const int32_t* __restrict__ bk, int m,
+__device__ inline void down_heavy(const Layout& lo, int l, int bl, int dt, bool active, const int32_t* __restrict__ bk, int m,
                                   const uint4* __restrict__ tileB, int tid, HeavyLds<kUnrollWide>& sm) {
     const int lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int F = lo.F;
@@ -524,14 +524,14 @@ __device__ inline void down_heavy(const Layout& lo, int l, int dt, bool active, 
         if (tok < m) {
             const int s = pr[q] >> 8, k = pr[q] & 255;
             const float gk = lo.gates[((int64_t)l * lo.S + s) * lo.K + k];
-            store_gated(lo, s, k, dt * 32 + 4 * g, gk, c0[q], c1[q]);
+            store_gated(lo, bl, s, k, dt * 32 + 4 * g, gk, c0[q], c1[q]);
         }
     }
 }
 
 // A unit of 65 to kUnitTokensGrouped tokens in the grouped launch: one pass,
 // eight token groups, the SwiGLU intermediate shared by the workgroup.
-__device__ __forceinline__ void down_heavy_wide(const Layout& lo, int l, int dt, bool active, const int32_t* __restrict__ bk,
+__device__ __forceinline__ void down_heavy_wide(const Layout& lo, int l, int bl, int dt, bool active, const int32_t* __restrict__ bk,
                                        int m, const uint4* __restrict__ tileB, int tid, WideLds& sm) {
     const int lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int F = lo.F, q0 = 4 * (tid >> 7);
@@ -552,14 +552,14 @@ __device__ __forceinline__ void down_heavy_wide(const Layout& lo, int l, int dt,
             const int pair = bk[tok];
             const int s = pair >> 8, k = pair & 255;
             const float gk = lo.gates[((int64_t)l * lo.S + s) * lo.K + k];
-            store_gated(lo, s, k, dt * 32 + 4 * g, gk, c0[q], c1[q]);
+            store_gated(lo, bl, s, k, dt * 32 + 4 * g, gk, c0[q], c1[q]);
         }
     }
 }
 
 // Workgroup (u, j): the W 32-row d-tiles W j + wavefront of unit u.
 template <int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void ffn_down_bf16(Layout lo, int l, int bbuf, int /*sv: slots come with the units*/) {
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void ffn_down_bf16(Layout lo, int l, int bl, int /*sv: slots come with the units*/) {
     const int dtn = lo.d / 32;
     const int wgn = (dtn + W - 1) / W;
     int u, j;
@@ -572,33 +572,33 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
     if (ui.x < 0) return;
     const int e = ui.x & 255, t0 = lo.unit_tokens * (ui.x >> 8), slot = ui.y, m = ui.z;
     if (m <= 0 || slot < 0 || slot >= lo.n_slots) return;
-    const int32_t* bk = lo.pairs + ((int64_t)bbuf * lo.N + e) * lo.S + t0;
+    const int32_t* bk = lo.pairs + ((int64_t)bl * lo.N + e) * lo.S + t0;
     // packed slot layout: after the gate/up part (F d / 4 units), chunk c of
     // this 32-row tile is 256 units: rows 0-15 half 0, half 1, rows 16-31
     // half 0, half 1, each 64 units
     const uint4* tileB = reinterpret_cast<const uint4*>(slot_base(lo, l, slot)) + (int64_t)lo.F * lo.d / 4 +
                          (int64_t)(active ? dt : 0) * (lo.F / 64) * 256 + lane;
     if (m <= 16) {  // workgroup-uniform; this path has no barriers
-        if (active) down_passes<1, kUnroll>(lo, l, dt, bk, m, tileB, lane);
+        if (active) down_passes<1, kUnroll>(lo, l, bl, dt, bk, m, tileB, lane);
     } else if constexpr (W == 1) {
-        down_passes<kNG, kUnrollSolo>(lo, l, dt, bk, m, tileB, lane);
+        down_passes<kNG, kUnrollSolo>(lo, l, bl, dt, bk, m, tileB, lane);
     } else {
         __shared__ GroupedLds sm;
         if (m <= 16 * kNG)
-            down_heavy(lo, l, dt, active, bk, m, tileB, threadIdx.x, sm.narrow);
+            down_heavy(lo, l, bl, dt, active, bk, m, tileB, threadIdx.x, sm.narrow);
         else
-            down_heavy_wide(lo, l, dt, active, bk, m, tileB, threadIdx.x, sm.wide);
+            down_heavy_wide(lo, l, bl, dt, active, bk, m, tileB, threadIdx.x, sm.wide);
     }
 }
 
 // ---------------------------------------------------------------- fp32
-__global__ __launch_bounds__(64) void ffn_up_f32(Layout lo, int l, int bbuf, int sv, int round,
+__global__ __launch_bounds__(64) void ffn_up_f32(Layout lo, int l, int bl, int sv, int round,
                                                  const float* __restrict__ h) {
     const int ftn = lo.F / 64;
     const int e = blockIdx.x / ftn, ft = blockIdx.x - e * ftn;
-    const int m = lo.bcount[(int64_t)bbuf * lo.N + e];
+    const int m = lo.bcount[(int64_t)bl * lo.N + e];
     if (m == 0 || lo.round_of[e] != round) return;
-    const int32_t* bk = lo.pairs + ((int64_t)bbuf * lo.N + e) * lo.S;
+    const int32_t* bk = lo.pairs + ((int64_t)bl * lo.N + e) * lo.S;
     const int slot = lo.slot_of[((int64_t)sv * lo.L + l) * lo.N + e];
     if (slot < 0 || slot >= lo.n_slots) return;
     // transposed in the slot (the fill writes W_gate^T, W_up^T as [d][F]):
@@ -630,12 +630,12 @@ __global__ __launch_bounds__(64) void ffn_up_f32(Layout lo, int l, int bbuf, int
     }
 }
 
-__global__ __launch_bounds__(64) void ffn_down_f32(Layout lo, int l, int bbuf, int sv, int round) {
+__global__ __launch_bounds__(64) void ffn_down_f32(Layout lo, int l, int bl, int sv, int round) {
     const int dtn = lo.d / 64;
     const int e = blockIdx.x / dtn, dt = blockIdx.x - e * dtn;
-    const int m = lo.bcount[(int64_t)bbuf * lo.N + e];
+    const int m = lo.bcount[(int64_t)bl * lo.N + e];
     if (m == 0 || lo.round_of[e] != round) return;
-    const int32_t* bk = lo.pairs + ((int64_t)bbuf * lo.N + e) * lo.S;
+    const int32_t* bk = lo.pairs + ((int64_t)bl * lo.N + e) * lo.S;
     const int slot = lo.slot_of[((int64_t)sv * lo.L + l) * lo.N + e];
     if (slot < 0 || slot >= lo.n_slots) return;
     // W_down^T [F][d] in the slot: lanes (rows j) read consecutive floats
@@ -659,38 +659,38 @@ __global__ __launch_bounds__(64) void ffn_down_f32(Layout lo, int l, int bbuf, i
             for (int u = 0; u < 32; ++u) acc = __builtin_fmaf(wd[u], a32[u], acc);
         }
         const float gk = lo.gates[((int64_t)l * lo.S + s) * lo.K + k];
-        reinterpret_cast<float*>(lo.yp)[((int64_t)s * lo.K + k) * lo.d + j] = gk * acc;
+        reinterpret_cast<float*>(lo.yp)[(((int64_t)bl * lo.S + s) * lo.K + k) * lo.d + j] = gk * acc;
     }
 }
 
 }  // namespace
 
-hipError_t launch_ffn_up(const Layout& lo, int l, int bbuf, int sv, int round, const void* h, hipStream_t st,
+hipError_t launch_ffn_up(const Layout& lo, int l, int bl, int sv, int round, const void* h, hipStream_t st,
                          const Timing& tm) {
     if (lo.dtype == 1) {
         const uint16_t* hb = static_cast<const uint16_t*>(h);
         if (lo.ffn_waves == kWaves)
             launch_kernel(ffn_up_bf16<kWaves>, dim3(unit_groups(lo) * (lo.F / (16 * kWaves))), dim3(64 * kWaves), st, tm,
-                          lo, l, bbuf, sv, hb);
+                          lo, l, bl, sv, hb);
         else
-            launch_kernel(ffn_up_bf16<1>, dim3(unit_groups(lo) * (lo.F / 16)), dim3(64), st, tm, lo, l, bbuf, sv, hb);
+            launch_kernel(ffn_up_bf16<1>, dim3(unit_groups(lo) * (lo.F / 16)), dim3(64), st, tm, lo, l, bl, sv, hb);
     } else {
-        launch_kernel(ffn_up_f32, dim3(lo.N * (lo.F / 64)), dim3(64), st, tm, lo, l, bbuf, sv, round,
+        launch_kernel(ffn_up_f32, dim3(lo.N * (lo.F / 64)), dim3(64), st, tm, lo, l, bl, sv, round,
                       static_cast<const float*>(h));
     }
     return hipGetLastError();
 }
 
-hipError_t launch_ffn_down(const Layout& lo, int l, int bbuf, int sv, int round, hipStream_t st, const Timing& tm) {
+hipError_t launch_ffn_down(const Layout& lo, int l, int bl, int sv, int round, hipStream_t st, const Timing& tm) {
     if (lo.dtype == 1) {
         const int dtn = lo.d / 32;
         if (lo.ffn_waves == kWaves)
             launch_kernel(ffn_down_bf16<kWaves>, dim3(unit_groups(lo) * ((dtn + kWaves - 1) / kWaves)), dim3(64 * kWaves),
-                          st, tm, lo, l, bbuf, sv);
+                          st, tm, lo, l, bl, sv);
         else
-            launch_kernel(ffn_down_bf16<1>, dim3(unit_groups(lo) * dtn), dim3(64), st, tm, lo, l, bbuf, sv);
+            launch_kernel(ffn_down_bf16<1>, dim3(unit_groups(lo) * dtn), dim3(64), st, tm, lo, l, bl, sv);
     } else {
-        launch_kernel(ffn_down_f32, dim3(lo.N * (lo.d / 64)), dim3(64), st, tm, lo, l, bbuf, sv, round);
+        launch_kernel(ffn_down_f32, dim3(lo.N * (lo.d / 64)), dim3(64), st, tm, lo, l, bl, sv, round);
     }
     return hipGetLastError();
 }

@@ -151,8 +151,10 @@ __device__ inline int64_t packed_of_source(int64_t i, int d, int F) {
     return 2 * nA + b * 128 + packed_dest_in_block(((row & 15) << 3) | (u & 7));
 }
 
-// Cache word i = s NW + j: word j of stream s's membership bits of the layer.
-__device__ inline unsigned long long cache_word(const Layout& lo, int layer, int i) {
+// Cache word i = s NW + j: word j of stream s's membership bits of the layer,
+// after the refinement (kind 1) or the access (kind 0).
+__device__ inline unsigned long long cache_word(const Layout& lo, int layer, int kind, int i) {
+    if (kind == 1) return lo.mid[(int64_t)layer * lo.S * lo.NW + i];
     const int s = i / lo.NW, j = i - s * lo.NW;
     return lo.cache[((int64_t)s * lo.L + layer) * lo.NW + j];
 }
@@ -191,14 +193,14 @@ __device__ __forceinline__ void residency_event(const Layout& lo, const FillArgs
     const int so_v = so_in[min(tid, N - 1)];
     const int se_v = se_in[min(tid, P - 1)];
     const int st_v = st_in[min(tid, P - 1)];
-    const int mb_v = lo.bcount[(int64_t)f.bbuf * N + min(tid, N - 1)];
+    const int mb_v = lo.bcount[(int64_t)f.bl * N + min(tid, N - 1)];
     const int ro_v = lo.round_of[min(tid, N - 1)];
     const int64_t phys_v = lo.phys[layer * 2 + f.kind];
     const int32_t sf_v = lo.step_fills[layer * 2];
     constexpr int kWords = 4;  // cache words per thread per batch
     unsigned long long w[kWords];
 #pragma unroll
-    for (int u = 0; u < kWords; ++u) w[u] = cache_word(lo, layer, min(tid + u * kFillThreads, S_NW - 1));
+    for (int u = 0; u < kWords; ++u) w[u] = cache_word(lo, layer, f.kind, min(tid + u * kFillThreads, S_NW - 1));
     __builtin_amdgcn_sched_barrier(0);
     if (tid < 4) U[tid] = 0ull;
     if (tid < N) so[tid] = so_v;
@@ -211,7 +213,7 @@ __device__ __forceinline__ void residency_event(const Layout& lo, const FillArgs
         if (i0 > 0) {
 #pragma unroll
             for (int u = 0; u < kWords; ++u)
-                w[u] = cache_word(lo, layer, min(i0 + tid + u * kFillThreads, S_NW - 1));
+                w[u] = cache_word(lo, layer, f.kind, min(i0 + tid + u * kFillThreads, S_NW - 1));
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll

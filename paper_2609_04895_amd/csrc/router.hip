@@ -1,6 +1,6 @@
 // router.hip - router logits z = W h for the native, Temporal and Spatio
-// routers of one layer (Section 2: W^R h; Section 3.2: W^T h; Section 3.3:
-// W^S h), all streams at once.
+// routers of a batch of layers (Section 2: W^R h; Section 3.2: W^T h; Section
+// 3.3: W^S h), all streams at once.
 //
 // The logits decide expert selection and cache priorities, so they are
 // summed in fp64 and rounded to fp32 once (after the bias), like the plain
@@ -92,11 +92,11 @@ __device__ inline void mfma_batch(const Raw8<BF16>* ra, const Raw8<BF16>* rb, in
     }
 }
 
-// grid: x = n_r * ceil(N/16) * ceil(S/16), z = nsplit; block: kRouterWaves
-// wavefronts; KB = k chunks whose loads are issued together (at most the
+// grid: x = n_r * ceil(N/16) * ceil(S/16), y = layers of the batch, z = nsplit;
+// block: kRouterWaves wavefronts; KB = k chunks whose loads are issued together (at most the
 // chunks of a wavefront's range)
 template <bool BF16, int KB>
-__global__ __launch_bounds__(64 * kRouterWaves) void router_kernel(Layout lo, int l, const void* h, int dk) {
+__global__ __launch_bounds__(64 * kRouterWaves) void router_kernel(Layout lo, int l0, const void* h, int dk) {
     __shared__ f64x4 red[kRouterWaves - 1][64];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int r16 = lane & 15, g = lane >> 4;
@@ -106,7 +106,9 @@ __global__ __launch_bounds__(64 * kRouterWaves) void router_kernel(Layout lo, in
     b /= st_n;
     const int et = b % et_n;
     const int r = b / et_n;
-    const int p = blockIdx.z;
+    const int p = blockIdx.z, bl = blockIdx.y, l = l0 + bl;
+    if (blockIdx.x == 0 && p == 0)  // the cache step counts the layer's buckets from zero
+        for (int i = threadIdx.x; i < lo.N; i += 64 * kRouterWaves) lo.bcount[(int64_t)bl * lo.N + i] = 0;
     const int i0 = (p * kRouterWaves + wv) * dk;
     const int nch = i0 < lo.d ? (min(i0 + dk, lo.d) - i0) / 32 : 0;  // 32-wide k chunks of this wavefront
 
@@ -140,24 +142,23 @@ __global__ __launch_bounds__(64 * kRouterWaves) void router_kernel(Layout lo, in
     }
     // Output of the fp64 16x16x4 MFMA: lane (r16, g) holds D[g + 4 q][r16] in
     // acc[q], i.e. expert row g + 4 q of the tile, stream column r16.  The
-    // partial of split p goes to zpart[s][r][e][p] (p padded to zstride): the
-    // splits of one logit are contiguous for the cache-step kernel, which adds
-    // them in order.
+    // partial of split p goes to zpart[bl][s][r][p][e]: the cache-step kernel,
+    // one expert per lane, reads each split's row in order.
     const int s = st * 16 + r16;
     if (s < lo.S) {
-        double* out = lo.zpart + ((int64_t)s * lo.n_r + r) * lo.N * lo.zstride + p;
+        double* out = lo.zpart + ((((int64_t)bl * lo.S + s) * lo.n_r + r) * lo.nsplit + p) * lo.N;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int e = et * 16 + g + 4 * q;
-            if (e < lo.N) out[(int64_t)e * lo.zstride] = acc[q];
+            if (e < lo.N) out[e] = acc[q];
         }
     }
 }
 
 template <bool BF16>
-static void launch_router_t(const Layout& lo, int l, const void* h, hipStream_t st, const Timing& tm) {
+static void launch_router_t(const Layout& lo, int l, int nl, const void* h, hipStream_t st, const Timing& tm) {
     const int dk = lo.rdk;  // multiple of 32; the last split may be shorter (d % 32 == 0)
-    const dim3 grid(lo.n_r * ((lo.N + 15) / 16) * ((lo.S + 15) / 16), 1, lo.nsplit);
+    const dim3 grid(lo.n_r * ((lo.N + 15) / 16) * ((lo.S + 15) / 16), nl, lo.nsplit);
     const dim3 block(64 * kRouterWaves);
     const int cpw = dk / 32;  // k chunks per wavefront
     if (cpw >= 4)
@@ -168,11 +169,11 @@ static void launch_router_t(const Layout& lo, int l, const void* h, hipStream_t 
         launch_kernel(router_kernel<BF16, 1>, grid, block, st, tm, lo, l, h, dk);
 }
 
-hipError_t launch_router(const Layout& lo, int l, const void* h, hipStream_t st, const Timing& tm) {
+hipError_t launch_router(const Layout& lo, int l0, int nl, const void* h, hipStream_t st, const Timing& tm) {
     if (lo.dtype == 1)
-        launch_router_t<true>(lo, l, h, st, tm);
+        launch_router_t<true>(lo, l0, nl, h, st, tm);
     else
-        launch_router_t<false>(lo, l, h, st, tm);
+        launch_router_t<false>(lo, l0, nl, h, st, tm);
     return hipGetLastError();
 }
 
