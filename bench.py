@@ -72,7 +72,7 @@ def describe(w):
 def fills_label(w, fills):
     if not w.has_spatio or w.R == 0:
         return "none (no refinement)"
-    return "side stream" if fills == "side" else "main stream, in the demand fill launch"
+    return "side stream" if fills == "side" else "main stream, before the demand fills"
 
 
 def cpu_baseline(w, budget_s, max_procs=16):

@@ -91,10 +91,10 @@ typedef enum {
 } cmoe_pool_kind;
 
 /* flags.  Demand fills always run on the main stream: they gate the layer's
- * FFN.  The proactive fills of layer l + 1 follow layer l's cache step: by
- * default they join layer l's demand fill launch on the main stream; with
- * CMOE_FLAG_FILL_ON_SIDE (and a side stream) they run on the side stream,
- * overlapping layer l's FFN.  Both flags: CMOE_ERR_INVALID_ARG. */
+ * FFN.  The proactive fills of a layer come before its demand fills: by default
+ * in a launch on the main stream; with CMOE_FLAG_FILL_ON_SIDE (and a side
+ * stream) they run on the side stream, overlapping the FFNs of the layers
+ * before.  Both flags: CMOE_ERR_INVALID_ARG. */
 #define CMOE_FLAG_FILL_ON_MAIN 0x1u /* proactive fills on the main stream (the default)      */
 #define CMOE_FLAG_FILL_ON_SIDE 0x8u /* proactive fills on the side stream                    */
 /* bf16 expert FFN launch shape.  Single: one wavefront per workgroup, each on

@@ -29,7 +29,7 @@
 //
 // The same kernel groups the layer's (stream, k) selections by expert for the
 // FFN (fixed-capacity buckets filled with integer atomics) and counts the
-// distinct experts executed.  Physical residency is handled by the fill
+// distinct experts executed.  Physical residency is handled by the residency
 // kernel.
 //
 // Fixed fp32 softmax: m = max z; u_e = exp(z_e - m) with the exponential
@@ -629,8 +629,8 @@ __global__ void init_kernel(Layout lo) {
     for (int64_t i = gid; i < (int64_t)lo.L * 2; i += gs) lo.phys[i] = 0;
     for (int64_t i = gid; i < lo.L; i += gs) lo.active_sum[i] = 0ull;
     for (int64_t i = gid; i < (int64_t)lo.L * lo.N; i += gs) lo.selcount[i] = 0ull;
-    for (int64_t i = gid; i < (int64_t)2 * lo.L * lo.N; i += gs) lo.slot_of[i] = -1;
-    for (int64_t i = gid; i < (int64_t)2 * lo.L * lo.n_slots; i += gs) {
+    for (int64_t i = gid; i < (int64_t)lo.L * lo.N; i += gs) lo.slot_of[i] = -1;
+    for (int64_t i = gid; i < (int64_t)lo.L * lo.n_slots; i += gs) {
         lo.slot_exp[i] = -1;
         lo.slot_stamp[i] = 0;
     }

@@ -9,11 +9,12 @@
 //   for each batch of layers:
 //     main: router GEMV (batch)
 //     main: cache step (batch): refinement, access, retention, counters, buckets
-//     for each layer l:
-//       main: fill(l, demand)  -- gates the FFN of this layer
-//       [refining] main or side: fill(l, proactive), before it
-//       main: expert gate/up(l), expert down(l)
+//     main: residency events (batch): slot maps, copy lists, FFN work units
+//     main: proactive copies (batch, if refining), demand copies (batch)
+//     for each layer l, main: expert gate/up(l), expert down(l)
 //     main: combine (batch)
+// With proactive fills on the side stream, each layer's proactive copies run
+// there, and its demand copies on the main stream just before its FFN.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -27,8 +28,8 @@
 #include "../../include/cmoe.h"
 #include "cmoe_internal.h"
 
-using cmoe::FillArgs;
 using cmoe::Layout;
+using cmoe::ResidencyArgs;
 using cmoe::StepArgs;
 
 // Per-step scratch of cmoe_step_noalloc, for callers that cannot allocate a
@@ -173,13 +174,19 @@ cmoe_status validate(const cmoe_config* c, Derived* dv) {
 // Offsets of every sub-buffer; used both for sizing and for carving.
 struct Plan {
     int G;  // layers per batch
-    size_t cache, aT, pol, pS, mid, ctr, phys, active_sum, selcount, slot_of, slot_exp, slot_stamp, state_total;
+    size_t cache, aT, pol, pS, mid, ctr, phys, active_sum, selcount, slot_of, slot_exp, slot_stamp, copy_list, copy_n;
+    size_t state_total;
     size_t zpart, logits, sel, gates, events, step_fills, bcount, pairs, act, yp, units, round_of, ws_total;
     size_t arena;
 };
 
-int max_units(const cmoe_config* c) {
-    return c->N + (int)(((int64_t)c->S * c->K + cmoe::kUnitTokens - 1) / cmoe::kUnitTokens);
+int unit_tokens(const Derived& dv) { return dv.ffn_waves > 1 ? cmoe::kUnitTokensGrouped : cmoe::kUnitTokens; }
+
+// FFN work units of a layer step, at most: one for each executed expert, and
+// one more for each full unit of tokens.
+int max_units(const cmoe_config* c, const Derived& dv) {
+    const int64_t tokens = (int64_t)c->S * c->K;
+    return (int)(std::min<int64_t>(c->N, tokens) + tokens / unit_tokens(dv));
 }
 
 // The plan with G layers per batch (the state does not depend on G).
@@ -202,9 +209,11 @@ Plan make_plan(const cmoe_config* c, const Derived& dv, int G) {
     p.phys = take(L * 2 * 8);
     p.active_sum = take(L * 8);
     p.selcount = take(L * N * 8);
-    p.slot_of = take(2 * L * N * 4);
-    p.slot_exp = take(2 * L * (size_t)dv.n_slots * 4);
-    p.slot_stamp = take(2 * L * (size_t)dv.n_slots * 4);
+    p.slot_of = take(L * N * 4);
+    p.slot_exp = take(L * (size_t)dv.n_slots * 4);
+    p.slot_stamp = take(L * (size_t)dv.n_slots * 4);
+    p.copy_list = take(L * 2 * N * 4);
+    p.copy_n = take(L * 2 * 4);
     p.state_total = o;
     o = 0;
     p.zpart = take(G * S * dv.n_r * N * (size_t)dv.nsplit * 8);
@@ -217,8 +226,8 @@ Plan make_plan(const cmoe_config* c, const Derived& dv, int G) {
     p.pairs = take(G * N * S * 4);
     p.act = take(S * K * (size_t)c->F * dv.esz);
     p.yp = take(G * S * K * (size_t)c->d * dv.esz);
-    p.units = take((size_t)max_units(c) * 16);
-    p.round_of = take(N * 4);
+    p.units = take((size_t)G * max_units(c, dv) * 16);
+    p.round_of = take(G * N * 4);
     p.ws_total = o;
     p.arena = L * (size_t)dv.n_slots * dv.expert_bytes;
     return p;
@@ -248,7 +257,7 @@ size_t scratch_need(const cmoe_config* c, const Derived& dv) {
     size_t o = 0;
     for (size_t bytes : {S * dv.n_r * N * slots * 8, L * S * dv.n_r * N * 4, L * S * K * 4, L * S * K * 4,
                          L * S * 16, L * 8, 2 * N * 4, 2 * N * S * 4, S * K * (size_t)c->F * dv.esz,
-                         S * K * (size_t)c->d * dv.esz, N * 4, (size_t)max_units(c) * 16, N * 4})
+                         S * K * (size_t)c->d * dv.esz, N * 4, (N + (S * K + cmoe::kUnitTokens - 1) / cmoe::kUnitTokens) * 16, N * 4})
         o += align256(bytes);
     return o;
 }
@@ -291,8 +300,7 @@ struct cmoe_handle {
     std::vector<hipEvent_t> ev_pro;  // each layer's proactive fill
     int32_t t = 0;            // next token
     int64_t g = 0;            // batches run so far (p^S buffer parity)
-    std::vector<int> ver;     // current slot-map version of each layer
-    std::vector<int32_t> clk; // arena clock of each layer: advances once per fill launch
+    int32_t clk = 0;          // arena clock: advances with every residency event of a layer
     int32_t R = 0;
     bool broken = false;
     // profiling
@@ -342,20 +350,11 @@ hipError_t timed(cmoe_handle* hd, int kid, int layers, F&& launch) {
     return launch(tm);
 }
 
-// The arguments of one residency event of `layer` (or one FFN round of it);
-// advances the layer's slot-map version and arena clock.
-FillArgs event(cmoe_handle* hd, int layer, int kind, bool counted, bool zero_pre, int bl = 0, bool units = false,
-               int round = 0) {
-    FillArgs f{layer, kind, hd->ver[layer], counted ? 1 : 0, zero_pre ? 1 : 0, bl, units ? 1 : 0, round,
-               ++hd->clk[layer]};
-    hd->ver[layer] ^= 1;
-    return f;
-}
-
-// One fill launch on stream st.
-hipError_t fill(cmoe_handle* hd, const FillArgs& f, hipStream_t st) {
-    return timed(hd, KID_FILL, f.kind == 0 ? 1 : 0,
-                 [&](const cmoe::Timing& tm) { return cmoe::launch_fill(*hd->cur, f, nullptr, st, tm); });
+// The listed copies of layers l0 .. l0 + nl - 1 on stream st.  Their time
+// belongs to the layer steps that the residency launch counts for.
+hipError_t copies(cmoe_handle* hd, int l0, int nl, int kind, hipStream_t st) {
+    return timed(hd, KID_FILL, 0,
+                 [&](const cmoe::Timing& tm) { return cmoe::launch_copies(*hd->cur, l0, nl, kind, st, tm); });
 }
 
 // One decode token.  h == nullptr selects injected logits (no router, no FFN).
@@ -387,37 +386,43 @@ cmoe_status run_token(cmoe_handle* hd, const void* h, float* y, const float* zR,
         HIPCHK(timed(hd, KID_CACHE, nl, [&](const cmoe::Timing& tm) { return cmoe::launch_cache_step(lo, a, M, tm); }),
                "cache step");
         hd->g += 1;
-        // Proactive loads (what the refinement inserted) come before the
-        // layer's demand loads; on the side stream they overlap the FFNs of
-        // the layers before.
-        if (refine && !hd->side_is_main) {
-            HIPCHK(hipEventRecord(hd->ev_access, M), "event record");
-            HIPCHK(hipStreamWaitEvent(Sd, hd->ev_access, 0), "stream wait");
-            for (int l = l0; l < l0 + nl; ++l) {
-                HIPCHK(fill(hd, event(hd, l, 1, counted, false), Sd), "fill");
-                HIPCHK(hipEventRecord(hd->ev_pro[l], Sd), "event record");
+        // Demand loads gate the layers' FFNs, after the proactive loads (what
+        // the refinement inserted); the residency launch also lays out the FFN
+        // work units.  An arena smaller than the union of the caches runs the
+        // FFN in rounds, each after the copies that bring its experts in.
+        int32_t clk = hd->clk;
+        for (int r = 0; r < hd->dv.rounds; ++r) {
+            const bool pro = refine && r == 0, side = pro && !hd->side_is_main;
+            const ResidencyArgs f{l0, nl, pro ? 1 : 0, r, counted ? 1 : 0, inject ? 0 : 1, clk + 1};
+            clk += pro ? 2 : 1;
+            HIPCHK(timed(hd, KID_FILL, nl, [&](const cmoe::Timing& tm) { return cmoe::launch_residency(lo, f, M, tm); }),
+                   "residency");
+            if (side) {  // each layer's copies on the side stream, overlapping the FFNs of the layers before
+                HIPCHK(hipEventRecord(hd->ev_access, M), "event record");
+                HIPCHK(hipStreamWaitEvent(Sd, hd->ev_access, 0), "stream wait");
+                for (int l = l0; l < l0 + nl; ++l) {
+                    HIPCHK(copies(hd, l, 1, 1, Sd), "copies");
+                    HIPCHK(hipEventRecord(hd->ev_pro[l], Sd), "event record");
+                }
+            } else {
+                if (pro) HIPCHK(copies(hd, l0, nl, 1, M), "copies");
+                HIPCHK(copies(hd, l0, nl, 0, M), "copies");
             }
-        }
-        for (int l = l0; l < l0 + nl; ++l) {
-            const int bl = l - l0;
-            if (refine && hd->side_is_main) HIPCHK(fill(hd, event(hd, l, 1, counted, false), M), "fill");
-            if (refine && !hd->side_is_main) HIPCHK(hipStreamWaitEvent(M, hd->ev_pro[l], 0), "stream wait");
-            // Demand loads gate this layer's FFN; the same launch lays out the
-            // FFN work units.  An arena smaller than the union of the caches
-            // runs the FFN in rounds, each after the fill that brings its
-            // experts in.
-            for (int r = 0; r < hd->dv.rounds; ++r) {
-                HIPCHK(fill(hd, event(hd, l, 0, counted, r == 0 && !refine, bl, !inject, r), M), "fill");
+            for (int l = l0; l < l0 + nl; ++l) {
+                if (side) {
+                    HIPCHK(hipStreamWaitEvent(M, hd->ev_pro[l], 0), "stream wait");
+                    HIPCHK(copies(hd, l, 1, 0, M), "copies");
+                }
                 if (inject) continue;
-                const int sv = hd->ver[l];
                 HIPCHK(timed(hd, KID_UP, 1,
-                             [&](const cmoe::Timing& tm) { return cmoe::launch_ffn_up(lo, l, bl, sv, r, h, M, tm); }),
+                             [&](const cmoe::Timing& tm) { return cmoe::launch_ffn_up(lo, l, l - l0, r, h, M, tm); }),
                        "ffn up");
                 HIPCHK(timed(hd, KID_DOWN, 1,
-                             [&](const cmoe::Timing& tm) { return cmoe::launch_ffn_down(lo, l, bl, sv, r, M, tm); }),
+                             [&](const cmoe::Timing& tm) { return cmoe::launch_ffn_down(lo, l, l - l0, r, M, tm); }),
                        "ffn down");
             }
         }
+        if (l0 + nl == c.L) hd->clk = clk;
         if (!inject)
             HIPCHK(timed(hd, KID_COMBINE, l0 + nl == c.L ? 1 : 0,
                          [&](const cmoe::Timing& tm) { return cmoe::launch_combine(lo, l0, nl, y, M, tm); }),
@@ -513,8 +518,6 @@ cmoe_status cmoe_init(const cmoe_config* cfg, const cmoe_weights* w, const cmoe_
     hd->scratch_bytes = need;
     hd->scratch_fits = need <= kScratchBytes;
     hd->R = has_spatio(cfg->mode) ? cfg->R : 0;
-    hd->ver.assign(cfg->L, 0);
-    hd->clk.assign(cfg->L, 0);
     hd->main = static_cast<hipStream_t>(main_stream);
     // proactive loads run on the side stream only when asked for: joined to
     // the demand fill launch on the main stream they were faster on every
@@ -549,10 +552,12 @@ cmoe_status cmoe_init(const cmoe_config* cfg, const cmoe_weights* w, const cmoe_
     lo.slot_of = reinterpret_cast<int32_t*>(sb + p.slot_of);
     lo.slot_exp = reinterpret_cast<int32_t*>(sb + p.slot_exp);
     lo.slot_stamp = reinterpret_cast<int32_t*>(sb + p.slot_stamp);
-    lo.max_units = max_units(cfg);
+    lo.copy_list = reinterpret_cast<int32_t*>(sb + p.copy_list);
+    lo.copy_n = reinterpret_cast<int32_t*>(sb + p.copy_n);
+    lo.max_units = max_units(cfg, dv);
     lo.ffn_waves = dv.ffn_waves;
     lo.xcd_units = dv.xcd_units;
-    lo.unit_tokens = dv.ffn_waves > 1 ? cmoe::kUnitTokensGrouped : cmoe::kUnitTokens;
+    lo.unit_tokens = unit_tokens(dv);
     hd->lo_static = lo;
     bind_workspace(lo, static_cast<char*>(buf->workspace), p);
     bind_workspace(hd->lo_static, hd->scratch_fits ? static_cast<char*>(scratch_dev) : nullptr,
@@ -698,8 +703,7 @@ cmoe_status cmoe_reset(cmoe_handle* hd) {
     HIPCHK(hipStreamSynchronize(hd->main), "reset");
     hd->t = 0;
     hd->g = 0;
-    hd->ver.assign(hd->cfg.L, 0);
-    hd->clk.assign(hd->cfg.L, 0);
+    hd->clk = 0;
     return CMOE_OK;
 }
 
@@ -750,14 +754,6 @@ cmoe_status cmoe_read(cmoe_handle* hd, int32_t view, void* host_out, size_t byte
     if (!lo.events) return fail(CMOE_ERR_STATE, "no per-step buffers to read");
     st = sync_all(hd);
     if (st != CMOE_OK) return st;
-    if (view == CMOE_VIEW_SLOTS) {  // the current version of each layer's slot map
-        const size_t N = hd->cfg.N;
-        for (int l = 0; l < hd->cfg.L; ++l)
-            HIPCHK(hipMemcpy(static_cast<char*>(host_out) + l * N * 4,
-                             lo.slot_of + ((size_t)hd->ver[l] * hd->cfg.L + l) * N, N * 4, hipMemcpyDeviceToHost),
-                   "view read");
-        return CMOE_OK;
-    }
     const void* src = nullptr;
     switch (view) {
         case CMOE_VIEW_LOGITS: src = lo.logits; break;
@@ -765,6 +761,7 @@ cmoe_status cmoe_read(cmoe_handle* hd, int32_t view, void* host_out, size_t byte
         case CMOE_VIEW_GATES: src = lo.gates; break;
         case CMOE_VIEW_CACHE: src = lo.cache; break;
         case CMOE_VIEW_COUNTERS: src = lo.ctr; break;
+        case CMOE_VIEW_SLOTS: src = lo.slot_of; break;
         case CMOE_VIEW_PHYS: src = lo.phys; break;
         case CMOE_VIEW_EVENTS: src = lo.events; break;
         case CMOE_VIEW_FILLS: src = lo.step_fills; break;
@@ -783,7 +780,7 @@ cmoe_status cmoe_profile_begin(cmoe_handle* hd, int32_t max_tokens, uint32_t ker
     hd->prof_mask = kernel_mask ? kernel_mask : ((1u << CMOE_KERNEL_COUNT) - 1u);
     int kinds = 0;
     for (int k = 0; k < CMOE_KERNEL_COUNT; ++k) kinds += (hd->prof_mask >> k) & 1u;
-    const size_t per_token = ((size_t)hd->cfg.L * (hd->dv.rounds + 1) + 2) * kinds;  // timed launches per token, at most
+    const size_t per_token = ((size_t)hd->cfg.L * (2 * hd->dv.rounds + 2) + 2) * kinds;  // timed launches per token, at most
     const size_t need = 2 * per_token * (size_t)max_tokens;
     while (hd->prof_pool.size() < need) {
         hipEvent_t e;

@@ -15,10 +15,9 @@ constexpr int kMaxK = 64;         // Top-K handled by the kernels (one lane per 
 constexpr int kMaxSplit = 4;         // router split-K partials per logit, at most
 constexpr int kRouterWaves = 4;      // router: wavefronts per workgroup, one k sub-range each
 constexpr int kMaxBatch = 64;        // layers of one batch (one launch of each phase), at most
-// fill kernel workgroups: copies out of an HBM pool want many loads in
-// flight (512 workgroups copy 2.7 times faster than 128); reads over the
-// host link peak with fewer (128: 56 GB/s, 1024: 47 GB/s)
-constexpr int kFillBlocksDevice = 512, kFillBlocksHost = 128;
+// workgroups of a copy launch: out of an HBM pool (measured with the copy
+// kernel's pieces), and over the host link
+constexpr int kCopyBlocksDevice = 512, kCopyBlocksHost = 128;
 // FFN work unit: one pass over an expert's weights for up to this many of its
 // tokens: 64 with one wavefront per workgroup, 128 in the grouped launch
 // (whose workgroups stage the activations in LDS for the four row tiles)
@@ -57,9 +56,12 @@ struct Layout {
     int64_t* phys;              // [L][2]      physical fills: demand, proactive
     unsigned long long* active_sum;  // [L]    distinct experts executed (counted tokens)
     unsigned long long* selcount;    // [L][N] native selections per expert (counted tokens)
-    int32_t* slot_of;           // [2][L][N]   slot of each expert, -1 absent (two versions)
-    int32_t* slot_exp;          // [2][L][n_slots] expert in each slot, -1 free
-    int32_t* slot_stamp;        // [2][L][n_slots] arena clock at the last use of each slot's expert
+    int32_t* slot_of;           // [L][N]      slot of each expert, -1 absent
+    int32_t* slot_exp;          // [L][n_slots] expert in each slot, -1 free
+    int32_t* slot_stamp;        // [L][n_slots] arena clock at the last use of each slot's expert
+    int32_t* copy_list;         // [L][2][N]   the last residency launch's copies, demand and proactive:
+                                //             (slot << 8) | expert
+    int32_t* copy_n;            // [L][2]      their numbers
     // workspace
     double* zpart;              // [G][S][n_r][nsplit][N] router partial sums
     float* logits;              // [L][S][n_r][N]
@@ -71,10 +73,10 @@ struct Layout {
     int32_t* pairs;             // [G][N][S]   (stream << 8) | k of each token of an expert
     void* act;                  // [S][K][F]   SwiGLU intermediate (dtype)
     void* yp;                   // [G][S][K][d] gated expert outputs (dtype)
-    int32_t* units;             // [max_units][4] FFN work units of the current round, heaviest
+    int32_t* units;             // [G][max_units][4] FFN work units of the current round, heaviest
                                 //             first: {(pass << 8) | expert, slot, tokens, 0},
                                 //             {-1, -1, 0, 0} past the end
-    int32_t* round_of;          // [N]         FFN round of each expert executed by the layer
+    int32_t* round_of;          // [G][N]      FFN round of each expert executed by the layer
                                 //             step, -1 if not executed
 };
 
@@ -93,20 +95,16 @@ struct StepArgs {
     const float* z[3];  // injected logits [S][L][N] per router slot (kFlagInject)
 };
 
-// One residency event of layer `layer` (or one round of it): the arena must
-// hold the union of the streams' caches, or, when the union does not fit,
-// the experts of this FFN round.  Slot maps and stamps are read from version
-// rv and written to version rv ^ 1.
-struct FillArgs {
-    int32_t layer;
-    int32_t kind;        // 0 after the post-access update, 1 after refinement
-    int32_t rv;
+// The residency events of layers l0 .. l0 + nl - 1 (one batch), or one round
+// of them: each layer's arena must hold the union of the streams' caches, or,
+// when the union does not fit, the experts of this FFN round.
+struct ResidencyArgs {
+    int32_t l0, nl;
+    int32_t refined;  // round 0: the proactive event (caches after the refinement) comes first
+    int32_t round;    // FFN round of the layer step (0 plans the rounds)
     int32_t counted;
-    int32_t zero_pre;    // kind 0: no refinement happened this token, clear its fill count
-    int32_t bl;          // the layer's index in its batch
-    int32_t units;       // kind 0: lay out the FFN work units of this round
-    int32_t round;       // kind 0: FFN round of the layer step (0 plans the rounds)
-    int32_t clk;         // arena clock of this launch: the last use it stamps
+    int32_t units;    // lay out the FFN work units of this round
+    int32_t clk;      // arena clock: the last use the first event stamps (the demand event after it: clk + 1)
 };
 
 // Optional timing of one launch: with events, they take the kernel's own
@@ -130,12 +128,13 @@ hipError_t launch_clear_buckets(const Layout& lo, int nl, hipStream_t st);
 // router logits of layers l0 .. l0 + nl - 1; also zeroes the batch's bucket counts
 hipError_t launch_router(const Layout& lo, int l0, int nl, const void* h, hipStream_t st, const Timing& tm = {});
 hipError_t launch_cache_step(const Layout& lo, const StepArgs& a, hipStream_t st, const Timing& tm = {});
-// g (or NULL): a second event of another layer in the same launch
-hipError_t launch_fill(const Layout& lo, const FillArgs& f, const FillArgs* g, hipStream_t st,
-                       const Timing& tm = {});
-hipError_t launch_ffn_up(const Layout& lo, int l, int bl, int sv, int round, const void* h, hipStream_t st,
+hipError_t launch_residency(const Layout& lo, const ResidencyArgs& f, hipStream_t st, const Timing& tm = {});
+// the copies the last residency launch listed for layers l0 .. l0 + nl - 1;
+// kind: 0 demand, 1 proactive
+hipError_t launch_copies(const Layout& lo, int l0, int nl, int kind, hipStream_t st, const Timing& tm = {});
+hipError_t launch_ffn_up(const Layout& lo, int l, int bl, int round, const void* h, hipStream_t st,
                          const Timing& tm = {});
-hipError_t launch_ffn_down(const Layout& lo, int l, int bl, int sv, int round, hipStream_t st,
+hipError_t launch_ffn_down(const Layout& lo, int l, int bl, int round, hipStream_t st,
                            const Timing& tm = {});
 // the combine of layers l0 .. l0 + nl - 1
 hipError_t launch_combine(const Layout& lo, int l0, int nl, float* y, hipStream_t st, const Timing& tm = {});

@@ -441,7 +441,7 @@ __device__ __forceinline__ void up_heavy_wide(const Layout& lo, int l, int ft, c
 // multiple of 64, so every wavefront has a tile).  W = 1: every wavefront
 // on its own; W = kWaves: grouped.
 template <int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void ffn_up_bf16(Layout lo, int l, int bl, int /*sv: slots come with the units*/,
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void ffn_up_bf16(Layout lo, int l, int bl,
                                                       const uint16_t* __restrict__ h) {
     const int wgn = lo.F / (16 * W);
     int u, j;
@@ -449,7 +449,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
     if (u >= lo.max_units) return;
     const int lane = threadIdx.x & 63;
     const int ft = j * W + (threadIdx.x >> 6);
-    const int4 ui = reinterpret_cast<const int4*>(lo.units)[u];  // expert, pass, slot, tokens in one load
+    const int4 ui = reinterpret_cast<const int4*>(lo.units)[(int64_t)bl * lo.max_units + u];  // expert, pass, slot, tokens in one load
     if (ui.x < 0) return;
     const int e = ui.x & 255, t0 = lo.unit_tokens * (ui.x >> 8), slot = ui.y, m = ui.z;
     if (m <= 0 || slot < 0 || slot >= lo.n_slots) return;
@@ -559,7 +559,7 @@ __device__ __forceinline__ void down_heavy_wide(const Layout& lo, int l, int bl,
 
 // Workgroup (u, j): the W 32-row d-tiles W j + wavefront of unit u.
 template <int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void ffn_down_bf16(Layout lo, int l, int bl, int /*sv: slots come with the units*/) {
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void ffn_down_bf16(Layout lo, int l, int bl) {
     const int dtn = lo.d / 32;
     const int wgn = (dtn + W - 1) / W;
     int u, j;
@@ -568,7 +568,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
     const int lane = threadIdx.x & 63;
     const int dt = j * W + (threadIdx.x >> 6);
     const bool active = dt < dtn;
-    const int4 ui = reinterpret_cast<const int4*>(lo.units)[u];  // expert, pass, slot, tokens in one load
+    const int4 ui = reinterpret_cast<const int4*>(lo.units)[(int64_t)bl * lo.max_units + u];  // expert, pass, slot, tokens in one load
     if (ui.x < 0) return;
     const int e = ui.x & 255, t0 = lo.unit_tokens * (ui.x >> 8), slot = ui.y, m = ui.z;
     if (m <= 0 || slot < 0 || slot >= lo.n_slots) return;
@@ -592,14 +592,14 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
 }
 
 // ---------------------------------------------------------------- fp32
-__global__ __launch_bounds__(64) void ffn_up_f32(Layout lo, int l, int bl, int sv, int round,
+__global__ __launch_bounds__(64) void ffn_up_f32(Layout lo, int l, int bl, int round,
                                                  const float* __restrict__ h) {
     const int ftn = lo.F / 64;
     const int e = blockIdx.x / ftn, ft = blockIdx.x - e * ftn;
     const int m = lo.bcount[(int64_t)bl * lo.N + e];
-    if (m == 0 || lo.round_of[e] != round) return;
+    if (m == 0 || lo.round_of[(int64_t)bl * lo.N + e] != round) return;
     const int32_t* bk = lo.pairs + ((int64_t)bl * lo.N + e) * lo.S;
-    const int slot = lo.slot_of[((int64_t)sv * lo.L + l) * lo.N + e];
+    const int slot = lo.slot_of[(int64_t)l * lo.N + e];
     if (slot < 0 || slot >= lo.n_slots) return;
     // transposed in the slot (the fill writes W_gate^T, W_up^T as [d][F]):
     // the 64 lanes, rows f, read 64 consecutive floats per k
@@ -630,13 +630,13 @@ __global__ __launch_bounds__(64) void ffn_up_f32(Layout lo, int l, int bl, int s
     }
 }
 
-__global__ __launch_bounds__(64) void ffn_down_f32(Layout lo, int l, int bl, int sv, int round) {
+__global__ __launch_bounds__(64) void ffn_down_f32(Layout lo, int l, int bl, int round) {
     const int dtn = lo.d / 64;
     const int e = blockIdx.x / dtn, dt = blockIdx.x - e * dtn;
     const int m = lo.bcount[(int64_t)bl * lo.N + e];
-    if (m == 0 || lo.round_of[e] != round) return;
+    if (m == 0 || lo.round_of[(int64_t)bl * lo.N + e] != round) return;
     const int32_t* bk = lo.pairs + ((int64_t)bl * lo.N + e) * lo.S;
-    const int slot = lo.slot_of[((int64_t)sv * lo.L + l) * lo.N + e];
+    const int slot = lo.slot_of[(int64_t)l * lo.N + e];
     if (slot < 0 || slot >= lo.n_slots) return;
     // W_down^T [F][d] in the slot: lanes (rows j) read consecutive floats
     const float* Wd = reinterpret_cast<const float*>(lo.arena) + ((int64_t)l * lo.n_slots + slot) * lo.expert_elems +
@@ -665,32 +665,32 @@ __global__ __launch_bounds__(64) void ffn_down_f32(Layout lo, int l, int bl, int
 
 }  // namespace
 
-hipError_t launch_ffn_up(const Layout& lo, int l, int bl, int sv, int round, const void* h, hipStream_t st,
+hipError_t launch_ffn_up(const Layout& lo, int l, int bl, int round, const void* h, hipStream_t st,
                          const Timing& tm) {
     if (lo.dtype == 1) {
         const uint16_t* hb = static_cast<const uint16_t*>(h);
         if (lo.ffn_waves == kWaves)
             launch_kernel(ffn_up_bf16<kWaves>, dim3(unit_groups(lo) * (lo.F / (16 * kWaves))), dim3(64 * kWaves), st, tm,
-                          lo, l, bl, sv, hb);
+                          lo, l, bl, hb);
         else
-            launch_kernel(ffn_up_bf16<1>, dim3(unit_groups(lo) * (lo.F / 16)), dim3(64), st, tm, lo, l, bl, sv, hb);
+            launch_kernel(ffn_up_bf16<1>, dim3(unit_groups(lo) * (lo.F / 16)), dim3(64), st, tm, lo, l, bl, hb);
     } else {
-        launch_kernel(ffn_up_f32, dim3(lo.N * (lo.F / 64)), dim3(64), st, tm, lo, l, bl, sv, round,
+        launch_kernel(ffn_up_f32, dim3(lo.N * (lo.F / 64)), dim3(64), st, tm, lo, l, bl, round,
                       static_cast<const float*>(h));
     }
     return hipGetLastError();
 }
 
-hipError_t launch_ffn_down(const Layout& lo, int l, int bl, int sv, int round, hipStream_t st, const Timing& tm) {
+hipError_t launch_ffn_down(const Layout& lo, int l, int bl, int round, hipStream_t st, const Timing& tm) {
     if (lo.dtype == 1) {
         const int dtn = lo.d / 32;
         if (lo.ffn_waves == kWaves)
             launch_kernel(ffn_down_bf16<kWaves>, dim3(unit_groups(lo) * ((dtn + kWaves - 1) / kWaves)), dim3(64 * kWaves),
-                          st, tm, lo, l, bl, sv);
+                          st, tm, lo, l, bl);
         else
-            launch_kernel(ffn_down_bf16<1>, dim3(unit_groups(lo) * dtn), dim3(64), st, tm, lo, l, bl, sv);
+            launch_kernel(ffn_down_bf16<1>, dim3(unit_groups(lo) * dtn), dim3(64), st, tm, lo, l, bl);
     } else {
-        launch_kernel(ffn_down_f32, dim3(lo.N * (lo.d / 64)), dim3(64), st, tm, lo, l, bl, sv, round);
+        launch_kernel(ffn_down_f32, dim3(lo.N * (lo.d / 64)), dim3(64), st, tm, lo, l, bl, round);
     }
     return hipGetLastError();
 }

@@ -1,19 +1,21 @@
 // fill.hip - physical residency and expert copies (the demand loads and
 // proactive loads of Section 2 / Algorithm 2 as transfers into HBM slots).
 //
-// One launch handles one residency event of one layer: after the post-access
-// update (demand loads) or after refinement (proactive loads), the layer's
-// HBM slots must hold the union U of the streams' caches.  Experts that left
-// U free their slot; each new expert, in ascending order, takes the lowest
-// free slot and is copied there from the cold pool.
+// A residency event of a layer follows the refinement (proactive loads) or the
+// post-access update (demand loads): the layer's HBM slots must hold the union
+// U of the streams' caches.  Experts that left U free their slot; each new
+// expert, in ascending order, takes the lowest free slot and is copied there
+// from the cold pool.
 //
-// Every workgroup derives the same assignment from the same inputs (the
-// caches and the slot maps of version rv, which nobody writes during the
-// launch), then copies its share of the new experts; workgroup 0 also writes
-// the new slot maps (version rv ^ 1) and, after the post-access update, lays
-// out the layer step's FFN work units.  No workgroup waits for another, and
-// the host never has to read the fill list.  The pool may be pinned host
-// memory mapped into the device; copies then run over the host link.
+// Two kernels, each launched once for a batch of layers:
+//   residency_kernel  one workgroup per layer decides the layer's events in
+//                     order (the proactive one, if the token refined, then the
+//                     demand one) on its slot maps in LDS, lists the copies of
+//                     each and lays out the layer step's FFN work units;
+//   copy_kernel       walks the listed copies of all layers of the batch in
+//                     pieces of 16 or 32 KB.
+// The host never reads the lists.  The pool may be pinned host memory mapped
+// into the device; copies then run over the host link.
 #include "cmoe_internal.h"
 
 namespace cmoe {
@@ -53,18 +55,22 @@ __device__ void block_counts(const bool (&v)[NF], int (&below)[NF], int (&total)
     }
 }
 
-// Values: an inclusive wavefront scan in DPP steps (shifts by 1, 2, 4 and 8
-// inside each 16-lane row, then the last lane of row 0 and of row 1 added to
-// the rows after them); a lane whose source is outside its row adds 0.
-__device__ int block_scan(int v, int* total, int* slot) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int x = v;
+// Inclusive wavefront scan in DPP steps (shifts by 1, 2, 4 and 8 inside each
+// 16-lane row, then the last lane of row 0 and of row 1 added to the rows
+// after them); a lane whose source is outside its row adds 0.
+__device__ inline int wave_scan(int x) {
     x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr:1
     x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);  // row_shr:2
     x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);  // row_shr:4
     x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);  // row_shr:8
     x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1, 3
     x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2, 3
+    return x;
+}
+
+__device__ int block_scan(int v, int* total, int* slot) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int x = wave_scan(v);
     if (lane == 63) slot[w] = x;
     __syncthreads();
     int off = 0, tot = 0;
@@ -92,139 +98,109 @@ __device__ int block_scan(int v, int* total, int* slot) {
 // the packed order (one run for each half) holds 16 source rows x 128
 // contiguous bytes: rows 16 ft + r of W_mat at columns 64 c .. 64 c + 63 for
 // the gate/up part, rows 32 dt + 16 mt + r of W_down at columns 64 c .. for
-// the down part.  Two copy orders give the same result:
-//   - block order (pool in HBM): walk the packed blocks, 8 consecutive lanes
-//     reading one 128-byte row segment, and write each block's contiguous
-//     2 KB;
-//   - source order (pool in pinned host memory): walk the source in its own
-//     order, so each wavefront reads 1 KB of one row.  Reads over the host
-//     link are then long requests (56 GB/s measured on MI355X, against 42 GB/s
-//     for 128-byte segments).  Each 16-byte unit is scattered to its packed
-//     position; the L2 merges the partial lines.
-struct BlockMap {
-    int64_t src;  // source unit of row 0, chunk 0 of the block
-    int64_t row;  // source units between consecutive rows
-};
-
-__device__ inline BlockMap packed_block(int b, int d, int F) {
-    const int partA = F / 16 * (d / 64) * 2;  // gate/up blocks
-    BlockMap m;
-    if (b < partA) {
-        const int sub = b & 1;  // gate or up
-        const int t = b >> 1;
-        const int c = t % (d / 64), tile = t / (d / 64);
-        m.src = ((int64_t)sub * F * d + (int64_t)16 * tile * d + 64 * c) / 8;
-        m.row = d / 8;
-    } else {
-        const int v = b - partA;
-        const int sub = v & 1;  // 16-row half of the 32-row tile
-        const int t = v >> 1;
-        const int c = t % (F / 64), tile = t / (F / 64);
-        m.src = (2 * (int64_t)F * d + (int64_t)(32 * tile + 16 * sub) * F + 64 * c) / 8;
-        m.row = F / 8;
-    }
-    return m;
-}
-
-// Source unit w of a block (row w / 8, 16-byte chunk w % 8 of the row's 128
-// bytes) goes to packed unit (chunk / 4) * 64 + row + 16 (chunk % 4).
+// the down part.
+//
+// A piece is up to CH k chunks c of one tile, both blocks (gate and up, or the
+// two 16-row halves) of each chunk: 32 source row segments of up to 128 CH
+// bytes, one contiguous run of up to 4 CH KB in the slot.  It passes through
+// LDS, so that both the loads and the stores of a wavefront are contiguous, and
+// the next piece's loads are in flight while this one is stored.  Measured on
+// MI355X (read plus write, 96 experts of 9.4 MB and 16 of 49.8 MB): CH = 4 with
+// 512 workgroups and nontemporal loads and stores 6.2 and 5.7 TB/s, without
+// them 5.9 and 5.3; CH = 8 5.5 and 5.4, CH = 2 5.7; 1280 workgroups 5.7 and 5.2;
+// without LDS, 128-byte row segments read straight into the packed order, 4.0
+// to 4.5 one load a thread and at most 5.6 four loads a thread; a plain copy of
+// the same bytes 6.0.
+// Source unit w of a block (row w / 8, 16-byte unit w % 8 of the row's 128
+// bytes) goes to packed unit (unit / 4) * 64 + row + 16 (unit % 4).
 __device__ inline int packed_dest_in_block(int w) {
     const int r = w >> 3, j = w & 7;
     return (j >> 2) * 64 + r + 16 * (j & 3);
 }
 
-// Packed position of source unit i of an expert (row-major W_gate, W_up,
-// then W_down, 16-byte units): the inverse of the block order above.
-__device__ inline int64_t packed_of_source(int64_t i, int d, int F) {
-    const int ud = d / 8, uf = F / 8;      // units per row
-    const int64_t nA = (int64_t)F * ud;    // units of W_gate (and of W_up)
-    if (i < 2 * nA) {
-        const int mat = i >= nA;
-        const int64_t k = i - mat * nA;
-        const int row = (int)(k / ud), u = (int)(k - (int64_t)row * ud);
-        const int64_t b = ((int64_t)(row >> 4) * (ud / 8) + (u >> 3)) * 2 + mat;
-        return b * 128 + packed_dest_in_block(((row & 15) << 3) | (u & 7));
-    }
-    const int64_t k = i - 2 * nA;
-    const int row = (int)(k / uf), u = (int)(k - (int64_t)row * uf);
-    const int64_t b = ((int64_t)(row >> 5) * (uf / 8) + (u >> 3)) * 2 + ((row >> 4) & 1);
-    return 2 * nA + b * 128 + packed_dest_in_block(((row & 15) << 3) | (u & 7));
+// LDS place of piece unit p = 256 c + 128 sub + packed unit.  A wavefront
+// stores one row's units (bits 4-6 and 8-10 of p vary: a stride of 256 bytes
+// or more, all in one bank group) and loads 64 consecutive p; the low four
+// bits, xored with those six, spread the stores over the sixteen 16-byte bank
+// groups and stay a permutation for the loads.
+__device__ inline int piece_place(int p) { return p ^ (((p >> 4) & 7) ^ (((p >> 8) & 7) << 1)); }
+
+// Expert copies are read once and written once: nontemporal both ways.
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+__device__ inline uint4 load_once(const uint4* p) {
+    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    return uint4{v.x, v.y, v.z, v.w};
+}
+__device__ inline void store_once(uint4* p, const uint4& v) {
+    __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4*>(p));
 }
 
 // Cache word i = s NW + j: word j of stream s's membership bits of the layer,
-// after the refinement (kind 1) or the access (kind 0).
-__device__ inline unsigned long long cache_word(const Layout& lo, int layer, int kind, int i) {
-    if (kind == 1) return lo.mid[(int64_t)layer * lo.S * lo.NW + i];
-    const int s = i / lo.NW, j = i - s * lo.NW;
-    return lo.cache[((int64_t)s * lo.L + layer) * lo.NW + j];
+// after the refinement or (demand) after the access.
+template <bool DEMAND>
+__device__ inline unsigned long long cache_word(const Layout& lo, int layer, int i) {
+    if constexpr (!DEMAND) {
+        return lo.mid[(int64_t)layer * lo.S * lo.NW + i];
+    } else {
+        const int s = i / lo.NW, j = i - s * lo.NW;
+        return lo.cache[((int64_t)s * lo.L + layer) * lo.NW + j];
+    }
 }
 
-// Workgroup-local state of one residency event.
-struct FillLds {
-    unsigned long long U[4];
-    int so[kMaxN], se[kMaxN], stp[kMaxN], rnd_s[kMaxN], free_list[kMaxN], enter_list[kMaxN], victim_list[kMaxN];
-    int lds4[4];       // block-scan slots
-    int lds_cnt[2][12];  // block-count slots: round plan; free slots, entries, multi-pass units
+constexpr int kWords = 4;  // cache words per thread per batch of loads
+
+// A layer's state during its residency events.
+struct ResLds {
+    unsigned long long U[2][4];  // unions of the caches: after the access, after the refinement
+    int so[kMaxN], se[kMaxN], stp[kMaxN], rnd_s[kMaxN], free_list[kMaxN], victim_list[kMaxN];
+    int lds4[4];         // block-scan slots
+    int lds_cnt[2][16];  // block-count slots: round plan; free slots, entries, units
     __align__(16) int key[kMaxN];
     int by_rank[kMaxN], who[kMaxN], m_rank[kMaxN];
 };
 
-// One residency event (or one FFN round of one), run by nwg workgroups of the
-// launch, this one being number wg; returns once its share of the copies is
-// done.  Workgroup 0 of the event writes the new slot maps and work units.
-__device__ __forceinline__ void residency_event(const Layout& lo, const FillArgs& f, FillLds& sm, int wg, int nwg) {
-    unsigned long long* U = sm.U;
-    int *so = sm.so, *se = sm.se, *stp = sm.stp, *rnd_s = sm.rnd_s, *free_list = sm.free_list;
-    int *enter_list = sm.enter_list, *victim_list = sm.victim_list, *lds4 = sm.lds4;
-    const int tid = threadIdx.x;
-    const int N = lo.N, layer = f.layer, P = lo.n_slots;
-    const int64_t vin = (int64_t)f.rv * lo.L + layer, vout = (int64_t)(f.rv ^ 1) * lo.L + layer;
-    const int32_t* so_in = lo.slot_of + vin * N;
-    const int32_t* se_in = lo.slot_exp + vin * P;
-    const int32_t* st_in = lo.slot_stamp + vin * P;
-    const bool demand = f.kind == 0;
-    // Every global load of the prologue is issued before the first is used,
-    // whatever the event (indices clamped; a value that is not needed is not
-    // used): the slot maps and stamps, the bucket sizes (the executed experts
-    // and the FFN work units), the round plan of a later round, the fill
-    // counters workgroup 0 adds to, and the first batch of cache words.
-    const bool units = demand && f.units && wg == 0;
-    const int S_NW = lo.S * lo.NW;
-    const int so_v = so_in[min(tid, N - 1)];
-    const int se_v = se_in[min(tid, P - 1)];
-    const int st_v = st_in[min(tid, P - 1)];
-    const int mb_v = lo.bcount[(int64_t)f.bl * N + min(tid, N - 1)];
-    const int ro_v = lo.round_of[min(tid, N - 1)];
-    const int64_t phys_v = lo.phys[layer * 2 + f.kind];
-    const int32_t sf_v = lo.step_fills[layer * 2];
-    constexpr int kWords = 4;  // cache words per thread per batch
-    unsigned long long w[kWords];
+template <bool DEMAND>
+__device__ inline void load_words(const Layout& lo, int layer, int i0, unsigned long long (&w)[kWords]) {
 #pragma unroll
-    for (int u = 0; u < kWords; ++u) w[u] = cache_word(lo, layer, f.kind, min(tid + u * kFillThreads, S_NW - 1));
-    __builtin_amdgcn_sched_barrier(0);
-    if (tid < 4) U[tid] = 0ull;
-    if (tid < N) so[tid] = so_v;
-    if (tid < P) {
-        se[tid] = se_v;
-        stp[tid] = st_v;
-    }
-    __syncthreads();
+    for (int u = 0; u < kWords; ++u)
+        w[u] = cache_word<DEMAND>(lo, layer, min(i0 + (int)threadIdx.x + u * kFillThreads, lo.S * lo.NW - 1));
+}
+
+// U gets the union of the layer's caches; w holds the first batch of words.
+template <bool DEMAND>
+__device__ inline void unite(const Layout& lo, int layer, unsigned long long (&w)[kWords], unsigned long long* U) {
+    const int S_NW = lo.S * lo.NW, tid = threadIdx.x;
+    const bool fixed = kFillThreads % lo.NW == 0;  // all of a thread's words are the same word of their stream
+    unsigned long long acc = 0ull;
     for (int i0 = 0; i0 < S_NW; i0 += kWords * kFillThreads) {
         if (i0 > 0) {
-#pragma unroll
-            for (int u = 0; u < kWords; ++u)
-                w[u] = cache_word(lo, layer, f.kind, min(i0 + tid + u * kFillThreads, S_NW - 1));
+            load_words<DEMAND>(lo, layer, i0, w);
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int u = 0; u < kWords; ++u) {
             const int i = i0 + tid + u * kFillThreads;
-            if (i < S_NW && w[u]) atomicOr(&U[i % lo.NW], w[u]);
+            if (i >= S_NW) continue;
+            if (fixed)
+                acc |= w[u];
+            else if (w[u])
+                atomicOr(&U[i % lo.NW], w[u]);
         }
     }
-    __syncthreads();
-    const int m_v = demand ? mb_v : 0;
-    const int e = tid;
+    if (fixed && acc) atomicOr(&U[tid % lo.NW], acc);
+}
+
+// One residency event of `layer`; the slot maps in sm are current on entry and
+// on return, and list gets the copies ((slot << 8) | expert, in the experts'
+// ascending order).  Returns their number.  Every thread of the workgroup runs
+// it.  m_v, ro_v: this thread's expert's bucket size and (later rounds) its
+// planned round.
+template <bool DEMAND>
+__device__ __forceinline__ int residency_event(const Layout& lo, ResLds& sm, int bl, int round, int m_v, int ro_v,
+                                               bool units, int clk, int32_t* list) {
+    const unsigned long long* U = sm.U[DEMAND ? 0 : 1];
+    int *so = sm.so, *se = sm.se, *stp = sm.stp, *rnd_s = sm.rnd_s, *free_list = sm.free_list;
+    const int tid = threadIdx.x, e = tid, N = lo.N, P = lo.n_slots;
     const bool inU = e < N && ((U[e >> 6] >> (e & 63)) & 1ull);
     int cur = e < N ? so[e] : -1;
     if (e < N && cur >= 0 && !inU) {  // left every cache: free its slot
@@ -240,12 +216,12 @@ __device__ __forceinline__ void residency_event(const Layout& lo, const FillArgs
     // all run in round 0.  Otherwise round 0 plans the rounds: the executed
     // experts already resident first, then the others, each group ascending,
     // P per round; later rounds read the plan.
-    const bool inE = demand && e < N && m_v > 0;
+    const bool inE = DEMAND && e < N && m_v > 0;
     int rnd = -1;
-    if (demand) {
+    if (DEMAND) {
         if (!overflow) {
             rnd = inE ? 0 : -1;
-        } else if (f.round == 0) {
+        } else if (round == 0) {
             const bool res_e = inE && cur >= 0, mis_e = inE && cur < 0;
             const bool fl[2] = {res_e, mis_e};
             int rk[2], n[2];
@@ -254,25 +230,26 @@ __device__ __forceinline__ void residency_event(const Layout& lo, const FillArgs
         } else {
             rnd = e < N ? ro_v : -1;
         }
+        if (round == 0 && e < N) lo.round_of[(int64_t)bl * N + e] = rnd;
     }
     if (e < N) rnd_s[e] = rnd;
-    const bool now = demand && rnd >= 0 && rnd == f.round;  // executed in this round
+    const bool now = DEMAND && rnd >= 0 && rnd == round;  // executed in this round
     bool enter;
-    if (!demand) enter = e < N && inU && cur < 0;
-    else if (!overflow) enter = f.round == 0 && e < N && inU && cur < 0;
+    if (!DEMAND) enter = e < N && inU && cur < 0;
+    else if (!overflow) enter = round == 0 && e < N && inU && cur < 0;
     else enter = now && cur < 0;
     const bool is_free = tid < P && se[tid] == -1;
     // The work units of this round (below) need to know whether any bucket
     // takes more than one pass, and rank the experts by their bucket sizes
-    // if one does: the flag joins the free-slot and entry counts, and the
+    // if one does: the flags join the free-slot and entry counts, and the
     // ranking keys are stored before the same barrier.
     const int m_own = (units && now) ? m_v : 0;
     const int ut = lo.unit_tokens;
     const int mykey = (m_own << 8) | (255 - tid);
     if (units) sm.key[tid] = tid < N ? mykey : -1;  // kFillThreads == kMaxN: every entry is written
-    const bool fl[3] = {is_free, enter, units && m_own > ut};
-    int rk[3], n[3];
-    block_counts<3>(fl, rk, n, sm.lds_cnt[1]);
+    const bool fl[4] = {is_free, enter, m_own > ut, m_own > 0};
+    int rk[4], n[4];
+    block_counts<4>(fl, rk, n, sm.lds_cnt[1]);
     const int rf = rk[0], re = rk[1], nfree = n[0], nenter = n[1];
     const bool multi = n[2] > 0;
     if (is_free) free_list[rf] = tid;
@@ -280,25 +257,25 @@ __device__ __forceinline__ void residency_event(const Layout& lo, const FillArgs
     // used experts that no remaining round needs (lower slot on ties), ranked
     // by (stamp, slot); after refinement only free slots are filled.
     int nvict = 0;
-    if (demand && overflow && nenter > nfree) {  // block-uniform
+    if (DEMAND && overflow && nenter > nfree) {  // block-uniform
         bool vict = false;
         int rank = 0;
         if (tid < P && se[tid] >= 0) {
-            vict = rnd_s[se[tid]] < f.round;
+            vict = rnd_s[se[tid]] < round;
             if (vict) {
                 const int sq = stp[tid];
                 for (int q2 = 0; q2 < P; ++q2) {
                     const int v2 = se[q2];
-                    if (v2 < 0 || rnd_s[v2] >= f.round) continue;
+                    if (v2 < 0 || rnd_s[v2] >= round) continue;
                     const int s2 = stp[q2];
                     rank += (s2 < sq || (s2 == sq && q2 < tid)) ? 1 : 0;
                 }
             }
         }
-        if (vict) victim_list[rank] = tid;
+        if (vict) sm.victim_list[rank] = tid;
         nvict = __syncthreads_count(vict);
     }
-    const int nent = (!demand && overflow) ? min(nenter, nfree) : nenter;
+    const int nent = (!DEMAND && overflow) ? min(nenter, nfree) : nenter;
     __syncthreads();
     const bool takes = enter && re < nent;
     if (takes) {  // rank re among new experts takes the rank-re free slot, then the victims in rank order
@@ -306,47 +283,26 @@ __device__ __forceinline__ void residency_event(const Layout& lo, const FillArgs
         if (re < nfree)
             q = free_list[re];
         else if (re - nfree < nvict)
-            q = victim_list[re - nfree];
+            q = sm.victim_list[re - nfree];
         if (q >= 0) {
             if (re >= nfree) so[se[q]] = -1;  // evicted
             so[e] = q;
             se[q] = e;
         }
-        enter_list[re] = q >= 0 ? e : -1;  // q < 0 cannot happen: a round fits the arena
+        list[re] = (max(q, 0) << 8) | e;  // q < 0 cannot happen: a round fits the arena
     }
     __syncthreads();
     // last use: the experts executed in this round and every expert copied in
-    if (e < N && (now || takes) && so[e] >= 0) stp[so[e]] = f.clk;
+    if (e < N && (now || takes) && so[e] >= 0) stp[so[e]] = clk;
     __syncthreads();
-    if (wg == 0) {
-        int32_t* so_out = lo.slot_of + vout * N;
-        int32_t* se_out = lo.slot_exp + vout * P;
-        int32_t* st_out = lo.slot_stamp + vout * P;
-        if (tid < N) so_out[tid] = so[tid];
-        if (tid < P) {
-            se_out[tid] = se[tid];
-            st_out[tid] = stp[tid];
-        }
-        if (demand && f.round == 0 && tid < N) lo.round_of[tid] = rnd;
-        if (tid == 0) {
-            if (demand && f.round > 0)
-                lo.step_fills[layer * 2] = sf_v + nent;
-            else
-                lo.step_fills[layer * 2 + f.kind] = nent;
-            if (f.zero_pre) lo.step_fills[layer * 2 + 1] = 0;
-            if (f.counted) lo.phys[layer * 2 + f.kind] = phys_v + nent;
-        }
-    }
     // FFN work units of this round: each of its experts' buckets cut into
     // passes of up to lo.unit_tokens tokens, each stored with its expert's new
     // slot and its token count, so that an FFN wavefront finds all three with
-    // one load.  When no bucket needs a second pass, unit e is expert e (or
-    // none if it has no tokens in this round).
-    int4* unit4 = reinterpret_cast<int4*>(lo.units);
-    if (units && !multi) {
-        // kFillThreads >= N: thread e holds expert e's bucket size
-        for (int i = tid; i < lo.max_units; i += kFillThreads)
-            unit4[i] = (i < N && m_own > 0) ? int4{i, so[i], m_own, 0} : int4{-1, -1, 0, 0};
+    // one load; {-1, -1, 0, 0} past the last unit.
+    int4* unit4 = reinterpret_cast<int4*>(lo.units) + (int64_t)bl * lo.max_units;
+    if (units && !multi) {  // one unit per expert, in ascending order
+        if (m_own > 0) unit4[rk[3]] = int4{e, so[e], m_own, 0};
+        for (int i = n[3] + tid; i < lo.max_units; i += kFillThreads) unit4[i] = int4{-1, -1, 0, 0};
     } else if (units) {
         // otherwise experts with more tokens go first (lower index on ties),
         // so the longest units start first.  Rank of expert e = number of
@@ -376,79 +332,232 @@ __device__ __forceinline__ void residency_event(const Layout& lo, const FillArgs
         __syncthreads();
         const int passes = tid < N ? by_rank[tid] : 0;
         int total;
-        const int off = block_scan(passes, &total, lds4);
+        const int off = block_scan(passes, &total, sm.lds4);
         if (tid < N) {
-            const int e = who[tid];
+            const int x = who[tid];
             for (int q = 0; q < passes; ++q)
-                unit4[off + q] = int4{(q << 8) | e, so[e], min(ut, m_rank[tid] - ut * q), 0};
+                unit4[off + q] = int4{(q << 8) | x, so[x], min(ut, m_rank[tid] - ut * q), 0};
         }
         for (int i = total + tid; i < lo.max_units; i += kFillThreads) unit4[i] = int4{-1, -1, 0, 0};
     }
-    if (nent == 0) return;
-    const int64_t bytes = lo.expert_elems * (lo.dtype == 1 ? 2 : 4);
-    const int64_t n16 = bytes / 16;
-    const int64_t gid = (int64_t)wg * kFillThreads + tid;
-    const int64_t gs = (int64_t)nwg * kFillThreads;
-    for (int k = 0; k < nent; ++k) {
-        const int ex = enter_list[k];
-        if (ex < 0) continue;
-        const int q = so[ex];
-        const uint4* src =
-            reinterpret_cast<const uint4*>(static_cast<const char*>(lo.pool) + ((int64_t)layer * N + ex) * bytes);
-        uint4* dst = reinterpret_cast<uint4*>(static_cast<char*>(lo.arena) + ((int64_t)layer * lo.n_slots + q) * bytes);
-        if (lo.dtype == 1 && lo.pool_host) {
-            for (int64_t i = gid; i < n16; i += gs) dst[packed_of_source(i, lo.d, lo.F)] = src[i];
-        } else if (lo.dtype == 1) {
-            for (int64_t i = gid; i < n16; i += gs) {
-                const int b = (int)(i >> 7), w = (int)(i & 127);
-                const BlockMap m = packed_block(b, lo.d, lo.F);
-                dst[(int64_t)b * 128 + packed_dest_in_block(w)] = src[m.src + (w >> 3) * m.row + (w & 7)];
-            }
-        } else {
-            // fp32: each matrix transposed (W_gate^T, W_up^T [d][F], W_down^T
-            // [F][d]) so that the lanes of the FFN kernels, one output row
-            // each, read consecutive addresses; walked in source order
-            const float* s32 = reinterpret_cast<const float*>(src);
-            float* d32 = reinterpret_cast<float*>(dst);
-            const int64_t dF = (int64_t)lo.d * lo.F;
-            for (int64_t i = gid; i < 3 * dF; i += gs) {
-                const int part = (int)(i / dF);
-                const int64_t r = i - part * dF;
-                int64_t o;
-                if (part < 2) {
-                    const int64_t f = r / lo.d, k = r - f * lo.d;  // W[f][k]
-                    o = part * dF + k * lo.F + f;
-                } else {
-                    const int64_t j = r / lo.F, f = r - j * lo.F;  // W_down[j][f]
-                    o = 2 * dF + f * lo.d + j;
-                }
-                d32[o] = s32[i];
-            }
+    return nent;
+}
+
+// grid: one workgroup per layer of the batch.  Latency-bound (one round trip
+// of loads, then some twelve barriers), so the layers of a batch run side by
+// side.
+__global__ __launch_bounds__(kFillThreads) void residency_kernel(Layout lo, ResidencyArgs f) {
+    __shared__ ResLds sm;
+    const int bl = blockIdx.x, layer = f.l0 + bl, tid = threadIdx.x, N = lo.N, P = lo.n_slots;
+    const bool pro = f.refined && f.round == 0;
+    int32_t* so_g = lo.slot_of + (int64_t)layer * N;
+    int32_t* se_g = lo.slot_exp + (int64_t)layer * P;
+    int32_t* st_g = lo.slot_stamp + (int64_t)layer * P;
+    // Every global load is issued before the first is used (indices clamped; a
+    // value that is not needed is not used): the slot maps and stamps, the
+    // bucket sizes (the executed experts and the FFN work units), the round
+    // plan of a later round, the fill counters, and the first batch of cache
+    // words of each event.
+    const int so_v = so_g[min(tid, N - 1)], se_v = se_g[min(tid, P - 1)], st_v = st_g[min(tid, P - 1)];
+    const int mb_v = lo.bcount[(int64_t)bl * N + min(tid, N - 1)];
+    const int ro_v = lo.round_of[(int64_t)bl * N + min(tid, N - 1)];
+    const int64_t phys0 = lo.phys[layer * 2], phys1 = lo.phys[layer * 2 + 1];
+    const int32_t sf_v = lo.step_fills[layer * 2];
+    unsigned long long w[kWords], wp[kWords];
+    load_words<true>(lo, layer, 0, w);
+    if (pro) load_words<false>(lo, layer, 0, wp);
+    __builtin_amdgcn_sched_barrier(0);
+    if (tid < 8) sm.U[tid >> 2][tid & 3] = 0ull;
+    if (tid < N) sm.so[tid] = so_v;
+    if (tid < P) {
+        sm.se[tid] = se_v;
+        sm.stp[tid] = st_v;
+    }
+    __syncthreads();
+    unite<true>(lo, layer, w, sm.U[0]);
+    if (pro) unite<false>(lo, layer, wp, sm.U[1]);
+    __syncthreads();
+    int32_t* list = lo.copy_list + (int64_t)layer * 2 * N;
+    int npro = 0;
+    if (pro) {
+        npro = residency_event<false>(lo, sm, bl, 0, 0, -1, false, f.clk, list + N);
+        __syncthreads();
+    }
+    const int ndem =
+        residency_event<true>(lo, sm, bl, f.round, mb_v, ro_v, f.units != 0, f.clk + (pro ? 1 : 0), list);
+    if (tid < N) so_g[tid] = sm.so[tid];
+    if (tid < P) {
+        se_g[tid] = sm.se[tid];
+        st_g[tid] = sm.stp[tid];
+    }
+    if (tid == 0) {
+        lo.copy_n[layer * 2] = ndem;
+        lo.step_fills[layer * 2] = (f.round > 0 ? sf_v : 0) + ndem;
+        if (f.counted) lo.phys[layer * 2] = phys0 + ndem;
+        if (f.round == 0) {
+            lo.copy_n[layer * 2 + 1] = npro;
+            lo.step_fills[layer * 2 + 1] = npro;
+            if (f.counted && npro) lo.phys[layer * 2 + 1] = phys1 + npro;
         }
     }
 }
 
-// One residency event, or two of different layers (g.layer >= 0): the
-// demand event of one layer and the proactive event of the next, which both
-// follow the same cache step, in one launch, each on half the workgroups
-// (even ones: f, odd ones: g).
-__global__ __launch_bounds__(kFillThreads) void fill_kernel(Layout lo, FillArgs f, FillArgs g) {
-    __shared__ FillLds sm;
-    if (g.layer < 0)
-        residency_event(lo, f, sm, blockIdx.x, gridDim.x);
-    else if ((blockIdx.x & 1) == 0)
-        residency_event(lo, f, sm, blockIdx.x >> 1, (gridDim.x + 1) >> 1);
-    else
-        residency_event(lo, g, sm, blockIdx.x >> 1, gridDim.x >> 1);
+// One piece of one copy: where its data comes from and goes.
+struct Piece {
+    const char* src;
+    char* dst;
+    int piece;  // -1: nothing to copy
+};
+
+// bf16: gate/up tiles first, then the down tiles.
+template <int CH>
+struct PackedCopy {
+    static constexpr int kRows = 256 / (8 * CH);  // row segments that the workgroup loads at once
+    static constexpr size_t kLds = sizeof(uint4) * 256 * CH;
+    uint4 v[CH];
+    int64_t d0;  // first packed unit
+    int nc;      // chunks of this piece
+
+    __host__ __device__ static int pieces(const Layout& lo) {
+        const int gA = (lo.d / 64 + CH - 1) / CH, gB = (lo.F / 64 + CH - 1) / CH;
+        return lo.F / 16 * gA + lo.d / 32 * gB;
+    }
+    __device__ void load(const Piece& pc, int d, int F) {
+        const int nA = d / 64, gA = (nA + CH - 1) / CH, nB = F / 64, gB = (nB + CH - 1) / CH;
+        const int partA = F / 16 * gA;
+        int64_t s0, row, sub;  // source units: first, between rows, between the two blocks
+        if (pc.piece < partA) {
+            const int tile = pc.piece / gA, c0 = (pc.piece - tile * gA) * CH;
+            nc = min(CH, nA - c0);
+            row = d / 8;
+            sub = (int64_t)F * row;
+            s0 = (int64_t)16 * tile * row + 8 * c0;
+            d0 = ((int64_t)tile * nA + c0) * 256;
+        } else {
+            const int q = pc.piece - partA, tile = q / gB, c0 = (q - tile * gB) * CH;
+            nc = min(CH, nB - c0);
+            row = F / 8;
+            sub = 16 * row;
+            s0 = (int64_t)2 * F * (d / 8) + (int64_t)32 * tile * row + 8 * c0;
+            d0 = (int64_t)2 * F * (d / 8) + ((int64_t)tile * nB + c0) * 256;
+        }
+        const int u = threadIdx.x % (8 * CH), r0 = threadIdx.x / (8 * CH);
+        const uint4* src = reinterpret_cast<const uint4*>(pc.src) + s0 + u;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int r = i * kRows + r0;  // rows 0-15: first block, 16-31: second
+            if ((u >> 3) < nc) v[i] = load_once(src + (r >> 4) * sub + (r & 15) * row);
+        }
+    }
+    __device__ void stage(uint4* buf) const {
+        const int u = threadIdx.x % (8 * CH), c = u >> 3, r0 = threadIdx.x / (8 * CH);
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int r = i * kRows + r0;
+            if (c < nc)
+                buf[piece_place(c * 256 + (r >> 4) * 128 + packed_dest_in_block(((r & 15) << 3) | (u & 7)))] = v[i];
+        }
+    }
+    __device__ static void store(const uint4* buf, char* dst, int64_t d0, int nc) {
+        uint4* o = reinterpret_cast<uint4*>(dst) + d0 + threadIdx.x;
+#pragma unroll
+        for (int i = 0; i < CH; ++i)
+            if (i < nc) store_once(o + i * 256, buf[piece_place(i * 256 + (int)threadIdx.x)]);
+    }
+};
+
+// fp32: each matrix transposed (W_gate^T, W_up^T [d][F], W_down^T [F][d]) so
+// that the lanes of the FFN kernels, one output row each, read consecutive
+// addresses; a piece is one 64 x 64 tile, through LDS.
+struct TransposeCopy {
+    static constexpr size_t kLds = sizeof(float) * 64 * 65 + 48;  // a multiple of 16
+    float v[16];
+    int64_t d0;  // first output float
+    int nc;      // floats between output rows
+
+    __host__ __device__ static int pieces(const Layout& lo) { return 3 * (lo.F / 64) * (lo.d / 64); }
+    __device__ void load(const Piece& pc, int d, int F) {
+        const int per = (F / 64) * (d / 64), mat = pc.piece / per, t = pc.piece - mat * per;
+        const int rows = mat < 2 ? F : d, cols = mat < 2 ? d : F, ct = cols / 64;
+        const int r0 = t / ct * 64, c0 = (t % ct) * 64;
+        const float* s = reinterpret_cast<const float*>(pc.src) + (int64_t)mat * d * F +
+                         (int64_t)(r0 + (threadIdx.x >> 6)) * cols + c0 + (threadIdx.x & 63);
+        d0 = (int64_t)mat * d * F + (int64_t)c0 * rows + r0;
+        nc = rows;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = s[(int64_t)4 * i * cols];
+    }
+    __device__ void stage(uint4* buf) const {
+        float* b = reinterpret_cast<float*>(buf) + (threadIdx.x >> 6) * 65 + (threadIdx.x & 63);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) b[4 * i * 65] = v[i];
+    }
+    __device__ static void store(const uint4* buf, char* dst, int64_t d0, int nc) {
+        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+        const float* b = reinterpret_cast<const float*>(buf) + lane * 65 + w;
+        float* o = reinterpret_cast<float*>(dst) + d0 + (int64_t)w * nc + lane;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[(int64_t)4 * i * nc] = b[4 * i];
+    }
+};
+
+// The listed copies of layers l0 .. l0 + nl - 1 (nl <= kMaxBatch = 64): every
+// wavefront finds the copies of all layers from one load and a prefix sum, and
+// the workgroups walk the pieces of all copies in turn.  kind: 0 demand, 1
+// proactive.
+template <class COPY>
+__global__ __launch_bounds__(kFillThreads) void copy_kernel(Layout lo, int l0, int nl, int kind) {
+    __shared__ uint4 buf[COPY::kLds / sizeof(uint4)];
+    const int lane = threadIdx.x & 63;
+    const int mine = lane < nl ? lo.copy_n[(l0 + lane) * 2 + kind] : 0;
+    const int below = wave_scan(mine);  // copies of this lane's layer and the ones before it
+    const int ncopies = __builtin_amdgcn_readlane(below, 63);
+    const int pieces = COPY::pieces(lo);
+    const int64_t total = (int64_t)ncopies * pieces, bytes = lo.expert_elems * (lo.dtype == 1 ? 2 : 4);
+    auto piece_of = [&](int64_t item) {  // workgroup-uniform
+        Piece pc{nullptr, nullptr, -1};
+        if (item < total) {
+            const int c = (int)(item / pieces);
+            const int bl = __popcll(__ballot(below <= c));  // layers whose copies all come before this one
+            const int layer = l0 + bl, k = c - (bl > 0 ? __builtin_amdgcn_readlane(below, bl - 1) : 0);
+            const int ent = lo.copy_list[((int64_t)layer * 2 + kind) * lo.N + k];
+            pc.src = static_cast<const char*>(lo.pool) + ((int64_t)layer * lo.N + (ent & 255)) * bytes;
+            pc.dst = static_cast<char*>(lo.arena) + ((int64_t)layer * lo.n_slots + (ent >> 8)) * bytes;
+            pc.piece = (int)(item - (int64_t)c * pieces);
+        }
+        return pc;
+    };
+    COPY cp;
+    Piece pc = piece_of(blockIdx.x);
+    if (pc.piece >= 0) cp.load(pc, lo.d, lo.F);
+    for (int64_t item = blockIdx.x; item < total; item += gridDim.x) {
+        __syncthreads();  // the previous piece has left the buffer
+        cp.stage(buf);
+        __syncthreads();
+        char* dst = pc.dst;
+        const int64_t d0 = cp.d0;
+        const int nc = cp.nc;
+        pc = piece_of(item + gridDim.x);
+        if (pc.piece >= 0) cp.load(pc, lo.d, lo.F);
+        COPY::store(buf, dst, d0, nc);
+    }
 }
 
 }  // namespace
 
-hipError_t launch_fill(const Layout& lo, const FillArgs& f, const FillArgs* g, hipStream_t st, const Timing& tm) {
-    FillArgs none{};
-    none.layer = -1;
-    launch_kernel(fill_kernel, dim3(lo.pool_host ? kFillBlocksHost : kFillBlocksDevice), dim3(kFillThreads), st, tm, lo, f,
-                  g ? *g : none);
+hipError_t launch_residency(const Layout& lo, const ResidencyArgs& f, hipStream_t st, const Timing& tm) {
+    launch_kernel(residency_kernel, dim3(f.nl), dim3(kFillThreads), st, tm, lo, f);
+    return hipGetLastError();
+}
+
+hipError_t launch_copies(const Layout& lo, int l0, int nl, int kind, hipStream_t st, const Timing& tm) {
+    if (lo.dtype != 1)
+        launch_kernel(copy_kernel<TransposeCopy>, dim3(lo.pool_host ? kCopyBlocksHost : kCopyBlocksDevice),
+                      dim3(kFillThreads), st, tm, lo, l0, nl, kind);
+    else if (lo.pool_host)
+        launch_kernel(copy_kernel<PackedCopy<8>>, dim3(kCopyBlocksHost), dim3(kFillThreads), st, tm, lo, l0, nl, kind);
+    else
+        launch_kernel(copy_kernel<PackedCopy<4>>, dim3(kCopyBlocksDevice), dim3(kFillThreads), st, tm, lo, l0, nl, kind);
     return hipGetLastError();
 }
 
