@@ -11,8 +11,7 @@
 //     main: cache step (batch): refinement, access, retention, counters, buckets
 //     main: residency events (batch): slot maps, copy lists, FFN work units
 //     main: proactive copies (batch, if refining), demand copies (batch)
-//     for each layer l, main: expert gate/up(l), expert down(l)
-//     main: combine (batch)
+//     main: expert gate/up, expert down, combine (batch)
 // With proactive fills on the side stream, each layer's proactive copies run
 // there, and its demand copies on the main stream just before its FFN.
 #include <hip/hip_runtime.h>
@@ -224,7 +223,7 @@ Plan make_plan(const cmoe_config* c, const Derived& dv, int G) {
     p.step_fills = take(L * 2 * 4);
     p.bcount = take(G * N * 4);
     p.pairs = take(G * N * S * 4);
-    p.act = take(S * K * (size_t)c->F * dv.esz);
+    p.act = take(G * S * K * (size_t)c->F * dv.esz);
     p.yp = take(G * S * K * (size_t)c->d * dv.esz);
     p.units = take((size_t)G * max_units(c, dv) * 16);
     p.round_of = take(G * N * 4);
@@ -408,17 +407,23 @@ cmoe_status run_token(cmoe_handle* hd, const void* h, float* y, const float* zR,
                 if (pro) HIPCHK(copies(hd, l0, nl, 1, M), "copies");
                 HIPCHK(copies(hd, l0, nl, 0, M), "copies");
             }
-            for (int l = l0; l < l0 + nl; ++l) {
+            // one FFN launch pair for the batch, or one per layer behind its copies
+            const int step = side ? 1 : nl;
+            for (int l = l0; l < l0 + nl; l += step) {
                 if (side) {
                     HIPCHK(hipStreamWaitEvent(M, hd->ev_pro[l], 0), "stream wait");
                     HIPCHK(copies(hd, l, 1, 0, M), "copies");
                 }
                 if (inject) continue;
-                HIPCHK(timed(hd, KID_UP, 1,
-                             [&](const cmoe::Timing& tm) { return cmoe::launch_ffn_up(lo, l, l - l0, r, h, M, tm); }),
+                HIPCHK(timed(hd, KID_UP, step,
+                             [&](const cmoe::Timing& tm) {
+                                 return cmoe::launch_ffn_up(lo, l, l - l0, step, r, h, M, tm);
+                             }),
                        "ffn up");
-                HIPCHK(timed(hd, KID_DOWN, 1,
-                             [&](const cmoe::Timing& tm) { return cmoe::launch_ffn_down(lo, l, l - l0, r, M, tm); }),
+                HIPCHK(timed(hd, KID_DOWN, step,
+                             [&](const cmoe::Timing& tm) {
+                                 return cmoe::launch_ffn_down(lo, l, l - l0, step, r, M, tm);
+                             }),
                        "ffn down");
             }
         }

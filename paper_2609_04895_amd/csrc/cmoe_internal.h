@@ -71,7 +71,7 @@ struct Layout {
     int32_t* step_fills;        // [L][2]      physical fills of the last token
     int32_t* bcount;            // [G][N]      tokens per expert
     int32_t* pairs;             // [G][N][S]   (stream << 8) | k of each token of an expert
-    void* act;                  // [S][K][F]   SwiGLU intermediate (dtype)
+    void* act;                  // [G][S][K][F] SwiGLU intermediate (dtype)
     void* yp;                   // [G][S][K][d] gated expert outputs (dtype)
     int32_t* units;             // [G][max_units][4] FFN work units of the current round, heaviest
                                 //             first: {(pass << 8) | expert, slot, tokens, 0},
@@ -132,10 +132,10 @@ hipError_t launch_residency(const Layout& lo, const ResidencyArgs& f, hipStream_
 // the copies the last residency launch listed for layers l0 .. l0 + nl - 1;
 // kind: 0 demand, 1 proactive
 hipError_t launch_copies(const Layout& lo, int l0, int nl, int kind, hipStream_t st, const Timing& tm = {});
-hipError_t launch_ffn_up(const Layout& lo, int l, int bl, int round, const void* h, hipStream_t st,
+// the FFN round of layers l0 .. l0 + nl - 1, numbers b0 .. of their batch
+hipError_t launch_ffn_up(const Layout& lo, int l0, int b0, int nl, int round, const void* h, hipStream_t st,
                          const Timing& tm = {});
-hipError_t launch_ffn_down(const Layout& lo, int l, int bl, int round, hipStream_t st,
-                           const Timing& tm = {});
+hipError_t launch_ffn_down(const Layout& lo, int l0, int b0, int nl, int round, hipStream_t st, const Timing& tm = {});
 // the combine of layers l0 .. l0 + nl - 1
 hipError_t launch_combine(const Layout& lo, int l0, int nl, float* y, hipStream_t st, const Timing& tm = {});
 // streaming read of per_wave 16-byte units by each wavefront of the probe

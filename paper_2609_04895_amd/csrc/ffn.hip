@@ -87,7 +87,9 @@ __device__ inline void store_gated(const Layout& lo, int bl, int s, int k, int j
         make_uint2(pack_bf16x2(gk * c1[0], gk * c1[1]), pack_bf16x2(gk * c1[2], gk * c1[3]));
 }
 
-// The FFN grids hold wgn workgroups per work unit; consecutive workgroups go
+// The FFN grids take a batch of layers (y), so that the next layer's first
+// workgroups run beside this layer's last ones.  Per layer they hold wgn
+// workgroups per work unit; consecutive workgroups go
 // to the eight XCDs in turn.  With xcd_units, workgroup b takes unit
 // u = 8 (q / wgn) + b % 8 and part q % wgn of it, q = b / 8, so that all the
 // workgroups of a unit have the same b % 8: a unit runs on one XCD and its
@@ -113,6 +115,12 @@ inline int unit_groups(const Layout& lo) { return lo.xcd_units ? (lo.max_units +
 
 __device__ inline const uint16_t* slot_base(const Layout& lo, int l, int slot) {
     return reinterpret_cast<const uint16_t*>(lo.arena) + ((int64_t)l * lo.n_slots + slot) * lo.expert_elems;
+}
+
+// The SwiGLU intermediate [S][K][F] of layer bl of the batch.
+template <typename T>
+__device__ inline T* act_base(const Layout& lo, int bl) {
+    return static_cast<T*>(lo.act) + (int64_t)bl * lo.S * lo.K * lo.F;
 }
 
 // U consecutive 64-wide k chunks of one 16-row (gate/up) or 2 x 16-row (down)
@@ -343,11 +351,11 @@ __device__ __forceinline__ void mfma_pass_wide(const uint4* __restrict__ tile, i
 // Token groups of one pass over the weights: one group (up to 16 tokens, the
 // common case) with a deep k block, or kNG groups with a shallower one.
 template <int NG, int U>
-__device__ inline void up_passes(const Layout& lo, int l, int ft, const int32_t* __restrict__ bk, int m,
+__device__ inline void up_passes(const Layout& lo, int l, int bl, int ft, const int32_t* __restrict__ bk, int m,
                                  const uint4* __restrict__ tileA, const uint16_t* __restrict__ h, int lane) {
     const int r = lane & 15, g = lane >> 4;
     const int d = lo.d;
-    uint16_t* act = reinterpret_cast<uint16_t*>(lo.act);
+    uint16_t* act = act_base<uint16_t>(lo, bl);
     for (int t0 = 0; t0 < m; t0 += 16 * NG) {
         const int ng = min(NG, (m - t0 + 15) / 16);
         int pr[NG];
@@ -377,12 +385,12 @@ __device__ inline void up_passes(const Layout& lo, int l, int ft, const int32_t*
 
 // A unit of 17 to 16 kNG tokens: one pass with the activations shared by the
 // workgroup.
-__device__ inline void up_heavy(const Layout& lo, int l, int ft, const int32_t* __restrict__ bk, int m,
+__device__ inline void up_heavy(const Layout& lo, int l, int bl, int ft, const int32_t* __restrict__ bk, int m,
                                 const uint4* __restrict__ tileA, const uint16_t* __restrict__ h, int tid,
                                 HeavyLds<kUnrollWide>& sm) {
     const int lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int d = lo.d;
-    uint16_t* act = reinterpret_cast<uint16_t*>(lo.act);
+    uint16_t* act = act_base<uint16_t>(lo, bl);
     int pr[kNG];
     const uint16_t* xb[kNG];
 #pragma unroll
@@ -407,12 +415,12 @@ __device__ inline void up_heavy(const Layout& lo, int l, int ft, const int32_t* 
 
 // A unit of 65 to kUnitTokensGrouped tokens: one pass, eight token groups,
 // the activations shared by the workgroup.
-__device__ __forceinline__ void up_heavy_wide(const Layout& lo, int l, int ft, const int32_t* __restrict__ bk, int m,
+__device__ __forceinline__ void up_heavy_wide(const Layout& lo, int l, int bl, int ft, const int32_t* __restrict__ bk, int m,
                                      const uint4* __restrict__ tileA, const uint16_t* __restrict__ h, int tid,
                                      WideLds& sm) {
     const int lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int d = lo.d, q0 = 4 * (tid >> 7);
-    uint16_t* act = reinterpret_cast<uint16_t*>(lo.act);
+    uint16_t* act = act_base<uint16_t>(lo, bl);
     const uint16_t* xs[4];  // token rows of this thread's staging groups
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -441,8 +449,9 @@ __device__ __forceinline__ void up_heavy_wide(const Layout& lo, int l, int ft, c
 // multiple of 64, so every wavefront has a tile).  W = 1: every wavefront
 // on its own; W = kWaves: grouped.
 template <int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void ffn_up_bf16(Layout lo, int l, int bl,
-                                                      const uint16_t* __restrict__ h) {
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void ffn_up_bf16(Layout lo, int l0, int b0,
+                                                                                                  const uint16_t* __restrict__ h) {
+    const int l = l0 + blockIdx.y, bl = b0 + blockIdx.y;
     const int wgn = lo.F / (16 * W);
     int u, j;
     unit_of_block(blockIdx.x, wgn, lo.xcd_units != 0, u, j);
@@ -459,15 +468,15 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
     const uint4* tileA =
         reinterpret_cast<const uint4*>(slot_base(lo, l, slot)) + (int64_t)ft * (lo.d / 64) * 256 + lane;
     if (m <= 16) {  // workgroup-uniform
-        up_passes<1, kUnroll>(lo, l, ft, bk, m, tileA, h, lane);
+        up_passes<1, kUnroll>(lo, l, bl, ft, bk, m, tileA, h, lane);
     } else if constexpr (W == 1) {
-        up_passes<kNG, kUnrollSolo>(lo, l, ft, bk, m, tileA, h, lane);
+        up_passes<kNG, kUnrollSolo>(lo, l, bl, ft, bk, m, tileA, h, lane);
     } else {
         __shared__ GroupedLds sm;
         if (m <= 16 * kNG)
-            up_heavy(lo, l, ft, bk, m, tileA, h, threadIdx.x, sm.narrow);
+            up_heavy(lo, l, bl, ft, bk, m, tileA, h, threadIdx.x, sm.narrow);
         else
-            up_heavy_wide(lo, l, ft, bk, m, tileA, h, threadIdx.x, sm.wide);
+            up_heavy_wide(lo, l, bl, ft, bk, m, tileA, h, threadIdx.x, sm.wide);
     }
 }
 
@@ -476,7 +485,7 @@ __device__ inline void down_passes(const Layout& lo, int l, int bl, int dt, cons
                                    const uint4* __restrict__ tileB, int lane) {
     const int r = lane & 15, g = lane >> 4;
     const int F = lo.F;
-    const uint16_t* act = reinterpret_cast<const uint16_t*>(lo.act);
+    const uint16_t* act = act_base<uint16_t>(lo, bl);
     for (int t0 = 0; t0 < m; t0 += 16 * NG) {
         const int ng = min(NG, (m - t0 + 15) / 16);
         int pr[NG];
@@ -508,7 +517,7 @@ __device__ inline void down_heavy(const Layout& lo, int l, int bl, int dt, bool 
                                   const uint4* __restrict__ tileB, int tid, HeavyLds<kUnrollWide>& sm) {
     const int lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int F = lo.F;
-    const uint16_t* act = reinterpret_cast<const uint16_t*>(lo.act);
+    const uint16_t* act = act_base<uint16_t>(lo, bl);
     int pr[kNG];
     const uint16_t* xb[kNG];
 #pragma unroll
@@ -535,7 +544,7 @@ __device__ __forceinline__ void down_heavy_wide(const Layout& lo, int l, int bl,
                                        int m, const uint4* __restrict__ tileB, int tid, WideLds& sm) {
     const int lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int F = lo.F, q0 = 4 * (tid >> 7);
-    const uint16_t* act = reinterpret_cast<const uint16_t*>(lo.act);
+    const uint16_t* act = act_base<uint16_t>(lo, bl);
     const uint16_t* xs[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -559,7 +568,8 @@ __device__ __forceinline__ void down_heavy_wide(const Layout& lo, int l, int bl,
 
 // Workgroup (u, j): the W 32-row d-tiles W j + wavefront of unit u.
 template <int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void ffn_down_bf16(Layout lo, int l, int bl) {
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void ffn_down_bf16(Layout lo, int l0, int b0) {
+    const int l = l0 + blockIdx.y, bl = b0 + blockIdx.y;
     const int dtn = lo.d / 32;
     const int wgn = (dtn + W - 1) / W;
     int u, j;
@@ -592,8 +602,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
 }
 
 // ---------------------------------------------------------------- fp32
-__global__ __launch_bounds__(64) void ffn_up_f32(Layout lo, int l, int bl, int round,
+__global__ __launch_bounds__(64) void ffn_up_f32(Layout lo, int l0, int b0, int round,
                                                  const float* __restrict__ h) {
+    const int l = l0 + blockIdx.y, bl = b0 + blockIdx.y;
     const int ftn = lo.F / 64;
     const int e = blockIdx.x / ftn, ft = blockIdx.x - e * ftn;
     const int m = lo.bcount[(int64_t)bl * lo.N + e];
@@ -606,7 +617,7 @@ __global__ __launch_bounds__(64) void ffn_up_f32(Layout lo, int l, int bl, int r
     const float* Wg = reinterpret_cast<const float*>(lo.arena) + ((int64_t)l * lo.n_slots + slot) * lo.expert_elems;
     const float* Wu = Wg + (int64_t)lo.F * lo.d;
     const int f = ft * 64 + threadIdx.x;
-    float* act = reinterpret_cast<float*>(lo.act);
+    float* act = act_base<float>(lo, bl);
     for (int tok = 0; tok < m; ++tok) {
         const int pair = bk[tok];
         const int s = pair >> 8;
@@ -630,7 +641,8 @@ __global__ __launch_bounds__(64) void ffn_up_f32(Layout lo, int l, int bl, int r
     }
 }
 
-__global__ __launch_bounds__(64) void ffn_down_f32(Layout lo, int l, int bl, int round) {
+__global__ __launch_bounds__(64) void ffn_down_f32(Layout lo, int l0, int b0, int round) {
+    const int l = l0 + blockIdx.y, bl = b0 + blockIdx.y;
     const int dtn = lo.d / 64;
     const int e = blockIdx.x / dtn, dt = blockIdx.x - e * dtn;
     const int m = lo.bcount[(int64_t)bl * lo.N + e];
@@ -642,7 +654,7 @@ __global__ __launch_bounds__(64) void ffn_down_f32(Layout lo, int l, int bl, int
     const float* Wd = reinterpret_cast<const float*>(lo.arena) + ((int64_t)l * lo.n_slots + slot) * lo.expert_elems +
                       2 * (int64_t)lo.F * lo.d;
     const int j = dt * 64 + threadIdx.x;
-    const float* act = reinterpret_cast<const float*>(lo.act);
+    const float* act = act_base<float>(lo, bl);
     for (int tok = 0; tok < m; ++tok) {
         const int pair = bk[tok];
         const int s = pair >> 8, k = pair & 255;
@@ -665,32 +677,32 @@ __global__ __launch_bounds__(64) void ffn_down_f32(Layout lo, int l, int bl, int
 
 }  // namespace
 
-hipError_t launch_ffn_up(const Layout& lo, int l, int bl, int round, const void* h, hipStream_t st,
+hipError_t launch_ffn_up(const Layout& lo, int l0, int b0, int nl, int round, const void* h, hipStream_t st,
                          const Timing& tm) {
     if (lo.dtype == 1) {
         const uint16_t* hb = static_cast<const uint16_t*>(h);
         if (lo.ffn_waves == kWaves)
-            launch_kernel(ffn_up_bf16<kWaves>, dim3(unit_groups(lo) * (lo.F / (16 * kWaves))), dim3(64 * kWaves), st, tm,
-                          lo, l, bl, hb);
+            launch_kernel(ffn_up_bf16<kWaves>, dim3(unit_groups(lo) * (lo.F / (16 * kWaves)), nl), dim3(64 * kWaves), st,
+                          tm, lo, l0, b0, hb);
         else
-            launch_kernel(ffn_up_bf16<1>, dim3(unit_groups(lo) * (lo.F / 16)), dim3(64), st, tm, lo, l, bl, hb);
+            launch_kernel(ffn_up_bf16<1>, dim3(unit_groups(lo) * (lo.F / 16), nl), dim3(64), st, tm, lo, l0, b0, hb);
     } else {
-        launch_kernel(ffn_up_f32, dim3(lo.N * (lo.F / 64)), dim3(64), st, tm, lo, l, bl, round,
+        launch_kernel(ffn_up_f32, dim3(lo.N * (lo.F / 64), nl), dim3(64), st, tm, lo, l0, b0, round,
                       static_cast<const float*>(h));
     }
     return hipGetLastError();
 }
 
-hipError_t launch_ffn_down(const Layout& lo, int l, int bl, int round, hipStream_t st, const Timing& tm) {
+hipError_t launch_ffn_down(const Layout& lo, int l0, int b0, int nl, int round, hipStream_t st, const Timing& tm) {
     if (lo.dtype == 1) {
         const int dtn = lo.d / 32;
         if (lo.ffn_waves == kWaves)
-            launch_kernel(ffn_down_bf16<kWaves>, dim3(unit_groups(lo) * ((dtn + kWaves - 1) / kWaves)), dim3(64 * kWaves),
-                          st, tm, lo, l, bl);
+            launch_kernel(ffn_down_bf16<kWaves>, dim3(unit_groups(lo) * ((dtn + kWaves - 1) / kWaves), nl),
+                          dim3(64 * kWaves), st, tm, lo, l0, b0);
         else
-            launch_kernel(ffn_down_bf16<1>, dim3(unit_groups(lo) * dtn), dim3(64), st, tm, lo, l, bl);
+            launch_kernel(ffn_down_bf16<1>, dim3(unit_groups(lo) * dtn, nl), dim3(64), st, tm, lo, l0, b0);
     } else {
-        launch_kernel(ffn_down_f32, dim3(lo.N * (lo.d / 64)), dim3(64), st, tm, lo, l, bl, round);
+        launch_kernel(ffn_down_f32, dim3(lo.N * (lo.d / 64), nl), dim3(64), st, tm, lo, l0, b0, round);
     }
     return hipGetLastError();
 }
