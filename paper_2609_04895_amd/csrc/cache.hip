@@ -637,24 +637,13 @@ __global__ void init_kernel(Layout lo) {
     if (lo.events == nullptr) return;  // no workspace bound (kernel-uniform)
     for (int64_t i = gid; i < (int64_t)lo.L * 2; i += gs) lo.step_fills[i] = 0;
     for (int64_t i = gid; i < (int64_t)lo.L * lo.S * 4; i += gs) lo.events[i] = 0;
-}
-
-// Bucket counts of a batch whose logits are injected (otherwise the router
-// launch clears them).
-__global__ __launch_bounds__(256) void clear_buckets_kernel(Layout lo, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) lo.bcount[i] = 0;
+    for (int64_t i = gid; i < (int64_t)lo.G * lo.N; i += gs) lo.bcount[i] = 0;
 }
 
 }  // namespace
 
 hipError_t launch_init(const Layout& lo, hipStream_t st) {
     hipLaunchKernelGGL(init_kernel, dim3(256), dim3(256), 0, st, lo);
-    return hipGetLastError();
-}
-
-hipError_t launch_clear_buckets(const Layout& lo, int nl, hipStream_t st) {
-    hipLaunchKernelGGL(clear_buckets_kernel, dim3((nl * lo.N + 255) / 256), dim3(256), 0, st, lo, nl * lo.N);
     return hipGetLastError();
 }
 

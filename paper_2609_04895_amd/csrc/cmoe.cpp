@@ -372,11 +372,10 @@ cmoe_status run_token(cmoe_handle* hd, const void* h, float* y, const float* zR,
 
     for (int l0 = 0; l0 < c.L; l0 += lo.G) {
         const int nl = std::min(lo.G, c.L - l0);
-        if (inject)
-            HIPCHK(cmoe::launch_clear_buckets(lo, nl, M), "bucket counts");
-        else
+        // every batch leaves zero bucket counts, but other handles share the scratch array
+        if (!inject)
             HIPCHK(timed(hd, KID_ROUTER, nl,
-                         [&](const cmoe::Timing& tm) { return cmoe::launch_router(lo, l0, nl, h, M, tm); }),
+                         [&](const cmoe::Timing& tm) { return cmoe::launch_router(lo, l0, nl, h, on_scratch, M, tm); }),
                    "router");
         StepArgs a{l0, nl, hd->R, (int)(hd->g & 1), 0, hd->t, {zR, nullptr, nullptr}};
         a.flags = (inject ? cmoe::kFlagInject : 0u) | (refine ? cmoe::kFlagRefine : 0u) | (counted ? cmoe::kFlagCount : 0u);
@@ -392,7 +391,8 @@ cmoe_status run_token(cmoe_handle* hd, const void* h, float* y, const float* zR,
         int32_t clk = hd->clk;
         for (int r = 0; r < hd->dv.rounds; ++r) {
             const bool pro = refine && r == 0, side = pro && !hd->side_is_main;
-            const ResidencyArgs f{l0, nl, pro ? 1 : 0, r, counted ? 1 : 0, inject ? 0 : 1, clk + 1};
+            const ResidencyArgs f{l0, nl, pro ? 1 : 0, r, counted ? 1 : 0, inject ? 0 : 1,
+                                  r + 1 == hd->dv.rounds ? 1 : 0, clk + 1};
             clk += pro ? 2 : 1;
             HIPCHK(timed(hd, KID_FILL, nl, [&](const cmoe::Timing& tm) { return cmoe::launch_residency(lo, f, M, tm); }),
                    "residency");
@@ -417,12 +417,12 @@ cmoe_status run_token(cmoe_handle* hd, const void* h, float* y, const float* zR,
                 if (inject) continue;
                 HIPCHK(timed(hd, KID_UP, step,
                              [&](const cmoe::Timing& tm) {
-                                 return cmoe::launch_ffn_up(lo, l, l - l0, step, r, h, M, tm);
+                                 return cmoe::launch_ffn_up(lo, l, l - l0, step, h, M, tm);
                              }),
                        "ffn up");
                 HIPCHK(timed(hd, KID_DOWN, step,
                              [&](const cmoe::Timing& tm) {
-                                 return cmoe::launch_ffn_down(lo, l, l - l0, step, r, M, tm);
+                                 return cmoe::launch_ffn_down(lo, l, l - l0, step, M, tm);
                              }),
                        "ffn down");
             }

@@ -69,7 +69,7 @@ struct Layout {
     float* gates;               // [L][S][K]
     int32_t* events;            // [L][S][4]   hits, D, P, 0 of the last token
     int32_t* step_fills;        // [L][2]      physical fills of the last token
-    int32_t* bcount;            // [G][N]      tokens per expert
+    int32_t* bcount;            // [G][N]      tokens per expert; zero between batches
     int32_t* pairs;             // [G][N][S]   (stream << 8) | k of each token of an expert
     void* act;                  // [G][S][K][F] SwiGLU intermediate (dtype)
     void* yp;                   // [G][S][K][d] gated expert outputs (dtype)
@@ -104,6 +104,7 @@ struct ResidencyArgs {
     int32_t round;    // FFN round of the layer step (0 plans the rounds)
     int32_t counted;
     int32_t units;    // lay out the FFN work units of this round
+    int32_t last;     // last round: the bucket counts are zeroed for the next batch
     int32_t clk;      // arena clock: the last use the first event stamps (the demand event after it: clk + 1)
 };
 
@@ -124,18 +125,18 @@ inline void launch_kernel(void (*kernel)(KArgs...), dim3 grid, dim3 block, hipSt
 }
 
 hipError_t launch_init(const Layout& lo, hipStream_t st);  // state, and the workspace if bound
-hipError_t launch_clear_buckets(const Layout& lo, int nl, hipStream_t st);
-// router logits of layers l0 .. l0 + nl - 1; also zeroes the batch's bucket counts
-hipError_t launch_router(const Layout& lo, int l0, int nl, const void* h, hipStream_t st, const Timing& tm = {});
+// router logits of layers l0 .. l0 + nl - 1; dirty: also zeroes the batch's bucket counts
+hipError_t launch_router(const Layout& lo, int l0, int nl, const void* h, bool dirty, hipStream_t st,
+                         const Timing& tm = {});
 hipError_t launch_cache_step(const Layout& lo, const StepArgs& a, hipStream_t st, const Timing& tm = {});
 hipError_t launch_residency(const Layout& lo, const ResidencyArgs& f, hipStream_t st, const Timing& tm = {});
 // the copies the last residency launch listed for layers l0 .. l0 + nl - 1;
 // kind: 0 demand, 1 proactive
 hipError_t launch_copies(const Layout& lo, int l0, int nl, int kind, hipStream_t st, const Timing& tm = {});
 // the FFN round of layers l0 .. l0 + nl - 1, numbers b0 .. of their batch
-hipError_t launch_ffn_up(const Layout& lo, int l0, int b0, int nl, int round, const void* h, hipStream_t st,
+hipError_t launch_ffn_up(const Layout& lo, int l0, int b0, int nl, const void* h, hipStream_t st,
                          const Timing& tm = {});
-hipError_t launch_ffn_down(const Layout& lo, int l0, int b0, int nl, int round, hipStream_t st, const Timing& tm = {});
+hipError_t launch_ffn_down(const Layout& lo, int l0, int b0, int nl, hipStream_t st, const Timing& tm = {});
 // the combine of layers l0 .. l0 + nl - 1
 hipError_t launch_combine(const Layout& lo, int l0, int nl, float* y, hipStream_t st, const Timing& tm = {});
 // streaming read of per_wave 16-byte units by each wavefront of the probe

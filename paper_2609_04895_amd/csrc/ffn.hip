@@ -24,9 +24,8 @@
 // SwiGLU intermediate is stored in bf16 (the input type of the down kernel's
 // matrix core).
 //
-// fp32: VALU kernels, one lane per output row, fp32 accumulation, over
-// transposed weights (the fill kernel writes them so): the lanes of a
-// wavefront read consecutive floats for each k, 32 k at a time.
+// fp32: the same units on the fp32 matrix core, over transposed weights (the
+// copy kernel writes them so).
 #include "cmoe_internal.h"
 
 namespace cmoe {
@@ -602,82 +601,198 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
 }
 
 // ---------------------------------------------------------------- fp32
-__global__ __launch_bounds__(64) void ffn_up_f32(Layout lo, int l0, int b0, int round,
-                                                 const float* __restrict__ h) {
-    const int l = l0 + blockIdx.y, bl = b0 + blockIdx.y;
-    const int ftn = lo.F / 64;
-    const int e = blockIdx.x / ftn, ft = blockIdx.x - e * ftn;
-    const int m = lo.bcount[(int64_t)bl * lo.N + e];
-    if (m == 0 || lo.round_of[(int64_t)bl * lo.N + e] != round) return;
-    const int32_t* bk = lo.pairs + ((int64_t)bl * lo.N + e) * lo.S;
-    const int slot = lo.slot_of[(int64_t)l * lo.N + e];
-    if (slot < 0 || slot >= lo.n_slots) return;
-    // transposed in the slot (the fill writes W_gate^T, W_up^T as [d][F]):
-    // the 64 lanes, rows f, read 64 consecutive floats per k
-    const float* Wg = reinterpret_cast<const float*>(lo.arena) + ((int64_t)l * lo.n_slots + slot) * lo.expert_elems;
-    const float* Wu = Wg + (int64_t)lo.F * lo.d;
-    const int f = ft * 64 + threadIdx.x;
-    float* act = act_base<float>(lo, bl);
-    for (int tok = 0; tok < m; ++tok) {
-        const int pair = bk[tok];
-        const int s = pair >> 8;
-        const float* x = h + ((int64_t)s * lo.L + l) * lo.d;
-        float ag = 0.0f, au = 0.0f;
-        for (int i0 = 0; i0 < lo.d; i0 += 32) {  // d is a multiple of 64
-            float wg[32], wu[32], xv[32];        // every load of a batch issued before the FMAs
+// On the fp32 matrix core (v_mfma_f32_16x16x4_f32), over transposed weights
+// W^T [k][row] (the copy kernel writes them so).  A workgroup takes 64 rows of
+// one work unit and cuts k into four ranges, one per wavefront (whole blocks of
+// 16), whose partial products are added in LDS in wavefront order.  In a block
+// of 16 k, lane (r, g) loads W^T[k0 + 4 g + j][4 r .. 4 r + 3] for j = 0 .. 3:
+// 256 contiguous bytes per row and 1 KB per instruction; its value i is the A
+// operand (row r, k-slot g) of the product that gives rows 4 r' + i, r' = 0 ..
+// 15, and step j takes k = k0 + 4 g + j on both sides, so that the B operand is
+// value j of the 16-byte load x[k0 + 4 g ..] of token column r.
+// HBM-bound: a pass of up to 16 kNG32 tokens streams the expert once, where
+// one lane per row walked k once for each token.  Measured (6 layers of 60
+// experts, d = 704, F = 448, 13 streams, gate/up and down of a token step):
+// 237 + 119 us before, 123 + 61 us now (5.5 TB/s); the error against fp64
+// falls from 8.2e-7 to 4.2e-7 (four chains instead of one).  kNG32 = 4 holds
+// 362 registers and one wave per SIMD: 139 + 71 us; a budget of four waves per
+// SIMD spills: 130 + 63.
+constexpr int kNG32 = 2;  // token groups (of 16) per pass
+constexpr int kWaves32 = 4;
+
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+
+__device__ inline f32x4 load_stream_f32(const float* p) {
+    return __builtin_nontemporal_load(reinterpret_cast<const f32x4v*>(p));
+}
+
+// acc[m][q][i] += the products of one block of 16 k, M matrices `stride`
+// floats apart, ld floats between their rows.
+template <int M, int NG, int U>
+__device__ inline void block_f32(const float* __restrict__ w, int64_t stride, int64_t ld, const float* const* xb, int k0,
+                                 f32x4 (&acc)[M][NG][4]) {
+    f32x4 a[U][M][4], x[U][NG];
 #pragma unroll
-            for (int u = 0; u < 32; ++u) {
-                wg[u] = Wg[(int64_t)(i0 + u) * lo.F + f];
-                wu[u] = Wu[(int64_t)(i0 + u) * lo.F + f];
-                xv[u] = x[i0 + u];
-            }
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int u = 0; u < 32; ++u) {
-                ag = __builtin_fmaf(wg[u], xv[u], ag);
-                au = __builtin_fmaf(wu[u], xv[u], au);
-            }
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a[u][m][j] = load_stream_f32(w + m * stride + (int64_t)(k0 + 16 * u + j) * ld);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int q = 0; q < NG; ++q) x[u][q] = *reinterpret_cast<const f32x4*>(xb[q] + k0 + 16 * u);
+    __builtin_amdgcn_sched_barrier(0);  // keep every load of the block ahead of the matrix-core work
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+#pragma unroll
+                for (int q = 0; q < NG; ++q)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        acc[m][q][i] =
+                            __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][m][j][i], x[u][q][j], acc[m][q][i], 0, 0, 0);
+}
+
+// The products of 64 rows with up to 16 NG token columns over k in [0, kn),
+// kn a multiple of 16: returned in wavefront 0's acc, summed over the
+// workgroup.  w points at the workgroup's first row of k = 4 g, column 4 r;
+// xb at each token column's value at k = 4 g.
+template <int M, int NG, int U>
+__device__ inline void pass_f32(const float* __restrict__ w, int64_t stride, int64_t ld, const float* const* xb, int kn,
+                                f32x4 (&acc)[M][NG][4], f32x4 (*red)[M * 4][64]) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+        for (int q = 0; q < NG; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[m][q][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int nb = kn / 16, b1 = __builtin_amdgcn_readfirstlane(nb * (wv + 1) / kWaves32);
+    int b = __builtin_amdgcn_readfirstlane(nb * wv / kWaves32);
+    for (; b + U <= b1; b += U) block_f32<M, NG, U>(w, stride, ld, xb, 16 * b, acc);
+    for (; b < b1; ++b) block_f32<M, NG, 1>(w, stride, ld, xb, 16 * b, acc);
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+        if (wv > 0) {
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) red[wv - 1][m * 4 + i][lane] = acc[m][q][i];
         }
-        act[((int64_t)s * lo.K + (pair & 255)) * lo.F + f] = ag / (1.0f + expf(-ag)) * au;
+        __syncthreads();
+        if (wv == 0) {
+#pragma unroll
+            for (int v = 0; v < kWaves32 - 1; ++v)
+#pragma unroll
+                for (int m = 0; m < M; ++m)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[m][q][i] = acc[m][q][i] + red[v][m * 4 + i][lane];
+        }
+        __syncthreads();  // the buffer is free for the next group
     }
 }
 
-__global__ __launch_bounds__(64) void ffn_down_f32(Layout lo, int l0, int b0, int round) {
-    const int l = l0 + blockIdx.y, bl = b0 + blockIdx.y;
-    const int dtn = lo.d / 64;
-    const int e = blockIdx.x / dtn, dt = blockIdx.x - e * dtn;
-    const int m = lo.bcount[(int64_t)bl * lo.N + e];
-    if (m == 0 || lo.round_of[(int64_t)bl * lo.N + e] != round) return;
-    const int32_t* bk = lo.pairs + ((int64_t)bl * lo.N + e) * lo.S;
-    const int slot = lo.slot_of[(int64_t)l * lo.N + e];
-    if (slot < 0 || slot >= lo.n_slots) return;
-    // W_down^T [F][d] in the slot: lanes (rows j) read consecutive floats
-    const float* Wd = reinterpret_cast<const float*>(lo.arena) + ((int64_t)l * lo.n_slots + slot) * lo.expert_elems +
-                      2 * (int64_t)lo.F * lo.d;
-    const int j = dt * 64 + threadIdx.x;
-    const float* act = act_base<float>(lo, bl);
-    for (int tok = 0; tok < m; ++tok) {
-        const int pair = bk[tok];
-        const int s = pair >> 8, k = pair & 255;
-        const float* av = act + ((int64_t)s * lo.K + k) * lo.F;
-        float acc = 0.0f;
-        for (int f0 = 0; f0 < lo.F; f0 += 32) {  // F is a multiple of 64
-            float wd[32], a32[32];
+// Gate/up of tokens [t0, t0 + 16 NG) of a unit of m tokens: rows 64 ft .. of F.
+template <int NG, int U>
+__device__ inline void up_f32(const Layout& lo, int l, int bl, int ft, const int32_t* __restrict__ bk, int t0, int m,
+                              const float* __restrict__ slot, const float* __restrict__ h, f32x4 (*red)[8][64]) {
+    const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4, F = lo.F;
+    int pr[NG];
+    const float* xb[NG];
 #pragma unroll
-            for (int u = 0; u < 32; ++u) {
-                wd[u] = Wd[(int64_t)(f0 + u) * lo.d + j];
-                a32[u] = av[f0 + u];
+    for (int q = 0; q < NG; ++q) pr[q] = bk[min(t0 + 16 * q + r, m - 1)];
+#pragma unroll
+    for (int q = 0; q < NG; ++q) xb[q] = h + ((int64_t)(pr[q] >> 8) * lo.L + l) * lo.d + 4 * g;
+    f32x4 acc[2][NG][4];
+    pass_f32<2, NG, U>(slot + (int64_t)4 * g * F + 64 * ft + 4 * r, (int64_t)F * lo.d, F, xb, lo.d, acc, red);
+    if (threadIdx.x >= 64) return;
+    float* act = act_base<float>(lo, bl);
+    // product i, value v: row 4 (4 g + v) + i, token column r
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+        if (t0 + 16 * q + r < m) {
+            float* o = act + ((int64_t)(pr[q] >> 8) * lo.K + (pr[q] & 255)) * F + 64 * ft + 16 * g;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                f32x4 y;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float a = acc[0][q][i][v];
+                    y[i] = a / (1.0f + expf(-a)) * acc[1][q][i][v];
+                }
+                *reinterpret_cast<f32x4*>(o + 4 * v) = y;
             }
-#pragma unroll
-            for (int u = 0; u < 32; ++u) acc = __builtin_fmaf(wd[u], a32[u], acc);
         }
-        const float gk = lo.gates[((int64_t)l * lo.S + s) * lo.K + k];
-        reinterpret_cast<float*>(lo.yp)[(((int64_t)bl * lo.S + s) * lo.K + k) * lo.d + j] = gk * acc;
+    }
+}
+
+template <int NG, int U>
+__device__ inline void down_f32(const Layout& lo, int l, int bl, int dt, const int32_t* __restrict__ bk, int t0, int m,
+                                const float* __restrict__ slot, f32x4 (*red)[4][64]) {
+    const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4, d = lo.d;
+    const float* act = act_base<float>(lo, bl);
+    int pr[NG];
+    const float* xb[NG];
+#pragma unroll
+    for (int q = 0; q < NG; ++q) pr[q] = bk[min(t0 + 16 * q + r, m - 1)];
+#pragma unroll
+    for (int q = 0; q < NG; ++q) xb[q] = act + ((int64_t)(pr[q] >> 8) * lo.K + (pr[q] & 255)) * lo.F + 4 * g;
+    f32x4 acc[1][NG][4];
+    pass_f32<1, NG, U>(slot + (int64_t)2 * lo.F * d + (int64_t)4 * g * d + 64 * dt + 4 * r, 0, d, xb, lo.F, acc, red);
+    if (threadIdx.x >= 64) return;
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+        if (t0 + 16 * q + r < m) {
+            const int s = pr[q] >> 8, k = pr[q] & 255;
+            const float gk = lo.gates[((int64_t)l * lo.S + s) * lo.K + k];
+            float* o = static_cast<float*>(lo.yp) + (((int64_t)bl * lo.S + s) * lo.K + k) * d + 64 * dt + 16 * g;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                f32x4 y;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) y[i] = gk * acc[0][q][i][v];
+                *reinterpret_cast<f32x4*>(o + 4 * v) = y;
+            }
+        }
+    }
+}
+
+// Workgroup (u, ft): rows 64 ft .. of work unit u.
+template <bool UP>
+__global__ __launch_bounds__(64 * kWaves32) __attribute__((amdgpu_waves_per_eu(3))) void ffn_f32(Layout lo, int l0, int b0, const float* __restrict__ h) {
+    __shared__ f32x4 red[kWaves32 - 1][UP ? 8 : 4][64];
+    const int l = l0 + blockIdx.y, bl = b0 + blockIdx.y;
+    int u, ft;
+    unit_of_block(blockIdx.x, (UP ? lo.F : lo.d) / 64, lo.xcd_units != 0, u, ft);
+    if (u >= lo.max_units) return;
+    const int4 ui = reinterpret_cast<const int4*>(lo.units)[(int64_t)bl * lo.max_units + u];
+    if (ui.x < 0) return;
+    const int e = ui.x & 255, t0 = lo.unit_tokens * (ui.x >> 8), slot = ui.y, m = ui.z;
+    if (m <= 0 || slot < 0 || slot >= lo.n_slots) return;
+    const int32_t* bk = lo.pairs + ((int64_t)bl * lo.N + e) * lo.S + t0;
+    const float* w = static_cast<const float*>(lo.arena) + ((int64_t)l * lo.n_slots + slot) * lo.expert_elems;
+    if (m <= 16) {  // workgroup-uniform
+        if constexpr (UP)
+            up_f32<1, 2>(lo, l, bl, ft, bk, 0, m, w, h, red);
+        else
+            down_f32<1, 4>(lo, l, bl, ft, bk, 0, m, w, red);
+    } else {
+        for (int t = 0; t < m; t += 16 * kNG32) {
+            if constexpr (UP)
+                up_f32<kNG32, 1>(lo, l, bl, ft, bk, t, m, w, h, red);
+            else
+                down_f32<kNG32, 1>(lo, l, bl, ft, bk, t, m, w, red);
+        }
     }
 }
 
 }  // namespace
 
-hipError_t launch_ffn_up(const Layout& lo, int l0, int b0, int nl, int round, const void* h, hipStream_t st,
+hipError_t launch_ffn_up(const Layout& lo, int l0, int b0, int nl, const void* h, hipStream_t st,
                          const Timing& tm) {
     if (lo.dtype == 1) {
         const uint16_t* hb = static_cast<const uint16_t*>(h);
@@ -687,13 +802,13 @@ hipError_t launch_ffn_up(const Layout& lo, int l0, int b0, int nl, int round, co
         else
             launch_kernel(ffn_up_bf16<1>, dim3(unit_groups(lo) * (lo.F / 16), nl), dim3(64), st, tm, lo, l0, b0, hb);
     } else {
-        launch_kernel(ffn_up_f32, dim3(lo.N * (lo.F / 64), nl), dim3(64), st, tm, lo, l0, b0, round,
+        launch_kernel(ffn_f32<true>, dim3(unit_groups(lo) * (lo.F / 64), nl), dim3(64 * kWaves32), st, tm, lo, l0, b0,
                       static_cast<const float*>(h));
     }
     return hipGetLastError();
 }
 
-hipError_t launch_ffn_down(const Layout& lo, int l0, int b0, int nl, int round, hipStream_t st, const Timing& tm) {
+hipError_t launch_ffn_down(const Layout& lo, int l0, int b0, int nl, hipStream_t st, const Timing& tm) {
     if (lo.dtype == 1) {
         const int dtn = lo.d / 32;
         if (lo.ffn_waves == kWaves)
@@ -702,7 +817,8 @@ hipError_t launch_ffn_down(const Layout& lo, int l0, int b0, int nl, int round, 
         else
             launch_kernel(ffn_down_bf16<1>, dim3(unit_groups(lo) * dtn, nl), dim3(64), st, tm, lo, l0, b0);
     } else {
-        launch_kernel(ffn_down_f32, dim3(lo.N * (lo.d / 64), nl), dim3(64), st, tm, lo, l0, b0, round);
+        launch_kernel(ffn_f32<false>, dim3(unit_groups(lo) * (lo.d / 64), nl), dim3(64 * kWaves32), st, tm, lo, l0, b0,
+                      static_cast<const float*>(nullptr));
     }
     return hipGetLastError();
 }

@@ -385,6 +385,7 @@ __global__ __launch_bounds__(kFillThreads) void residency_kernel(Layout lo, Resi
     }
     const int ndem =
         residency_event<true>(lo, sm, bl, f.round, mb_v, ro_v, f.units != 0, f.clk + (pro ? 1 : 0), list);
+    if (f.last && tid < N) lo.bcount[(int64_t)bl * N + tid] = 0;
     if (tid < N) so_g[tid] = sm.so[tid];
     if (tid < P) {
         se_g[tid] = sm.se[tid];

@@ -96,7 +96,7 @@ __device__ inline void mfma_batch(const Raw8<BF16>* ra, const Raw8<BF16>* rb, in
 // block: kRouterWaves wavefronts; KB = k chunks whose loads are issued together (at most the
 // chunks of a wavefront's range)
 template <bool BF16, int KB>
-__global__ __launch_bounds__(64 * kRouterWaves) void router_kernel(Layout lo, int l0, const void* h, int dk) {
+__global__ __launch_bounds__(64 * kRouterWaves) void router_kernel(Layout lo, int l0, const void* h, int dk, int dirty) {
     __shared__ f64x4 red[kRouterWaves - 1][64];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int r16 = lane & 15, g = lane >> 4;
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(64 * kRouterWaves) void router_kernel(Layout lo, in
     const int et = b % et_n;
     const int r = b / et_n;
     const int p = blockIdx.z, bl = blockIdx.y, l = l0 + bl;
-    if (blockIdx.x == 0 && p == 0)  // the cache step counts the layer's buckets from zero
+    if (dirty && blockIdx.x == 0 && p == 0)  // the cache step counts the layer's buckets from zero
         for (int i = threadIdx.x; i < lo.N; i += 64 * kRouterWaves) lo.bcount[(int64_t)bl * lo.N + i] = 0;
     const int i0 = (p * kRouterWaves + wv) * dk;
     const int nch = i0 < lo.d ? (min(i0 + dk, lo.d) - i0) / 32 : 0;  // 32-wide k chunks of this wavefront
@@ -156,24 +156,24 @@ __global__ __launch_bounds__(64 * kRouterWaves) void router_kernel(Layout lo, in
 }
 
 template <bool BF16>
-static void launch_router_t(const Layout& lo, int l, int nl, const void* h, hipStream_t st, const Timing& tm) {
+static void launch_router_t(const Layout& lo, int l0, int nl, const void* h, bool dirty, hipStream_t st, const Timing& tm) {
     const int dk = lo.rdk;  // multiple of 32; the last split may be shorter (d % 32 == 0)
     const dim3 grid(lo.n_r * ((lo.N + 15) / 16) * ((lo.S + 15) / 16), nl, lo.nsplit);
     const dim3 block(64 * kRouterWaves);
     const int cpw = dk / 32;  // k chunks per wavefront
     if (cpw >= 4)
-        launch_kernel(router_kernel<BF16, 4>, grid, block, st, tm, lo, l, h, dk);
+        launch_kernel(router_kernel<BF16, 4>, grid, block, st, tm, lo, l0, h, dk, dirty ? 1 : 0);
     else if (cpw >= 2)
-        launch_kernel(router_kernel<BF16, 2>, grid, block, st, tm, lo, l, h, dk);
+        launch_kernel(router_kernel<BF16, 2>, grid, block, st, tm, lo, l0, h, dk, dirty ? 1 : 0);
     else
-        launch_kernel(router_kernel<BF16, 1>, grid, block, st, tm, lo, l, h, dk);
+        launch_kernel(router_kernel<BF16, 1>, grid, block, st, tm, lo, l0, h, dk, dirty ? 1 : 0);
 }
 
-hipError_t launch_router(const Layout& lo, int l0, int nl, const void* h, hipStream_t st, const Timing& tm) {
+hipError_t launch_router(const Layout& lo, int l0, int nl, const void* h, bool dirty, hipStream_t st, const Timing& tm) {
     if (lo.dtype == 1)
-        launch_router_t<true>(lo, l0, nl, h, st, tm);
+        launch_router_t<true>(lo, l0, nl, h, dirty, st, tm);
     else
-        launch_router_t<false>(lo, l0, nl, h, st, tm);
+        launch_router_t<false>(lo, l0, nl, h, dirty, st, tm);
     return hipGetLastError();
 }
 
