@@ -22,6 +22,9 @@ constexpr int kCopyBlocksDevice = 512, kCopyBlocksHost = 128;
 // tokens: 64 with one wavefront per workgroup, 128 in the grouped launch
 // (whose workgroups stage the activations in LDS for the four row tiles)
 constexpr int kUnitTokens = 64, kUnitTokensGrouped = 128;
+// grouped bf16 shape: units of more than this many tokens have launches of
+// their own, whose wavefronts take two row tiles
+constexpr int kLightTokens = 32;
 
 // Every pointer the kernels use, carved out of the caller's buffers.
 struct Layout {
@@ -29,6 +32,8 @@ struct Layout {
     int32_t G;             // layers per batch: the per-batch buffers below hold G layers
     int32_t iT, iS;        // router slot of the Temporal / Spatio Router, -1 if not used
     int32_t max_units;     // FFN work units per layer step, at most N + ceil(S K / kUnitTokens)
+    int32_t max_heavy;     // units of more than kLightTokens tokens per layer step, at most (grouped bf16
+                           // shape; else 0): the first max_heavy entries of units
     int32_t unit_tokens;   // tokens per work unit: kUnitTokens, or kUnitTokensGrouped (grouped launch)
     int32_t ffn_waves;     // wavefronts per bf16 FFN workgroup: 1, or 4 (grouped: units of more
                            // than 16 tokens share their activations through LDS)
@@ -73,9 +78,11 @@ struct Layout {
     int32_t* pairs;             // [G][N][S]   (stream << 8) | k of each token of an expert
     void* act;                  // [G][S][K][F] SwiGLU intermediate (dtype)
     void* yp;                   // [G][S][K][d] gated expert outputs (dtype)
-    int32_t* units;             // [G][max_units][4] FFN work units of the current round, heaviest
-                                //             first: {(pass << 8) | expert, slot, tokens, 0},
-                                //             {-1, -1, 0, 0} past the end
+    int32_t* units;             // [G][max_units][4] FFN work units of the current round:
+                                //             {(pass << 8) | expert, slot, tokens, 0}, the big ones
+                                //             from entry 0, the others from entry max_heavy, each list
+                                //             heaviest first if some bucket takes several passes;
+                                //             {-1, -1, 0, 0} past the end of a list
     int32_t* round_of;          // [G][N]      FFN round of each expert executed by the layer
                                 //             step, -1 if not executed
 };
@@ -133,10 +140,12 @@ hipError_t launch_residency(const Layout& lo, const ResidencyArgs& f, hipStream_
 // the copies the last residency launch listed for layers l0 .. l0 + nl - 1;
 // kind: 0 demand, 1 proactive
 hipError_t launch_copies(const Layout& lo, int l0, int nl, int kind, hipStream_t st, const Timing& tm = {});
-// the FFN round of layers l0 .. l0 + nl - 1, numbers b0 .. of their batch
-hipError_t launch_ffn_up(const Layout& lo, int l0, int b0, int nl, const void* h, hipStream_t st,
-                         const Timing& tm = {});
-hipError_t launch_ffn_down(const Layout& lo, int l0, int b0, int nl, hipStream_t st, const Timing& tm = {});
+// the FFN round of layers l0 .. l0 + nl - 1, numbers b0 .. of their batch; with
+// max_heavy > 0 a launch of its own (heavy) for the big units comes first
+hipError_t launch_ffn_up(const Layout& lo, int l0, int b0, int nl, const void* h, hipStream_t st, const Timing& tm = {},
+                         const Timing& heavy = {});
+hipError_t launch_ffn_down(const Layout& lo, int l0, int b0, int nl, hipStream_t st, const Timing& tm = {},
+                           const Timing& heavy = {});
 // the combine of layers l0 .. l0 + nl - 1
 hipError_t launch_combine(const Layout& lo, int l0, int nl, float* y, hipStream_t st, const Timing& tm = {});
 // streaming read of per_wave 16-byte units by each wavefront of the probe

@@ -39,13 +39,11 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kNG = 4;          // token groups (of 16) per pass when a unit holds more than 16
 static_assert(kUnitTokens == 16 * kNG, "one work unit is one pass over the weights");
 constexpr int kUnroll = 4;      // k chunks per load block, one token group
-constexpr int kUnrollWide = 2;  // k chunks per load block, kNG token groups sharing LDS (grouped launch)
 constexpr int kUnrollSolo = 1;  // k chunks per load block, kNG token groups in one wavefront: this
                                 // path is rare in the launches that use it, and a deeper block would
                                 // set the register budget (and so the occupancy) of the whole kernel
-constexpr int kWaves = 4;       // wavefronts per grouped workgroup: consecutive row tiles of one work unit
-constexpr int kNGWide = kUnitTokensGrouped / 16;  // token groups of the widest pass (grouped launch)
-static_assert(kNGWide == 8, "the wide staging split gives each thread four of the eight groups");
+constexpr int kWaves = 4;       // wavefronts per grouped or heavy workgroup, on consecutive row tiles of one unit
+static_assert(kUnitTokensGrouped == 128, "the widest heavy pass takes eight token groups");
 
 __device__ inline bf16x8 as_bf16x8(uint4 v) {
     bf16x8 r;
@@ -110,7 +108,7 @@ __device__ inline void unit_of_block(int b, int wgn, bool xcd, int& u, int& j) {
     }
 }
 
-inline int unit_groups(const Layout& lo) { return lo.xcd_units ? (lo.max_units + 7) / 8 * 8 : lo.max_units; }
+inline int unit_groups(const Layout& lo, int units) { return lo.xcd_units ? (units + 7) / 8 * 8 : units; }
 
 __device__ inline const uint16_t* slot_base(const Layout& lo, int l, int slot) {
     return reinterpret_cast<const uint16_t*>(lo.arena) + ((int64_t)l * lo.n_slots + slot) * lo.expert_elems;
@@ -177,170 +175,133 @@ __device__ inline void mfma_pass(const uint4* __restrict__ tile, int nchunk, con
     for (; c < nchunk; ++c) mfma_block<NG, 1>(tile, c, xb, acc0, acc1);
 }
 
-// Grouped launch, units of more than 16 tokens: the kWaves wavefronts of a
-// workgroup (row tiles of the same unit) load the activations of each block
-// of U k-chunks from global memory once, into LDS, and read their B
-// fragments from there.
-// Slot (group q, chunk i, half hh) of a buffer holds, for lane (r, g), token
-// column r's 8 values at k = 64 (c + i) + 32 hh + 8 g.  Two buffers: one
-// barrier per block.
-template <int U>
-struct HeavyLds {
-    uint4 x[2][kNG * U * 2][64];
-};
-static_assert(kWaves == 4, "the staging split below assumes 4 wavefronts");
+// Grouped shape, units of more than 16 tokens: the kWaves wavefronts of a
+// workgroup take consecutive row tiles of one unit, T each, load the
+// activations of each block of U k-chunks from global memory once, into LDS,
+// and read their B fragments from there.  NG token groups of 16, columns past
+// the bucket repeating its last token.
+//
+// What bounds it: the L1 caches, whose misses in flight were all in use 69% of
+// the time (128 experts d = 2048, F = 768, 64 tokens each; a third of the
+// lines are activations): more loads in flight per wavefront only made each
+// take longer, a second block of weights in flight included.  So fewer lines:
+// a staging load takes whole 128-byte lines (8 tokens x one chunk; 16 tokens x
+// half a line fetched each line twice), and with many tokens per expert the
+// big units run in a launch of their own with T = 2, which halves the
+// activation lines and the LDS reads per byte of weights at two wavefronts per
+// SIMD.  Measured, gate/up and down of a layer with 64 tokens per expert:
+// 158 + 92 us with half lines, 150 + 88 us with whole lines, 146 + 85 us with
+// T = 2; with 128 tokens per expert of d = F = 2880: 370 + 200, 320 + 175 and
+// 275 + 146 us.  T = 2 for units of 17 to 32 tokens is slower than T = 1 at
+// four wavefronts per SIMD (16 tokens per expert on average, d = 4096,
+// F = 1536: 2151 + 1176 us against 1980 + 1089 us for four layers).
+//
+// Slot (group q, chunk i, half hh) of the buffer holds, for lane (r, g), token
+// column r's 8 values at k = 64 (c + i) + 32 hh + 8 g.  A staging load of a
+// wavefront covers 8 token rows: lane 8 t + j loads unit j (half j / 4,
+// g = j % 4) of token t, which goes to lane place (r, g) of its half's slot
+// with r xored with 2 j, so that the eight units of a row, 256 bytes or more
+// apart, fall into different banks.
+constexpr int kHeavyTiles = 2;   // row tiles per wavefront of the big units' launch
+constexpr int kHeavySlots = 16;  // slots of one buffer (16 KB), two buffers: NG U <= 8
 
-// Staging loads of thread tid (U = 2): group q, chunk tid / 128, half
-// (tid / 64) % 2, lane tid % 64 for every q, whose token row and k offset are
-// the thread's own xb[q] (a chunk past the end is clamped; it is never used).
-struct Staged {
-    uint4 v[kNG];
-};
+__device__ inline int lds_place(int r, int j) { return 16 * (j & 3) + (r ^ (2 * j)); }
 
-template <int U>
-__device__ inline Staged stage_load(const uint16_t* const* xb, int c, int nchunk, int tid) {
-    static_assert(U == 2, "the staging split assumes two chunks per block");
-    const int i = tid >> 7, hh = (tid >> 6) & 1;
-    const int off = min(c + i, nchunk - 1) * 64 + 32 * hh;
-    Staged st;
-#pragma unroll
-    for (int q = 0; q < kNG; ++q) st.v[q] = *reinterpret_cast<const uint4*>(xb[q] + off);
-    return st;
-}
-
-// LDS stores of the ng groups in use (wavefront-uniform).
-template <int U>
-__device__ inline void stage_store(uint4 (*xs)[64], int tid, int ng, const Staged& st) {
-    const int i = tid >> 7, hh = (tid >> 6) & 1;
-#pragma unroll
-    for (int q = 0; q < kNG; ++q)
-        if (q < ng) xs[(q * U + i) * 2 + hh][tid & 63] = st.v[q];
-}
-
-// One pass of ng (up to kNG) token groups over a 16-row (gate/up) or
-// 2 x 16-row (down) weight tile with the activations shared through LDS.
-// Every wavefront of the workgroup runs the loop (and its barriers); only
-// `active` wavefronts run the matrix-core work.  Every global load is
-// unconditional, so that the waits before the LDS stores cover the staging
-// loads only: the weight loads of an inactive wavefront re-read its tile's
-// first chunk (cached), and staging loads of unused groups repeat the last
-// token.
-template <int U>
-__device__ inline void mfma_pass_shared(const uint4* __restrict__ tile, int nchunk, const uint16_t* const* xb, int ng,
-                                        bool active, HeavyLds<U>& sm, int tid, f32x4* acc0, f32x4* acc1) {
-    const int lane = tid & 63;
-    ng = __builtin_amdgcn_readfirstlane(ng);
-#pragma unroll
-    for (int q = 0; q < kNG; ++q) {
-        acc0[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-        acc1[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+// The staging loads of a block: load n = kPer w + i of wavefront w takes token
+// half th of group q and one chunk.
+template <int NG, int U>
+struct Staging {
+    static constexpr int kPer = NG * U * 2 / kWaves;
+    static_assert(NG * U * 2 <= kHeavySlots && NG * U * 2 % kWaves == 0, "the loads fill the wavefronts evenly");
+    // token row (of the unit) whose values this lane loads in its load i
+    __device__ static __forceinline__ int row(int tid, int i) {
+        const int n = kPer * (tid >> 6) + i, q = n / (2 * U), th = n % (2 * U) / U;
+        return 16 * q + 8 * th + ((tid >> 3) & 7);
     }
+    __device__ static __forceinline__ void load(u32x4 (&v)[kPer], const uint16_t* const (&xs)[kPer], int c, int nchunk,
+                                                int wv) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int ch = (kPer * wv + i) % U;
+            v[i] = *reinterpret_cast<const u32x4*>(xs[i] + min(c + ch, nchunk - 1) * 64);
+        }
+    }
+    __device__ static __forceinline__ void store(const u32x4 (&v)[kPer], u32x4 (*x)[64], int tid, int wv) {
+        const int t = (tid >> 3) & 7, j = tid & 7;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int n = kPer * wv + i, q = n / (2 * U), th = n % (2 * U) / U, ch = n % U;
+            x[(q * U + ch) * 2 + (j >> 2)][lds_place(8 * th + t, j)] = v[i];
+        }
+    }
+};
+
+__device__ inline u32x4 load_stream4(const uint4* p) {
+    return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+}
+__device__ inline f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// One pass of NG token groups over T weight tiles (16-row gate/up or
+// 2 x 16-row down), `next` 16-byte units apart.  Every wavefront of the
+// workgroup runs the loop and its barriers; a wavefront that is not `active` (no
+// tile left for it) re-reads the first tile's first chunk (cached), and its
+// products are dropped.  Every global load is unconditional, so that the waits
+// before the LDS stores cover the staging loads only.  No branch in the loop:
+// one around the matrix-core work made the compiler copy the accumulators.
+template <int T, int NG, int U>
+__device__ __forceinline__ void mfma_pass_heavy(const uint4* __restrict__ tile, int64_t next, int nchunk,
+                                                const uint16_t* const (&xs)[Staging<NG, U>::kPer], bool active,
+                                                u32x4 (*x)[kHeavySlots][64], int tid, f32x4 (&acc0)[T][NG],
+                                                f32x4 (&acc1)[T][NG]) {
+    using St = Staging<NG, U>;
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int p0 = lds_place(lane & 15, lane >> 4), p1 = lds_place(lane & 15, 4 + (lane >> 4));
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int q = 0; q < NG; ++q) {
+            acc0[t][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+            acc1[t][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
     // The activations of block c + U are loaded while block c computes;
     // their LDS stores then wait only for them, not for the weight loads
-    // issued after them.
-    Staged st = stage_load<U>(xb, 0, nchunk, tid);
+    // issued after them.  Two buffers: one barrier per block.
+    u32x4 st[St::kPer];
+    St::load(st, xs, 0, nchunk, wv);
     int b = 0;
     for (int c = 0; c < nchunk; c += U, b ^= 1) {
-        uint4 A[U][4];
+        u32x4 A[U][T][4];
 #pragma unroll
         for (int i = 0; i < U; ++i) {
             const uint4* ch = tile + (int64_t)(active ? min(c + i, nchunk - 1) : 0) * 256;
-            A[i][0] = load_stream(ch);
-            A[i][1] = load_stream(ch + 64);
-            A[i][2] = load_stream(ch + 128);
-            A[i][3] = load_stream(ch + 192);
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) A[i][t][j] = load_stream4(ch + t * next + 64 * j);
         }
-        stage_store<U>(sm.x[b], tid, ng, st);
+        St::store(st, x[b], tid, wv);
         __syncthreads();
-        st = stage_load<U>(xb, c + U, nchunk, tid);
-        if (!active) continue;
+        St::load(st, xs, c + U, nchunk, wv);
 #pragma unroll
-        for (int q = 0; q < kNG; ++q) {
-            if (q >= ng) break;
-            uint4 X[U][2];
+        for (int i = 0; i < U; ++i) {
+            if (U == 1 || c + i < nchunk) {
 #pragma unroll
-            for (int i = 0; i < U; ++i) {
-                X[i][0] = sm.x[b][(q * U + i) * 2][lane];
-                X[i][1] = sm.x[b][(q * U + i) * 2 + 1][lane];
-            }
+                for (int q = 0; q < NG; ++q) {
+                    if (q % 2 == 0) __builtin_amdgcn_sched_barrier(0);  // bounds the B fragments held at once
+                    const u32x4 X0 = x[b][(q * U + i) * 2][p0], X1 = x[b][(q * U + i) * 2 + 1][p1];
 #pragma unroll
-            for (int i = 0; i < U; ++i) {
-                if (c + i < nchunk) {
-                    acc0[q] = mfma_bf16(A[i][0], X[i][0], acc0[q]);
-                    acc0[q] = mfma_bf16(A[i][1], X[i][1], acc0[q]);
-                    acc1[q] = mfma_bf16(A[i][2], X[i][0], acc1[q]);
-                    acc1[q] = mfma_bf16(A[i][3], X[i][1], acc1[q]);
+                    for (int t = 0; t < T; ++t) {
+                        acc0[t][q] = mfma_bf16(A[i][t][0], X0, acc0[t][q]);
+                        acc1[t][q] = mfma_bf16(A[i][t][2], X0, acc1[t][q]);
+                    }
+#pragma unroll
+                    for (int t = 0; t < T; ++t) {
+                        acc0[t][q] = mfma_bf16(A[i][t][1], X1, acc0[t][q]);
+                        acc1[t][q] = mfma_bf16(A[i][t][3], X1, acc1[t][q]);
+                    }
                 }
-            }
-        }
-    }
-}
-
-// Grouped launch, units of 65 to kUnitTokensGrouped tokens (a hot expert's
-// tokens in one pass, so its weights are streamed once): the activations of
-// one k chunk for all eight token groups (16 KB) are staged in LDS once per
-// workgroup, two buffers, one barrier per chunk.  Slot (group q, half hh)
-// holds, for lane (r, g), token column r's 8 values at k = 64 c + 32 hh + 8 g.
-// Its 32 KB share the workgroup's LDS with HeavyLds.
-struct WideLds {
-    uint4 x[2][kNGWide * 2][64];
-};
-union GroupedLds {
-    HeavyLds<kUnrollWide> narrow;
-    WideLds wide;
-};
-
-// Staging of thread tid: groups 4 (tid / 128) .. + 3 at half (tid / 64) % 2
-// of chunk c (clamped; a chunk past the end is never used), from the token
-// rows xs of those four groups.
-__device__ __forceinline__ Staged wide_stage_load(const uint16_t* const* xs, int c, int nchunk, int tid) {
-    const int off = min(c, nchunk - 1) * 64 + 32 * ((tid >> 6) & 1);
-    Staged st;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) st.v[q] = *reinterpret_cast<const uint4*>(xs[q] + off);
-    return st;
-}
-
-__device__ __forceinline__ void wide_stage_store(uint4 (*xb)[64], int tid, int ng, const Staged& st) {
-    const int q0 = 4 * (tid >> 7), hh = (tid >> 6) & 1;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-        if (q0 + q < ng) xb[(q0 + q) * 2 + hh][tid & 63] = st.v[q];
-}
-
-// One pass of ng (up to 8) token groups over a 16-row (gate/up) or 2 x 16-row
-// (down) weight tile, the activations shared through LDS, one k chunk per
-// block: the next chunk's weights are loaded while the current one computes.
-// As in the four-group pass, every wavefront runs the loop and its barriers
-// and every global load is unconditional; only `active` wavefronts compute.
-__device__ __forceinline__ void mfma_pass_wide(const uint4* __restrict__ tile, int nchunk, const uint16_t* const* xs, int ng,
-                                      bool active, WideLds& sm, int tid, f32x4* acc0, f32x4* acc1) {
-    const int lane = tid & 63;
-    ng = __builtin_amdgcn_readfirstlane(ng);
-#pragma unroll
-    for (int q = 0; q < kNGWide; ++q) {
-        acc0[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-        acc1[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    Staged st = wide_stage_load(xs, 0, nchunk, tid);
-    int b = 0;
-    for (int c = 0; c < nchunk; ++c, b ^= 1) {
-        uint4 A[4];
-        const uint4* ch = tile + (int64_t)(active ? c : 0) * 256;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) A[j] = load_stream(ch + 64 * j);
-        wide_stage_store(sm.x[b], tid, ng, st);
-        __syncthreads();
-        st = wide_stage_load(xs, c + 1, nchunk, tid);
-        if (active) {
-#pragma unroll
-            for (int q = 0; q < kNGWide; ++q) {
-                if (q >= ng) break;
-                const uint4 X0 = sm.x[b][q * 2][lane], X1 = sm.x[b][q * 2 + 1][lane];
-                acc0[q] = mfma_bf16(A[0], X0, acc0[q]);
-                acc0[q] = mfma_bf16(A[1], X1, acc0[q]);
-                acc1[q] = mfma_bf16(A[2], X0, acc1[q]);
-                acc1[q] = mfma_bf16(A[3], X1, acc1[q]);
             }
         }
     }
@@ -382,101 +343,106 @@ __device__ inline void up_passes(const Layout& lo, int l, int bl, int ft, const 
     }
 }
 
-// A unit of 17 to 16 kNG tokens: one pass with the activations shared by the
-// workgroup.
-__device__ inline void up_heavy(const Layout& lo, int l, int bl, int ft, const int32_t* __restrict__ bk, int m,
-                                const uint4* __restrict__ tileA, const uint16_t* __restrict__ h, int tid,
-                                HeavyLds<kUnrollWide>& sm) {
-    const int lane = tid & 63, r = lane & 15, g = lane >> 4;
-    const int d = lo.d;
+// Work unit u (the residency kernel lays them out) = tokens [ut p, ut (p + 1))
+// of expert e's bucket, ut = lo.unit_tokens: {(p << 8) | e, slot, tokens, 0}.
+struct Unit {
+    int slot, m;         // m = 0: no work
+    const int32_t* bk;   // the unit's tokens
+};
+
+template <bool HEAVY>
+__device__ inline Unit unit_at(const Layout& lo, int bl, int u) {
+    const int n = HEAVY ? lo.max_heavy : lo.max_units - lo.max_heavy;
+    const int4 ui = reinterpret_cast<const int4*>(lo.units)[(int64_t)bl * lo.max_units + (HEAVY ? 0 : lo.max_heavy) +
+                                                            min(u, n - 1)];
+    const int e = ui.x & 255, t0 = lo.unit_tokens * (ui.x >> 8);
+    const bool none = u >= n || ui.x < 0 || ui.y < 0 || ui.y >= lo.n_slots || ui.z <= 0;
+    return Unit{ui.y, none ? 0 : ui.z, lo.pairs + ((int64_t)bl * lo.N + e) * lo.S + t0};
+}
+
+// A unit of up to 16 NG tokens: F-tiles ft .. ft + T - 1 of each wavefront.
+template <int T, int NG, int U>
+__device__ __forceinline__ void up_heavy(const Layout& lo, int l, int bl, int ft, const Unit& un,
+                                         const uint16_t* __restrict__ h, int tid, u32x4 (*x)[kHeavySlots][64]) {
+    const int lane = tid & 63, r = lane & 15, g = lane >> 4, nchunk = lo.d / 64;
+    const bool active = ft < lo.F / 16;  // F / 16 is even: both tiles or none
+    const uint16_t* xs[Staging<NG, U>::kPer];
+#pragma unroll
+    for (int i = 0; i < Staging<NG, U>::kPer; ++i) {
+        const int p = un.bk[min(Staging<NG, U>::row(tid, i), un.m - 1)];
+        xs[i] = h + ((int64_t)(p >> 8) * lo.L + l) * lo.d + 8 * (tid & 7);
+    }
+    const uint4* tile = reinterpret_cast<const uint4*>(slot_base(lo, l, un.slot)) +
+                        (int64_t)(active ? ft : 0) * nchunk * 256 + lane;
+    f32x4 cg[T][NG], cu[T][NG];
+    mfma_pass_heavy<T, NG, U>(tile, (int64_t)nchunk * 256, nchunk, xs, active, x, tid, cg, cu);
+    if (!active) return;
     uint16_t* act = act_base<uint16_t>(lo, bl);
-    int pr[kNG];
-    const uint16_t* xb[kNG];
 #pragma unroll
-    for (int q = 0; q < kNG; ++q) pr[q] = bk[min(16 * q + r, m - 1)];
-#pragma unroll
-    for (int q = 0; q < kNG; ++q) xb[q] = h + ((int64_t)(pr[q] >> 8) * lo.L + l) * d + 8 * g;
-    f32x4 cg[kNG], cu[kNG];
-    mfma_pass_shared<kUnrollWide>(tileA, d / 64, xb, (m + 15) / 16, true, sm, tid, cg, cu);
-#pragma unroll
-    for (int q = 0; q < kNG; ++q) {
+    for (int q = 0; q < NG; ++q) {
         const int tok = 16 * q + r;
-        if (tok < m) {
-            uint2 o;
-            o.x = pack_bf16x2(silu_mul(cg[q][0], cu[q][0]), silu_mul(cg[q][1], cu[q][1]));
-            o.y = pack_bf16x2(silu_mul(cg[q][2], cu[q][2]), silu_mul(cg[q][3], cu[q][3]));
-            const int pair = pr[q];
-            const int64_t row = (int64_t)(pair >> 8) * lo.K + (pair & 255);
-            *reinterpret_cast<uint2*>(act + row * lo.F + ft * 16 + 4 * g) = o;
+        if (tok < un.m) {
+            const int pair = un.bk[tok];
+            uint16_t* o = act + ((int64_t)(pair >> 8) * lo.K + (pair & 255)) * lo.F + 16 * ft + 4 * g;
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                *reinterpret_cast<uint2*>(o + 16 * t) =
+                    make_uint2(pack_bf16x2(silu_mul(cg[t][q][0], cu[t][q][0]), silu_mul(cg[t][q][1], cu[t][q][1])),
+                               pack_bf16x2(silu_mul(cg[t][q][2], cu[t][q][2]), silu_mul(cg[t][q][3], cu[t][q][3])));
         }
     }
 }
 
-// A unit of 65 to kUnitTokensGrouped tokens: one pass, eight token groups,
-// the activations shared by the workgroup.
-__device__ __forceinline__ void up_heavy_wide(const Layout& lo, int l, int bl, int ft, const int32_t* __restrict__ bk, int m,
-                                     const uint4* __restrict__ tileA, const uint16_t* __restrict__ h, int tid,
-                                     WideLds& sm) {
-    const int lane = tid & 63, r = lane & 15, g = lane >> 4;
-    const int d = lo.d, q0 = 4 * (tid >> 7);
-    uint16_t* act = act_base<uint16_t>(lo, bl);
-    const uint16_t* xs[4];  // token rows of this thread's staging groups
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int p = bk[min(16 * (q0 + q) + r, m - 1)];
-        xs[q] = h + ((int64_t)(p >> 8) * lo.L + l) * d + 8 * g;
-    }
-    f32x4 cg[kNGWide], cu[kNGWide];
-    mfma_pass_wide(tileA, d / 64, xs, (m + 15) / 16, true, sm, tid, cg, cu);
-#pragma unroll
-    for (int q = 0; q < kNGWide; ++q) {
-        const int tok = 16 * q + r;
-        if (tok < m) {
-            uint2 o;
-            o.x = pack_bf16x2(silu_mul(cg[q][0], cu[q][0]), silu_mul(cg[q][1], cu[q][1]));
-            o.y = pack_bf16x2(silu_mul(cg[q][2], cu[q][2]), silu_mul(cg[q][3], cu[q][3]));
-            const int pair = bk[tok];
-            const int64_t row = (int64_t)(pair >> 8) * lo.K + (pair & 255);
-            *reinterpret_cast<uint2*>(act + row * lo.F + ft * 16 + 4 * g) = o;
-        }
-    }
-}
-
-// Work unit u (the fill kernel lays them out, heaviest first) = tokens
-// [ut p, ut (p + 1)) of expert e's bucket, ut = lo.unit_tokens; workgroup
-// (u, j) runs that pass for the W 16-row F-tiles W j + wavefront (F is a
-// multiple of 64, so every wavefront has a tile).  W = 1: every wavefront
-// on its own; W = kWaves: grouped.
-template <int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void ffn_up_bf16(Layout lo, int l0, int b0,
-                                                                                                  const uint16_t* __restrict__ h) {
+// Workgroup (u, j): the W 16-row F-tiles W j + wavefront of unit u (F is a
+// multiple of 64, so every wavefront has a tile).  W = kWaves: units of up to
+// 16 GROUPS tokens, those of more than 16 sharing their activations through
+// LDS; W = 1: a wavefront on its own.
+template <int W, int GROUPS>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void ffn_up_bf16(
+    Layout lo, int l0, int b0, const uint16_t* __restrict__ h) {
     const int l = l0 + blockIdx.y, bl = b0 + blockIdx.y;
-    const int wgn = lo.F / (16 * W);
     int u, j;
-    unit_of_block(blockIdx.x, wgn, lo.xcd_units != 0, u, j);
-    if (u >= lo.max_units) return;
-    const int lane = threadIdx.x & 63;
-    const int ft = j * W + (threadIdx.x >> 6);
-    const int4 ui = reinterpret_cast<const int4*>(lo.units)[(int64_t)bl * lo.max_units + u];  // expert, pass, slot, tokens in one load
-    if (ui.x < 0) return;
-    const int e = ui.x & 255, t0 = lo.unit_tokens * (ui.x >> 8), slot = ui.y, m = ui.z;
-    if (m <= 0 || slot < 0 || slot >= lo.n_slots) return;
-    const int32_t* bk = lo.pairs + ((int64_t)bl * lo.N + e) * lo.S + t0;
+    unit_of_block(blockIdx.x, lo.F / (16 * W), lo.xcd_units != 0, u, j);
+    const Unit un = unit_at<false>(lo, bl, u);
+    if (un.m == 0) return;
+    const int lane = threadIdx.x & 63, ft = j * W + (threadIdx.x >> 6);
     // packed slot layout: chunk c of this row tile is 256 units of 16 bytes,
     // gate half 0, gate half 1, up half 0, up half 1, each 64 units
     const uint4* tileA =
-        reinterpret_cast<const uint4*>(slot_base(lo, l, slot)) + (int64_t)ft * (lo.d / 64) * 256 + lane;
-    if (m <= 16) {  // workgroup-uniform
-        up_passes<1, kUnroll>(lo, l, bl, ft, bk, m, tileA, h, lane);
-    } else if constexpr (W == 1) {
-        up_passes<kNG, kUnrollSolo>(lo, l, bl, ft, bk, m, tileA, h, lane);
-    } else {
-        __shared__ GroupedLds sm;
-        if (m <= 16 * kNG)
-            up_heavy(lo, l, bl, ft, bk, m, tileA, h, threadIdx.x, sm.narrow);
+        reinterpret_cast<const uint4*>(slot_base(lo, l, un.slot)) + (int64_t)ft * (lo.d / 64) * 256 + lane;
+    if (un.m <= 16) {  // workgroup-uniform
+        up_passes<1, kUnroll>(lo, l, bl, ft, un.bk, un.m, tileA, h, lane);
+    } else if constexpr (GROUPS > 0) {
+        __shared__ u32x4 x[2][kHeavySlots][64];
+        if (GROUPS == 2 || un.m <= 32)
+            up_heavy<1, 2, 4>(lo, l, bl, ft, un, h, threadIdx.x, x);
+        else if (un.m <= 64)
+            up_heavy<1, 4, 2>(lo, l, bl, ft, un, h, threadIdx.x, x);
         else
-            up_heavy_wide(lo, l, bl, ft, bk, m, tileA, h, threadIdx.x, sm.wide);
+            up_heavy<1, 8, 1>(lo, l, bl, ft, un, h, threadIdx.x, x);
+    } else {
+        up_passes<kNG, kUnrollSolo>(lo, l, bl, ft, un.bk, un.m, tileA, h, lane);
     }
+}
+
+constexpr int kHeavyRows = kHeavyTiles * kWaves;  // row tiles per heavy workgroup
+
+// Workgroup (u, j): F-tiles 8 j .. 8 j + 7 of a big unit.
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))) void ffn_up_heavy(
+    Layout lo, int l0, int b0, const uint16_t* __restrict__ h) {
+    __shared__ u32x4 x[2][kHeavySlots][64];
+    const int l = l0 + blockIdx.y, bl = b0 + blockIdx.y, tid = threadIdx.x;
+    int u, j;
+    unit_of_block(blockIdx.x, (lo.F / 16 + kHeavyRows - 1) / kHeavyRows, lo.xcd_units != 0, u, j);
+    const Unit un = unit_at<true>(lo, bl, u);
+    if (un.m == 0) return;  // workgroup-uniform
+    const int ft = j * kHeavyRows + kHeavyTiles * (tid >> 6);
+    if (un.m <= 64)
+        up_heavy<kHeavyTiles, 4, 2>(lo, l, bl, ft, un, h, tid, x);
+    else if (un.m <= 96)
+        up_heavy<kHeavyTiles, 6, 1>(lo, l, bl, ft, un, h, tid, x);
+    else
+        up_heavy<kHeavyTiles, 8, 1>(lo, l, bl, ft, un, h, tid, x);
 }
 
 template <int NG, int U>
@@ -508,96 +474,85 @@ __device__ inline void down_passes(const Layout& lo, int l, int bl, int dt, cons
     }
 }
 
-// A unit of 17 to 16 kNG tokens in the grouped launch: one pass with
-// the SwiGLU intermediate shared by the workgroup.  Wavefronts past the last
-// d-tile (d not a multiple of 32 W) take part in the staging and barriers
-// only.
-__device__ inline void down_heavy(const Layout& lo, int l, int bl, int dt, bool active, const int32_t* __restrict__ bk, int m,
-                                  const uint4* __restrict__ tileB, int tid, HeavyLds<kUnrollWide>& sm) {
-    const int lane = tid & 63, r = lane & 15, g = lane >> 4;
-    const int F = lo.F;
+// A unit of up to 16 NG tokens: d-tiles dt .. dt + T - 1 of each wavefront (d / 32
+// is even: all or none).
+template <int T, int NG, int U>
+__device__ __forceinline__ void down_heavy(const Layout& lo, int l, int bl, int dt, const Unit& un, int tid,
+                                           u32x4 (*x)[kHeavySlots][64]) {
+    const int lane = tid & 63, r = lane & 15, g = lane >> 4, nchunk = lo.F / 64;
+    const bool active = dt < lo.d / 32;
     const uint16_t* act = act_base<uint16_t>(lo, bl);
-    int pr[kNG];
-    const uint16_t* xb[kNG];
+    const uint16_t* xs[Staging<NG, U>::kPer];
 #pragma unroll
-    for (int q = 0; q < kNG; ++q) pr[q] = bk[min(16 * q + r, m - 1)];
-#pragma unroll
-    for (int q = 0; q < kNG; ++q) xb[q] = act + ((int64_t)(pr[q] >> 8) * lo.K + (pr[q] & 255)) * F + 8 * g;
-    f32x4 c0[kNG], c1[kNG];
-    mfma_pass_shared<kUnrollWide>(tileB, F / 64, xb, (m + 15) / 16, active, sm, tid, c0, c1);
+    for (int i = 0; i < Staging<NG, U>::kPer; ++i) {
+        const int p = un.bk[min(Staging<NG, U>::row(tid, i), un.m - 1)];
+        xs[i] = act + ((int64_t)(p >> 8) * lo.K + (p & 255)) * lo.F + 8 * (tid & 7);
+    }
+    const uint4* tile = reinterpret_cast<const uint4*>(slot_base(lo, l, un.slot)) + (int64_t)lo.F * lo.d / 4 +
+                        (int64_t)(active ? dt : 0) * nchunk * 256 + lane;
+    f32x4 c0[T][NG], c1[T][NG];
+    mfma_pass_heavy<T, NG, U>(tile, (int64_t)nchunk * 256, nchunk, xs, active, x, tid, c0, c1);
     if (!active) return;
 #pragma unroll
-    for (int q = 0; q < kNG; ++q) {
+    for (int q = 0; q < NG; ++q) {
         const int tok = 16 * q + r;
-        if (tok < m) {
-            const int s = pr[q] >> 8, k = pr[q] & 255;
-            const float gk = lo.gates[((int64_t)l * lo.S + s) * lo.K + k];
-            store_gated(lo, bl, s, k, dt * 32 + 4 * g, gk, c0[q], c1[q]);
-        }
-    }
-}
-
-// A unit of 65 to kUnitTokensGrouped tokens in the grouped launch: one pass,
-// eight token groups, the SwiGLU intermediate shared by the workgroup.
-__device__ __forceinline__ void down_heavy_wide(const Layout& lo, int l, int bl, int dt, bool active, const int32_t* __restrict__ bk,
-                                       int m, const uint4* __restrict__ tileB, int tid, WideLds& sm) {
-    const int lane = tid & 63, r = lane & 15, g = lane >> 4;
-    const int F = lo.F, q0 = 4 * (tid >> 7);
-    const uint16_t* act = act_base<uint16_t>(lo, bl);
-    const uint16_t* xs[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int p = bk[min(16 * (q0 + q) + r, m - 1)];
-        xs[q] = act + ((int64_t)(p >> 8) * lo.K + (p & 255)) * F + 8 * g;
-    }
-    f32x4 c0[kNGWide], c1[kNGWide];
-    mfma_pass_wide(tileB, F / 64, xs, (m + 15) / 16, active, sm, tid, c0, c1);
-    if (!active) return;
-#pragma unroll
-    for (int q = 0; q < kNGWide; ++q) {
-        const int tok = 16 * q + r;
-        if (tok < m) {
-            const int pair = bk[tok];
+        if (tok < un.m) {
+            const int pair = un.bk[tok];
             const int s = pair >> 8, k = pair & 255;
             const float gk = lo.gates[((int64_t)l * lo.S + s) * lo.K + k];
-            store_gated(lo, bl, s, k, dt * 32 + 4 * g, gk, c0[q], c1[q]);
+#pragma unroll
+            for (int t = 0; t < T; ++t) store_gated(lo, bl, s, k, (dt + t) * 32 + 4 * g, gk, c0[t][q], c1[t][q]);
         }
     }
 }
 
 // Workgroup (u, j): the W 32-row d-tiles W j + wavefront of unit u.
-template <int W>
+template <int W, int GROUPS>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void ffn_down_bf16(Layout lo, int l0, int b0) {
     const int l = l0 + blockIdx.y, bl = b0 + blockIdx.y;
     const int dtn = lo.d / 32;
-    const int wgn = (dtn + W - 1) / W;
     int u, j;
-    unit_of_block(blockIdx.x, wgn, lo.xcd_units != 0, u, j);
-    if (u >= lo.max_units) return;
-    const int lane = threadIdx.x & 63;
-    const int dt = j * W + (threadIdx.x >> 6);
-    const bool active = dt < dtn;
-    const int4 ui = reinterpret_cast<const int4*>(lo.units)[(int64_t)bl * lo.max_units + u];  // expert, pass, slot, tokens in one load
-    if (ui.x < 0) return;
-    const int e = ui.x & 255, t0 = lo.unit_tokens * (ui.x >> 8), slot = ui.y, m = ui.z;
-    if (m <= 0 || slot < 0 || slot >= lo.n_slots) return;
-    const int32_t* bk = lo.pairs + ((int64_t)bl * lo.N + e) * lo.S + t0;
+    unit_of_block(blockIdx.x, (dtn + W - 1) / W, lo.xcd_units != 0, u, j);
+    const Unit un = unit_at<false>(lo, bl, u);
+    if (un.m == 0) return;
+    const int lane = threadIdx.x & 63, dt = j * W + (threadIdx.x >> 6);
+    if (dt >= dtn && !(GROUPS > 0 && un.m > 16)) return;  // wavefront-uniform; the path of bigger units has barriers
     // packed slot layout: after the gate/up part (F d / 4 units), chunk c of
     // this 32-row tile is 256 units: rows 0-15 half 0, half 1, rows 16-31
     // half 0, half 1, each 64 units
-    const uint4* tileB = reinterpret_cast<const uint4*>(slot_base(lo, l, slot)) + (int64_t)lo.F * lo.d / 4 +
-                         (int64_t)(active ? dt : 0) * (lo.F / 64) * 256 + lane;
-    if (m <= 16) {  // workgroup-uniform; this path has no barriers
-        if (active) down_passes<1, kUnroll>(lo, l, bl, dt, bk, m, tileB, lane);
-    } else if constexpr (W == 1) {
-        down_passes<kNG, kUnrollSolo>(lo, l, bl, dt, bk, m, tileB, lane);
-    } else {
-        __shared__ GroupedLds sm;
-        if (m <= 16 * kNG)
-            down_heavy(lo, l, bl, dt, active, bk, m, tileB, threadIdx.x, sm.narrow);
+    const uint4* tileB = reinterpret_cast<const uint4*>(slot_base(lo, l, un.slot)) + (int64_t)lo.F * lo.d / 4 +
+                         (int64_t)dt * (lo.F / 64) * 256 + lane;
+    if (un.m <= 16) {
+        down_passes<1, kUnroll>(lo, l, bl, dt, un.bk, un.m, tileB, lane);
+    } else if constexpr (GROUPS > 0) {
+        __shared__ u32x4 x[2][kHeavySlots][64];
+        if (GROUPS == 2 || un.m <= 32)
+            down_heavy<1, 2, 4>(lo, l, bl, dt, un, threadIdx.x, x);
+        else if (un.m <= 64)
+            down_heavy<1, 4, 2>(lo, l, bl, dt, un, threadIdx.x, x);
         else
-            down_heavy_wide(lo, l, bl, dt, active, bk, m, tileB, threadIdx.x, sm.wide);
+            down_heavy<1, 8, 1>(lo, l, bl, dt, un, threadIdx.x, x);
+    } else {
+        down_passes<kNG, kUnrollSolo>(lo, l, bl, dt, un.bk, un.m, tileB, lane);
     }
+}
+
+// Workgroup (u, j): d-tiles 8 j .. 8 j + 7 of a big unit.
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))) void ffn_down_heavy(Layout lo, int l0,
+                                                                                                     int b0) {
+    __shared__ u32x4 x[2][kHeavySlots][64];
+    const int l = l0 + blockIdx.y, bl = b0 + blockIdx.y, tid = threadIdx.x;
+    int u, j;
+    unit_of_block(blockIdx.x, (lo.d / 32 + kHeavyRows - 1) / kHeavyRows, lo.xcd_units != 0, u, j);
+    const Unit un = unit_at<true>(lo, bl, u);
+    if (un.m == 0) return;  // workgroup-uniform
+    const int dt = j * kHeavyRows + kHeavyTiles * (tid >> 6);
+    if (un.m <= 64)
+        down_heavy<kHeavyTiles, 4, 2>(lo, l, bl, dt, un, tid, x);
+    else if (un.m <= 96)
+        down_heavy<kHeavyTiles, 6, 1>(lo, l, bl, dt, un, tid, x);
+    else
+        down_heavy<kHeavyTiles, 8, 1>(lo, l, bl, dt, un, tid, x);
 }
 
 // ---------------------------------------------------------------- fp32
@@ -768,13 +723,11 @@ __global__ __launch_bounds__(64 * kWaves32) __attribute__((amdgpu_waves_per_eu(3
     const int l = l0 + blockIdx.y, bl = b0 + blockIdx.y;
     int u, ft;
     unit_of_block(blockIdx.x, (UP ? lo.F : lo.d) / 64, lo.xcd_units != 0, u, ft);
-    if (u >= lo.max_units) return;
-    const int4 ui = reinterpret_cast<const int4*>(lo.units)[(int64_t)bl * lo.max_units + u];
-    if (ui.x < 0) return;
-    const int e = ui.x & 255, t0 = lo.unit_tokens * (ui.x >> 8), slot = ui.y, m = ui.z;
-    if (m <= 0 || slot < 0 || slot >= lo.n_slots) return;
-    const int32_t* bk = lo.pairs + ((int64_t)bl * lo.N + e) * lo.S + t0;
-    const float* w = static_cast<const float*>(lo.arena) + ((int64_t)l * lo.n_slots + slot) * lo.expert_elems;
+    const Unit un = unit_at<false>(lo, bl, u);  // max_heavy is 0: the whole list
+    if (un.m == 0) return;
+    const int m = un.m;
+    const int32_t* bk = un.bk;
+    const float* w = static_cast<const float*>(lo.arena) + ((int64_t)l * lo.n_slots + un.slot) * lo.expert_elems;
     if (m <= 16) {  // workgroup-uniform
         if constexpr (UP)
             up_f32<1, 2>(lo, l, bl, ft, bk, 0, m, w, h, red);
@@ -793,31 +746,44 @@ __global__ __launch_bounds__(64 * kWaves32) __attribute__((amdgpu_waves_per_eu(3
 }  // namespace
 
 hipError_t launch_ffn_up(const Layout& lo, int l0, int b0, int nl, const void* h, hipStream_t st,
-                         const Timing& tm) {
+                         const Timing& tm, const Timing& heavy) {
+    const int units = unit_groups(lo, lo.max_units - lo.max_heavy), big = unit_groups(lo, lo.max_heavy);
     if (lo.dtype == 1) {
         const uint16_t* hb = static_cast<const uint16_t*>(h);
-        if (lo.ffn_waves == kWaves)
-            launch_kernel(ffn_up_bf16<kWaves>, dim3(unit_groups(lo) * (lo.F / (16 * kWaves)), nl), dim3(64 * kWaves), st,
-                          tm, lo, l0, b0, hb);
-        else
-            launch_kernel(ffn_up_bf16<1>, dim3(unit_groups(lo) * (lo.F / 16), nl), dim3(64), st, tm, lo, l0, b0, hb);
+        const dim3 grid(units * (lo.F / (16 * kWaves)), nl), block(64 * kWaves);
+        if (lo.ffn_waves == kWaves && big > 0) {
+            launch_kernel(ffn_up_heavy, dim3(big * ((lo.F / 16 + kHeavyRows - 1) / kHeavyRows), nl), block, st, heavy, lo,
+                          l0, b0, hb);
+            launch_kernel(ffn_up_bf16<kWaves, 2>, grid, block, st, tm, lo, l0, b0, hb);
+        } else if (lo.ffn_waves == kWaves) {
+            launch_kernel(ffn_up_bf16<kWaves, 8>, grid, block, st, tm, lo, l0, b0, hb);
+        } else {
+            launch_kernel(ffn_up_bf16<1, 0>, dim3(units * (lo.F / 16), nl), dim3(64), st, tm, lo, l0, b0, hb);
+        }
     } else {
-        launch_kernel(ffn_f32<true>, dim3(unit_groups(lo) * (lo.F / 64), nl), dim3(64 * kWaves32), st, tm, lo, l0, b0,
+        launch_kernel(ffn_f32<true>, dim3(units * (lo.F / 64), nl), dim3(64 * kWaves32), st, tm, lo, l0, b0,
                       static_cast<const float*>(h));
     }
     return hipGetLastError();
 }
 
-hipError_t launch_ffn_down(const Layout& lo, int l0, int b0, int nl, hipStream_t st, const Timing& tm) {
+hipError_t launch_ffn_down(const Layout& lo, int l0, int b0, int nl, hipStream_t st, const Timing& tm,
+                           const Timing& heavy) {
+    const int units = unit_groups(lo, lo.max_units - lo.max_heavy), big = unit_groups(lo, lo.max_heavy);
     if (lo.dtype == 1) {
         const int dtn = lo.d / 32;
-        if (lo.ffn_waves == kWaves)
-            launch_kernel(ffn_down_bf16<kWaves>, dim3(unit_groups(lo) * ((dtn + kWaves - 1) / kWaves), nl),
-                          dim3(64 * kWaves), st, tm, lo, l0, b0);
-        else
-            launch_kernel(ffn_down_bf16<1>, dim3(unit_groups(lo) * dtn, nl), dim3(64), st, tm, lo, l0, b0);
+        const dim3 grid(units * ((dtn + kWaves - 1) / kWaves), nl), block(64 * kWaves);
+        if (lo.ffn_waves == kWaves && big > 0) {
+            launch_kernel(ffn_down_heavy, dim3(big * ((dtn + kHeavyRows - 1) / kHeavyRows), nl), block, st, heavy, lo, l0,
+                          b0);
+            launch_kernel(ffn_down_bf16<kWaves, 2>, grid, block, st, tm, lo, l0, b0);
+        } else if (lo.ffn_waves == kWaves) {
+            launch_kernel(ffn_down_bf16<kWaves, 8>, grid, block, st, tm, lo, l0, b0);
+        } else {
+            launch_kernel(ffn_down_bf16<1, 0>, dim3(units * dtn, nl), dim3(64), st, tm, lo, l0, b0);
+        }
     } else {
-        launch_kernel(ffn_f32<false>, dim3(unit_groups(lo) * (lo.d / 64), nl), dim3(64 * kWaves32), st, tm, lo, l0, b0,
+        launch_kernel(ffn_f32<false>, dim3(units * (lo.d / 64), nl), dim3(64 * kWaves32), st, tm, lo, l0, b0,
                       static_cast<const float*>(nullptr));
     }
     return hipGetLastError();

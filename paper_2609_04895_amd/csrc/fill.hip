@@ -153,8 +153,8 @@ constexpr int kWords = 4;  // cache words per thread per batch of loads
 struct ResLds {
     unsigned long long U[2][4];  // unions of the caches: after the access, after the refinement
     int so[kMaxN], se[kMaxN], stp[kMaxN], rnd_s[kMaxN], free_list[kMaxN], victim_list[kMaxN];
-    int lds4[4];         // block-scan slots
-    int lds_cnt[2][16];  // block-count slots: round plan; free slots, entries, units
+    int lds4[8];         // block-scan slots
+    int lds_cnt[2][20];  // block-count slots: round plan; free slots, entries, units
     __align__(16) int key[kMaxN];
     int by_rank[kMaxN], who[kMaxN], m_rank[kMaxN];
 };
@@ -247,9 +247,10 @@ __device__ __forceinline__ int residency_event(const Layout& lo, ResLds& sm, int
     const int ut = lo.unit_tokens;
     const int mykey = (m_own << 8) | (255 - tid);
     if (units) sm.key[tid] = tid < N ? mykey : -1;  // kFillThreads == kMaxN: every entry is written
-    const bool fl[4] = {is_free, enter, m_own > ut, m_own > 0};
-    int rk[4], n[4];
-    block_counts<4>(fl, rk, n, sm.lds_cnt[1]);
+    const int light = lo.max_heavy > 0 ? kLightTokens : ut;  // tokens of the largest unit of the second list
+    const bool fl[5] = {is_free, enter, m_own > ut, m_own > light, m_own > 0 && m_own <= light};
+    int rk[5], n[5];
+    block_counts<5>(fl, rk, n, sm.lds_cnt[1]);
     const int rf = rk[0], re = rk[1], nfree = n[0], nenter = n[1];
     const bool multi = n[2] > 0;
     if (is_free) free_list[rf] = tid;
@@ -299,10 +300,12 @@ __device__ __forceinline__ int residency_event(const Layout& lo, ResLds& sm, int
     // passes of up to lo.unit_tokens tokens, each stored with its expert's new
     // slot and its token count, so that an FFN wavefront finds all three with
     // one load; {-1, -1, 0, 0} past the last unit.
-    int4* unit4 = reinterpret_cast<int4*>(lo.units) + (int64_t)bl * lo.max_units;
+    int4* big4 = reinterpret_cast<int4*>(lo.units) + (int64_t)bl * lo.max_units;
+    int4* unit4 = big4 + lo.max_heavy;
+    int nbig = n[3], nunit = n[4];
     if (units && !multi) {  // one unit per expert, in ascending order
-        if (m_own > 0) unit4[rk[3]] = int4{e, so[e], m_own, 0};
-        for (int i = n[3] + tid; i < lo.max_units; i += kFillThreads) unit4[i] = int4{-1, -1, 0, 0};
+        if (fl[3]) big4[rk[3]] = int4{e, so[e], m_own, 0};
+        if (fl[4]) unit4[rk[4]] = int4{e, so[e], m_own, 0};
     } else if (units) {
         // otherwise experts with more tokens go first (lower index on ties),
         // so the longest units start first.  Rank of expert e = number of
@@ -330,15 +333,23 @@ __device__ __forceinline__ int residency_event(const Layout& lo, ResLds& sm, int
             m_rank[rank] = m;
         }
         __syncthreads();
+        // full passes of ut tokens, and the last pass, of either list
         const int passes = tid < N ? by_rank[tid] : 0;
-        int total;
-        const int off = block_scan(passes, &total, sm.lds4);
+        const int tail = passes > 0 ? m_rank[tid] - ut * (passes - 1) : 0;
+        const int mine_big = lo.max_heavy > 0 ? (tail > light ? passes : max(passes - 1, 0)) : 0;
+        const int off_big = block_scan(mine_big, &nbig, sm.lds4);
+        const int off = block_scan(passes - mine_big, &nunit, sm.lds4 + 4);
         if (tid < N) {
             const int x = who[tid];
-            for (int q = 0; q < passes; ++q)
-                unit4[off + q] = int4{(q << 8) | x, so[x], min(ut, m_rank[tid] - ut * q), 0};
+            for (int q = 0; q < passes; ++q) {
+                int4* at = q < mine_big ? big4 + off_big + q : unit4 + off + (q - mine_big);
+                *at = int4{(q << 8) | x, so[x], min(ut, m_rank[tid] - ut * q), 0};
+            }
         }
-        for (int i = total + tid; i < lo.max_units; i += kFillThreads) unit4[i] = int4{-1, -1, 0, 0};
+    }
+    if (units) {
+        for (int i = nbig + tid; i < lo.max_heavy; i += kFillThreads) big4[i] = int4{-1, -1, 0, 0};
+        for (int i = nunit + tid; i < lo.max_units - lo.max_heavy; i += kFillThreads) unit4[i] = int4{-1, -1, 0, 0};
     }
     return nent;
 }
