@@ -28,9 +28,9 @@
 // of the causal predecessor).
 //
 // The same kernel groups the layer's (stream, k) selections by expert for the
-// FFN (fixed-capacity buckets filled with integer atomics) and counts the
-// distinct experts executed.  Physical residency is handled by the residency
-// kernel.
+// FFN (fixed-capacity buckets filled with integer atomics).  Physical
+// residency, and the counts of selections and of distinct experts, are the
+// residency kernel's.
 //
 // Fixed fp32 softmax: m = max z; u_e = exp(z_e - m) with the exponential
 // below; the sum is a strided halving over the next power of two P >= N
@@ -491,7 +491,6 @@ __device__ void stream_step(const Layout& lo, const StepArgs& a, int s, int bl, 
         // rest of it.
         bucket = (int64_t)bl * N + my_sel;
         bucket_pos = atomicAdd(&lo.bcount[bucket], 1);
-        if (counted) atomicAdd(&lo.selcount[(int64_t)l * N + my_sel], 1ull);
     }
 
 #pragma unroll
@@ -595,10 +594,7 @@ __device__ void stream_step(const Layout& lo, const StepArgs& a, int s, int bl, 
             }
         }
     }
-    if (lane < K) {
-        lo.pairs[bucket * lo.S + bucket_pos] = (s << 8) | lane;
-        if (counted && bucket_pos == 0) atomicAdd(&lo.active_sum[l], 1ull);
-    }
+    if (lane < K) lo.pairs[bucket * lo.S + bucket_pos] = (s << 8) | lane;
 }
 
 // grid: x = streams, y = layers of the batch; one wavefront per (stream,

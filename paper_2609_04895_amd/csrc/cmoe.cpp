@@ -520,7 +520,7 @@ cmoe_status cmoe_init(const cmoe_config* cfg, const cmoe_weights* w, const cmoe_
         }
     }
 
-    // The fill kernel reads the cold pool directly: resolve its device address
+    // The copy kernel reads the cold pool directly: resolve its device address
     // (a pinned host pool must be hipHostMalloc memory) and refuse pointers the
     // device cannot access rather than fault later.
     const void* pool_dev = w->cold_pool;
@@ -549,9 +549,8 @@ cmoe_status cmoe_init(const cmoe_config* cfg, const cmoe_weights* w, const cmoe_
     hd->scratch_fits = need <= kScratchBytes;
     hd->R = has_spatio(cfg->mode) ? cfg->R : 0;
     hd->main = static_cast<hipStream_t>(main_stream);
-    // proactive loads run on the side stream only when asked for: joined to
-    // the demand fill launch on the main stream they were faster on every
-    // workload measured, a host pool included
+    // proactive loads run on the side stream only when asked for: on the main
+    // stream they were faster on every workload measured, a host pool included
     hd->side_is_main = side_stream == nullptr || side_stream == main_stream || !(cfg->flags & CMOE_FLAG_FILL_ON_SIDE);
     hd->side = hd->side_is_main ? hd->main : static_cast<hipStream_t>(side_stream);
 

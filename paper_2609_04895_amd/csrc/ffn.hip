@@ -3,14 +3,16 @@
 //   a_e = silu(W_gate,e x) * (W_up,e x),  y_(s,k) = g_(s,k) W_down,e a_e,
 //   y_s = sum_k y_(s,k)  (k in ascending order).
 // Each expert's weights are read from its HBM slot once per work unit (a
-// pass over up to 64 of its tokens; nearly every expert needs one), so the
+// pass over up to 64 or 128 of its tokens; nearly every expert needs one), so the
 // layer step streams about |union of selected experts| x expert_bytes: the
 // kernels are HBM-bound.
 //
 // bf16: one wavefront per 16 rows of W_gate and of W_up (gate/up kernel) or
 // per 32 rows of W_down (down kernel), one wavefront per workgroup or four
-// (grouped: consecutive row tiles of one unit, big units sharing their
-// activations through LDS), on the bf16 matrix core
+// (grouped: consecutive row tiles of one unit, units of more than 16 tokens
+// sharing their activations through LDS; with many tokens per expert the big
+// units run in launches of their own, two row tiles per wavefront), on the
+// bf16 matrix core
 // (v_mfma_f32_16x16x32_bf16, fp32 accumulation).  The expert's tokens form the
 // 16 columns of the B operand (groups of 16 tokens; several groups reuse the
 // loaded weights).  Per 64-wide k chunk, lane (r, g) of the A operand holds
@@ -18,7 +20,7 @@
 // of a chunk take k-slots kc + 8 g + {0..7} and kc + 32 + 8 g + {0..7}, the
 // same for both operands.  Each activation load thus reads one contiguous
 // 64-byte half of a token's 128-byte k chunk.
-// The weights come from the expert's HBM slot in packed order (the fill
+// The weights come from the expert's HBM slot in packed order (the copy
 // kernel writes it so): each A operand load of a wavefront reads one
 // contiguous kilobyte and each wavefront streams one contiguous block.  The
 // SwiGLU intermediate is stored in bf16 (the input type of the down kernel's

@@ -374,6 +374,7 @@ __global__ __launch_bounds__(kFillThreads) void residency_kernel(Layout lo, Resi
     const int ro_v = lo.round_of[(int64_t)bl * N + min(tid, N - 1)];
     const int64_t phys0 = lo.phys[layer * 2], phys1 = lo.phys[layer * 2 + 1];
     const int32_t sf_v = lo.step_fills[layer * 2];
+    const unsigned long long sel_v = lo.selcount[(int64_t)layer * N + min(tid, N - 1)], act_v = lo.active_sum[layer];
     unsigned long long w[kWords], wp[kWords];
     load_words<true>(lo, layer, 0, w);
     if (pro) load_words<false>(lo, layer, 0, wp);
@@ -396,6 +397,16 @@ __global__ __launch_bounds__(kFillThreads) void residency_kernel(Layout lo, Resi
     }
     const int ndem =
         residency_event<true>(lo, sm, bl, f.round, mb_v, ro_v, f.units != 0, f.clk + (pro ? 1 : 0), list);
+    // the layer step's selections and distinct experts, from the bucket sizes:
+    // one atomic per selection in the cache step queued at the experts'
+    // counters (cache step of 24 layers and 64 streams 12.2 us with them, 8.1
+    // without; of 48 layers and 256 streams of given logits 36.2 and 32.0; this
+    // launch stays within 0.2 us)
+    if (f.counted && f.round == 0) {
+        if (tid < N) lo.selcount[(int64_t)layer * N + tid] = sel_v + (unsigned)mb_v;
+        const int distinct = __syncthreads_count(tid < N && mb_v > 0);
+        if (tid == 0) lo.active_sum[layer] = act_v + (unsigned)distinct;
+    }
     if (f.last && tid < N) lo.bcount[(int64_t)bl * N + tid] = 0;
     if (tid < N) so_g[tid] = sm.so[tid];
     if (tid < P) {

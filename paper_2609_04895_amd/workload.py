@@ -15,8 +15,7 @@ def config_for(w, C: Optional[int] = None, R: Optional[int] = None, warmup_token
                fills: Optional[str] = None, ffn_shape: Optional[str] = None):
     """ffn_shape: None or "auto" (the library's choice), "single" or "grouped".
     fills: where proactive fills run: None or "auto" (the library's choice:
-    the side stream for a host pool, else with the demand fill), "main" or
-    "side"."""
+    the main stream), "main" or "side"."""
     flags = FILLS[fills] | FFN_SHAPES[ffn_shape]
     return make_config(w.L, w.N, w.K, w.d, w.F, w.C if C is None else C, w.R if R is None else R, w.S, w.mode,
                        w.dtype, w.pool_kind, warmup_tokens, flags, w.policy, w.lrfu_lambda, w.arena_slots)
