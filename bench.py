@@ -12,7 +12,8 @@ second: streams x layers x timed tokens / time.
 Prints one JSON line.  The timed region launches the decode path and nothing
 else.  Besides the throughput the line carries the roofline of the dominant
 kernel (expert gate/up), whose average duration comes from HIP events that a
-second pass of the same length attaches to each of its launches, the cache
+second pass of the same length attaches to each of its launches (a launch
+takes a batch of layers; the figures are per layer step), the cache
 statistics (Hit, AdjHit, Load/token), the CPU oracle's throughput on a bounded
 sample (measured before the process touches the GPU) and, as context only, the
 paper's own hit-rate and traffic figures.
@@ -257,12 +258,13 @@ def overlap_study(w, warmup, steps):
 
     Configurations on the same inputs: A = the workload (full mode, demand and
     proactive loads; proactive copies on the side stream overlap the previous
-    layer's FFN), A_main = the same with the proactive copies in the demand
-    fill launch on the main stream (no overlap), B = update-only (demand loads only, all on the critical
+    layers' FFNs), A_main = the same with the proactive copies on the main
+    stream before the demand copies (no overlap), B = update-only (demand loads only, all on the critical
     path), Z = capacity N (after warm-up nearly every expert stays resident:
     the compute time of the same decode).  c_exp, the time of one expert copy,
-    and the launch cost of a fill with nothing to copy, solve fill time =
-    launches x t0 + copies x c_exp over the fill kernel's HIP events in B and Z.  The exposed load of a configuration is its time per
+    and the cost of a layer step's residency with nothing to copy, solve fill
+    time = layer steps x t0 + copies x c_exp over the residency and copy
+    launches' HIP events in B and Z.  The exposed load of a configuration is its time per
     token minus Z's, corrected for Z's few remaining copies."""
     import synth
     T = warmup + steps
@@ -468,12 +470,13 @@ def main():
         avg_s = ms_up / 1e3 / max(n_up, 1)
         bytes_up = (n_act_p * 2 * w.F * w.d * e) / (w.L * steps) + w.S * w.d * e + w.S * w.K * w.F * e
         gbs = bytes_up / avg_s / 1e9
-        res["roofline"] = {"kernel": "ffn_up_bf16" if w.dtype == 1 else "ffn_up_f32", "bound": "hbm",
+        res["roofline"] = {"kernel": "ffn_up_bf16" if w.dtype == 1 else "ffn_f32", "bound": "hbm",
                            "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS,
                            "traffic": measured_traffic(w), "avg_launch_us": avg_s * 1e6,
                            "algorithmic_bytes_per_launch": bytes_up,
-                           "timed_by": f"HIP events on each of its {n_up} launches in a second pass of {steps} "
-                                       f"tokens after the timed region",
+                           "timed_by": f"HIP events on each of its launches ({n_up} layer steps; a launch takes a batch "
+                                       f"of layers) in a second pass of {steps} tokens after the timed region; "
+                                       f"avg_launch_us and the bytes are per layer step",
                            "second_pass_ms_per_step": p0.elapsed_time(p1) / steps}
 
     A, D, P, Tc = tot["accesses"], tot["demand_misses"], tot["proactive_loads"], tot["tokens"]
