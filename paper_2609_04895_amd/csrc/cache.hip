@@ -478,8 +478,12 @@ __device__ void stream_step(const Layout& lo, const StepArgs& a, int s, int bl, 
             my_sel = e;
         }
     }
+    // the priorities, loaded with the logits, are waited for here: a first use
+    // behind the branch below would wait for the atomic in it as well
+#pragma unroll
+    for (int j = 0; j < NPL; ++j) asm volatile("" : "+v"(polv[j]));
     int64_t bucket = 0;  // lane k < K: bucket of its selection and position in it
-    int bucket_pos = 0;
+    uint32_t bucket_pos = 0;
     if (lane < K) {
         const int64_t o = ((int64_t)l * lo.S + s) * K + lane;
         lo.sel[o] = my_sel;
@@ -488,9 +492,11 @@ __device__ void stream_step(const Layout& lo, const StepArgs& a, int s, int bl, 
         // the bucket does not affect any result (each token is its own
         // column of the expert's matrix products).  The position is used
         // at the end of the step, so the atomic's round trip overlaps the
-        // rest of it.
+        // rest of it; unsigned, since the sign extension of an address offset
+        // was placed here, with a wait for the atomic (256 streams, one layer:
+        // 9.1 us with the wait, 8.5 without).
         bucket = (int64_t)bl * N + my_sel;
-        bucket_pos = atomicAdd(&lo.bcount[bucket], 1);
+        bucket_pos = (uint32_t)atomicAdd(&lo.bcount[bucket], 1);
     }
 
 #pragma unroll
