@@ -609,9 +609,16 @@ __device__ void stream_step(const Layout& lo, const StepArgs& a, int s, int bl, 
 // token, which the router launch has left for every layer of the batch, so
 // one launch takes a batch of layers.  A wavefront is a chain of dependent
 // wave reductions (about 4 us); only the number of them in flight hides it.
-// At 64 streams and 24 layers one launch replaces 24 of 5.9 us.
+// At 64 streams and 24 layers one launch replaces 24 of 5.9 us.  With a.snap one
+// more workgroup copies the slot maps of the batch's one layer (the fill launch
+// that follows reads the copy while it writes the maps).
 template <int NPL, int NR, bool INJECT, int ZS, bool REF>
 __global__ __launch_bounds__(64) void cache_step_kernel(Layout lo, StepArgs a) {
+    if (!REF && (int)blockIdx.x == lo.S) {  // only with a.snap
+        for (int i = threadIdx.x; i < lo.N; i += 64) lo.snap_of[i] = lo.slot_of[(int64_t)a.l0 * lo.N + i];
+        for (int i = threadIdx.x; i < lo.n_slots; i += 64) lo.snap_exp[i] = lo.slot_exp[(int64_t)a.l0 * lo.n_slots + i];
+        return;
+    }
     stream_step<NPL, NR, INJECT, ZS, REF>(lo, a, blockIdx.x, blockIdx.y, threadIdx.x);
 }
 
@@ -651,7 +658,7 @@ hipError_t launch_init(const Layout& lo, hipStream_t st) {
 
 template <int NPL, int NR, bool REF>
 void launch_step_ref(const Layout& lo, const StepArgs& a, hipStream_t st, const Timing& tm) {
-    const dim3 grid(lo.S, a.nl), block(64);
+    const dim3 grid(lo.S + (a.snap ? 1 : 0), a.nl), block(64);
     if (a.flags & kFlagInject)
         launch_kernel(cache_step_kernel<NPL, NR, true, 1, REF>, grid, block, st, tm, lo, a);
     else if (lo.nsplit <= 2)

@@ -10,7 +10,8 @@
 //     main: router GEMV (batch)
 //     main: cache step (batch): refinement, access, retention, counters, buckets
 //     main: residency events (batch): slot maps, copy lists, FFN work units
-//     main: proactive copies (batch, if refining), demand copies (batch)
+//     main: proactive copies (batch, if refining), demand copies (batch); for
+//           one layer with demand copies only, one launch with the events
 //     main: expert gate/up, expert down, combine (batch)
 // With proactive fills on the side stream, each layer's proactive copies run
 // there, and its demand copies on the main stream just before its FFN.
@@ -173,7 +174,8 @@ cmoe_status validate(const cmoe_config* c, Derived* dv) {
 // Offsets of every sub-buffer; used both for sizing and for carving.
 struct Plan {
     int G;  // layers per batch
-    size_t cache, aT, pol, pS, mid, ctr, phys, active_sum, selcount, slot_of, slot_exp, slot_stamp, copy_list, copy_n;
+    size_t cache, aT, pol, pS, mid, ctr, phys, active_sum, selcount, slot_of, slot_exp, slot_stamp, snap_of, snap_exp;
+    size_t copy_list, copy_n;
     size_t state_total;
     size_t zpart, logits, sel, gates, events, step_fills, bcount, pairs, act, yp, units, round_of, ws_total;
     size_t arena;
@@ -226,6 +228,8 @@ Plan make_plan(const cmoe_config* c, const Derived& dv, int G) {
     p.slot_of = take(L * N * 4);
     p.slot_exp = take(L * (size_t)dv.n_slots * 4);
     p.slot_stamp = take(L * (size_t)dv.n_slots * 4);
+    p.snap_of = take(N * 4);
+    p.snap_exp = take((size_t)dv.n_slots * 4);
     p.copy_list = take(L * 2 * N * 4);
     p.copy_n = take(L * 2 * 4);
     p.state_total = o;
@@ -402,8 +406,12 @@ cmoe_status run_token(cmoe_handle* hd, const void* h, float* y, const float* zR,
             HIPCHK(timed(hd, KID_ROUTER, nl,
                          [&](const cmoe::Timing& tm) { return cmoe::launch_router(lo, l0, nl, h, on_scratch, M, tm); }),
                    "router");
-        StepArgs a{l0, nl, hd->R, (int)(hd->g & 1), 0, hd->t, {zR, nullptr, nullptr}};
+        StepArgs a{l0, nl, hd->R, (int)(hd->g & 1), 0, hd->t, 0, {zR, nullptr, nullptr}};
         a.flags = (inject ? cmoe::kFlagInject : 0u) | (refine ? cmoe::kFlagRefine : 0u) | (counted ? cmoe::kFlagCount : 0u);
+        // one layer with demand copies only: its residency event and copies
+        // share a launch
+        const bool one = nl == 1 && !refine && hd->dv.rounds == 1;
+        a.snap = one ? 1 : 0;
         if (hd->dv.iT > 0) a.z[hd->dv.iT] = zT;
         if (hd->dv.iS > 0) a.z[hd->dv.iS] = zS;
         HIPCHK(timed(hd, KID_CACHE, nl, [&](const cmoe::Timing& tm) { return cmoe::launch_cache_step(lo, a, M, tm); }),
@@ -419,7 +427,10 @@ cmoe_status run_token(cmoe_handle* hd, const void* h, float* y, const float* zR,
             const ResidencyArgs f{l0, nl, pro ? 1 : 0, r, counted ? 1 : 0, inject ? 0 : 1,
                                   r + 1 == hd->dv.rounds ? 1 : 0, clk + 1};
             clk += pro ? 2 : 1;
-            HIPCHK(timed(hd, KID_FILL, nl, [&](const cmoe::Timing& tm) { return cmoe::launch_residency(lo, f, M, tm); }),
+            HIPCHK(timed(hd, KID_FILL, nl,
+                         [&](const cmoe::Timing& tm) {
+                             return one ? cmoe::launch_fill(lo, f, M, tm) : cmoe::launch_residency(lo, f, M, tm);
+                         }),
                    "residency");
             if (side) {  // each layer's copies on the side stream, overlapping the FFNs of the layers before
                 HIPCHK(hipEventRecord(hd->ev_access, M), "event record");
@@ -428,7 +439,7 @@ cmoe_status run_token(cmoe_handle* hd, const void* h, float* y, const float* zR,
                     HIPCHK(copies(hd, l, 1, 1, Sd), "copies");
                     HIPCHK(hipEventRecord(hd->ev_pro[l], Sd), "event record");
                 }
-            } else {
+            } else if (!one) {
                 if (pro) HIPCHK(copies(hd, l0, nl, 1, M), "copies");
                 HIPCHK(copies(hd, l0, nl, 0, M), "copies");
             }
@@ -581,6 +592,8 @@ cmoe_status cmoe_init(const cmoe_config* cfg, const cmoe_weights* w, const cmoe_
     lo.slot_of = reinterpret_cast<int32_t*>(sb + p.slot_of);
     lo.slot_exp = reinterpret_cast<int32_t*>(sb + p.slot_exp);
     lo.slot_stamp = reinterpret_cast<int32_t*>(sb + p.slot_stamp);
+    lo.snap_of = reinterpret_cast<int32_t*>(sb + p.snap_of);
+    lo.snap_exp = reinterpret_cast<int32_t*>(sb + p.snap_exp);
     lo.copy_list = reinterpret_cast<int32_t*>(sb + p.copy_list);
     lo.copy_n = reinterpret_cast<int32_t*>(sb + p.copy_n);
     lo.max_units = max_units(cfg, dv);

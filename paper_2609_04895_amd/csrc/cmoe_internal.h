@@ -64,6 +64,8 @@ struct Layout {
     int32_t* slot_of;           // [L][N]      slot of each expert, -1 absent
     int32_t* slot_exp;          // [L][n_slots] expert in each slot, -1 free
     int32_t* slot_stamp;        // [L][n_slots] arena clock at the last use of each slot's expert
+    int32_t* snap_of;           // [N]         slot_of and slot_exp of the layer that a fill launch
+    int32_t* snap_exp;          // [n_slots]   handles, as the cache step before it found them
     int32_t* copy_list;         // [L][2][N]   the last residency launch's copies, demand and proactive:
                                 //             (slot << 8) | expert
     int32_t* copy_n;            // [L][2]      their numbers
@@ -99,6 +101,7 @@ struct StepArgs {
     int32_t psw;        // pS buffer this batch writes (it reads the other one)
     uint32_t flags;
     int32_t t;          // token index (LRU clock)
+    int32_t snap;       // copy layer l0's slot maps for the fill launch that follows
     const float* z[3];  // injected logits [S][L][N] per router slot (kFlagInject)
 };
 
@@ -137,6 +140,9 @@ hipError_t launch_router(const Layout& lo, int l0, int nl, const void* h, bool d
                          const Timing& tm = {});
 hipError_t launch_cache_step(const Layout& lo, const StepArgs& a, hipStream_t st, const Timing& tm = {});
 hipError_t launch_residency(const Layout& lo, const ResidencyArgs& f, hipStream_t st, const Timing& tm = {});
+// the demand event of layer f.l0 (nl 1, not refined, the only round) and its
+// copies in one launch
+hipError_t launch_fill(const Layout& lo, const ResidencyArgs& f, hipStream_t st, const Timing& tm = {});
 // the copies the last residency launch listed for layers l0 .. l0 + nl - 1;
 // kind: 0 demand, 1 proactive
 hipError_t launch_copies(const Layout& lo, int l0, int nl, int kind, hipStream_t st, const Timing& tm = {});

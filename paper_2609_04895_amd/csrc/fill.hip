@@ -13,7 +13,12 @@
 //                     demand one) on its slot maps in LDS, lists the copies of
 //                     each and lays out the layer step's FFN work units;
 //   copy_kernel       walks the listed copies of all layers of the batch in
-//                     pieces of 16 or 32 KB.
+//                     pieces of 16 or 32 KB;
+// or, for a batch of one layer with a demand event only, one:
+//   fill_kernel       every workgroup decides the event by itself and copies
+//                     its share of the pieces.
+// fill_kernel's workgroups read a copy of the slot maps that the cache step has
+// made, and one of them writes the maps.
 // The host never reads the lists.  The pool may be pinned host memory mapped
 // into the device; copies then run over the host link.
 #include "cmoe_internal.h"
@@ -194,10 +199,12 @@ __device__ inline void unite(const Layout& lo, int layer, unsigned long long (&w
 // on return, and list gets the copies ((slot << 8) | expert, in the experts'
 // ascending order).  Returns their number.  Every thread of the workgroup runs
 // it.  m_v, ro_v: this thread's expert's bucket size and (later rounds) its
-// planned round.
+// planned round.  writer: this workgroup stores the round plan and the units.
 template <bool DEMAND>
-__device__ __forceinline__ int residency_event(const Layout& lo, ResLds& sm, int bl, int round, int m_v, int ro_v,
-                                               bool units, int clk, int32_t* list) {
+__device__ __forceinline__ int residency_event(const Layout& lo, const ResidencyArgs& f, ResLds& sm, int bl, int m_v, int ro_v,
+                                               bool writer, int clk, int32_t* list) {
+    const bool units = DEMAND && writer && f.units;
+    const int round = f.round;
     const unsigned long long* U = sm.U[DEMAND ? 0 : 1];
     int *so = sm.so, *se = sm.se, *stp = sm.stp, *rnd_s = sm.rnd_s, *free_list = sm.free_list;
     const int tid = threadIdx.x, e = tid, N = lo.N, P = lo.n_slots;
@@ -230,7 +237,7 @@ __device__ __forceinline__ int residency_event(const Layout& lo, ResLds& sm, int
         } else {
             rnd = e < N ? ro_v : -1;
         }
-        if (round == 0 && e < N) lo.round_of[(int64_t)bl * N + e] = rnd;
+        if (writer && round == 0 && e < N) lo.round_of[(int64_t)bl * N + e] = rnd;
     }
     if (e < N) rnd_s[e] = rnd;
     const bool now = DEMAND && rnd >= 0 && rnd == round;  // executed in this round
@@ -354,13 +361,14 @@ __device__ __forceinline__ int residency_event(const Layout& lo, ResLds& sm, int
     return nent;
 }
 
-// grid: one workgroup per layer of the batch.  Latency-bound (one round trip
-// of loads, then some twelve barriers), so the layers of a batch run side by
-// side.
-__global__ __launch_bounds__(kFillThreads) void residency_kernel(Layout lo, ResidencyArgs f) {
-    __shared__ ResLds sm;
-    const int bl = blockIdx.x, layer = f.l0 + bl, tid = threadIdx.x, N = lo.N, P = lo.n_slots;
-    const bool pro = f.refined && f.round == 0;
+// The residency events of layer f.l0 + bl, decided by the whole workgroup; the
+// copies go to dem and pro (PRO: the token may have refined).  Returns their
+// numbers.  writer: this workgroup stores the new state.
+template <bool PRO>
+__device__ __forceinline__ int2 layer_events(const Layout& lo, const ResidencyArgs& f, ResLds& sm, int bl, bool writer,
+                                             int32_t* dem, int32_t* pro) {
+    const int layer = f.l0 + bl, tid = threadIdx.x, N = lo.N, P = lo.n_slots;
+    const bool refined = PRO && f.refined && f.round == 0;
     int32_t* so_g = lo.slot_of + (int64_t)layer * N;
     int32_t* se_g = lo.slot_exp + (int64_t)layer * P;
     int32_t* st_g = lo.slot_stamp + (int64_t)layer * P;
@@ -369,7 +377,8 @@ __global__ __launch_bounds__(kFillThreads) void residency_kernel(Layout lo, Resi
     // bucket sizes (the executed experts and the FFN work units), the round
     // plan of a later round, the fill counters, and the first batch of cache
     // words of each event.
-    const int so_v = so_g[min(tid, N - 1)], se_v = se_g[min(tid, P - 1)], st_v = st_g[min(tid, P - 1)];
+    const int so_v = (PRO ? so_g : lo.snap_of)[min(tid, N - 1)], se_v = (PRO ? se_g : lo.snap_exp)[min(tid, P - 1)];
+    const int st_v = writer ? st_g[min(tid, P - 1)] : 0;
     const int mb_v = lo.bcount[(int64_t)bl * N + min(tid, N - 1)];
     const int ro_v = lo.round_of[(int64_t)bl * N + min(tid, N - 1)];
     const int64_t phys0 = lo.phys[layer * 2], phys1 = lo.phys[layer * 2 + 1];
@@ -377,7 +386,7 @@ __global__ __launch_bounds__(kFillThreads) void residency_kernel(Layout lo, Resi
     const unsigned long long sel_v = lo.selcount[(int64_t)layer * N + min(tid, N - 1)], act_v = lo.active_sum[layer];
     unsigned long long w[kWords], wp[kWords];
     load_words<true>(lo, layer, 0, w);
-    if (pro) load_words<false>(lo, layer, 0, wp);
+    if (refined) load_words<false>(lo, layer, 0, wp);
     __builtin_amdgcn_sched_barrier(0);
     if (tid < 8) sm.U[tid >> 2][tid & 3] = 0ull;
     if (tid < N) sm.so[tid] = so_v;
@@ -387,16 +396,17 @@ __global__ __launch_bounds__(kFillThreads) void residency_kernel(Layout lo, Resi
     }
     __syncthreads();
     unite<true>(lo, layer, w, sm.U[0]);
-    if (pro) unite<false>(lo, layer, wp, sm.U[1]);
+    if (refined) unite<false>(lo, layer, wp, sm.U[1]);
     __syncthreads();
-    int32_t* list = lo.copy_list + (int64_t)layer * 2 * N;
     int npro = 0;
-    if (pro) {
-        npro = residency_event<false>(lo, sm, bl, 0, 0, -1, false, f.clk, list + N);
+    if (refined) {
+        npro = residency_event<false>(lo, f, sm, bl, 0, -1, writer, f.clk, pro);
         __syncthreads();
     }
-    const int ndem =
-        residency_event<true>(lo, sm, bl, f.round, mb_v, ro_v, f.units != 0, f.clk + (pro ? 1 : 0), list);
+    // the bucket sizes decide nothing but what the writer stores while the
+    // union fits the arena
+    const int ndem = residency_event<true>(lo, f, sm, bl, writer ? mb_v : 0, ro_v, writer, f.clk + (refined ? 1 : 0), dem);
+    if (!writer) return int2{ndem, npro};
     // the layer step's selections and distinct experts, from the bucket sizes:
     // one atomic per selection in the cache step queued at the experts'
     // counters (cache step of 24 layers and 64 streams 12.2 us with them, 8.1
@@ -414,14 +424,27 @@ __global__ __launch_bounds__(kFillThreads) void residency_kernel(Layout lo, Resi
         st_g[tid] = sm.stp[tid];
     }
     if (tid == 0) {
-        lo.copy_n[layer * 2] = ndem;
         lo.step_fills[layer * 2] = (f.round > 0 ? sf_v : 0) + ndem;
         if (f.counted) lo.phys[layer * 2] = phys0 + ndem;
         if (f.round == 0) {
-            lo.copy_n[layer * 2 + 1] = npro;
             lo.step_fills[layer * 2 + 1] = npro;
             if (f.counted && npro) lo.phys[layer * 2 + 1] = phys1 + npro;
         }
+    }
+    return int2{ndem, npro};
+}
+
+// grid: one workgroup per layer of the batch.  Latency-bound (one round trip
+// of loads, then some twelve barriers), so the layers of a batch run side by
+// side.
+__global__ __launch_bounds__(kFillThreads) void residency_kernel(Layout lo, ResidencyArgs f) {
+    __shared__ ResLds sm;
+    const int layer = f.l0 + blockIdx.x;
+    int32_t* list = lo.copy_list + (int64_t)layer * 2 * lo.N;
+    const int2 n = layer_events<true>(lo, f, sm, blockIdx.x, true, list, list + lo.N);
+    if (threadIdx.x == 0) {
+        lo.copy_n[layer * 2] = n.x;
+        if (f.round == 0) lo.copy_n[layer * 2 + 1] = n.y;
     }
 }
 
@@ -524,32 +547,9 @@ struct TransposeCopy {
     }
 };
 
-// The listed copies of layers l0 .. l0 + nl - 1 (nl <= kMaxBatch = 64): every
-// wavefront finds the copies of all layers from one load and a prefix sum, and
-// the workgroups walk the pieces of all copies in turn.  kind: 0 demand, 1
-// proactive.
-template <class COPY>
-__global__ __launch_bounds__(kFillThreads) void copy_kernel(Layout lo, int l0, int nl, int kind) {
-    __shared__ uint4 buf[COPY::kLds / sizeof(uint4)];
-    const int lane = threadIdx.x & 63;
-    const int mine = lane < nl ? lo.copy_n[(l0 + lane) * 2 + kind] : 0;
-    const int below = wave_scan(mine);  // copies of this lane's layer and the ones before it
-    const int ncopies = __builtin_amdgcn_readlane(below, 63);
-    const int pieces = COPY::pieces(lo);
-    const int64_t total = (int64_t)ncopies * pieces, bytes = lo.expert_elems * (lo.dtype == 1 ? 2 : 4);
-    auto piece_of = [&](int64_t item) {  // workgroup-uniform
-        Piece pc{nullptr, nullptr, -1};
-        if (item < total) {
-            const int c = (int)(item / pieces);
-            const int bl = __popcll(__ballot(below <= c));  // layers whose copies all come before this one
-            const int layer = l0 + bl, k = c - (bl > 0 ? __builtin_amdgcn_readlane(below, bl - 1) : 0);
-            const int ent = lo.copy_list[((int64_t)layer * 2 + kind) * lo.N + k];
-            pc.src = static_cast<const char*>(lo.pool) + ((int64_t)layer * lo.N + (ent & 255)) * bytes;
-            pc.dst = static_cast<char*>(lo.arena) + ((int64_t)layer * lo.n_slots + (ent >> 8)) * bytes;
-            pc.piece = (int)(item - (int64_t)c * pieces);
-        }
-        return pc;
-    };
+// The workgroups walk `total` pieces in turn; piece_of(item) finds one.
+template <class COPY, class PIECE_OF>
+__device__ __forceinline__ void copy_pieces(const Layout& lo, int64_t total, uint4* buf, PIECE_OF piece_of) {
     COPY cp;
     Piece pc = piece_of(blockIdx.x);
     if (pc.piece >= 0) cp.load(pc, lo.d, lo.F);
@@ -566,6 +566,73 @@ __global__ __launch_bounds__(kFillThreads) void copy_kernel(Layout lo, int l0, i
     }
 }
 
+__device__ inline int64_t expert_bytes(const Layout& lo) { return lo.expert_elems * (lo.dtype == 1 ? 2 : 4); }
+
+// Piece number `piece` of the copy that list entry ent ((slot << 8) | expert)
+// of a layer asks for.
+__device__ inline Piece piece_at(const Layout& lo, int64_t bytes, int layer, int ent, int piece) {
+    return Piece{static_cast<const char*>(lo.pool) + ((int64_t)layer * lo.N + (ent & 255)) * bytes,
+                 static_cast<char*>(lo.arena) + ((int64_t)layer * lo.n_slots + (ent >> 8)) * bytes, piece};
+}
+
+// The listed copies of layers l0 .. l0 + nl - 1 (nl <= kMaxBatch, a layer per
+// lane): every wavefront finds the copies of all layers from one load and a
+// prefix sum, and the workgroups walk the pieces of all copies.  kind: 0
+// demand, 1 proactive.
+static_assert(kMaxBatch <= 64, "copy_kernel holds one layer of the batch per lane");
+template <class COPY>
+__global__ __launch_bounds__(kFillThreads) void copy_kernel(Layout lo, int l0, int nl, int kind) {
+    __shared__ uint4 buf[COPY::kLds / sizeof(uint4)];
+    const int lane = threadIdx.x & 63;
+    const int mine = lane < nl ? lo.copy_n[(l0 + lane) * 2 + kind] : 0;
+    const int below = wave_scan(mine);  // copies of this lane's layer and the ones before it
+    const int ncopies = __builtin_amdgcn_readlane(below, 63);
+    const int pieces = COPY::pieces(lo);
+    const int64_t total = (int64_t)ncopies * pieces, bytes = expert_bytes(lo);
+    copy_pieces<COPY>(lo, total, buf, [&](int64_t item) {  // workgroup-uniform
+        if (item >= total) return Piece{nullptr, nullptr, -1};
+        const int c = (int)(item / pieces);
+        const int bl = __popcll(__ballot(below <= c));  // layers whose copies all come before this one
+        const int layer = l0 + bl, k = c - (bl > 0 ? __builtin_amdgcn_readlane(below, bl - 1) : 0);
+        return piece_at(lo, bytes, layer, lo.copy_list[((int64_t)layer * 2 + kind) * lo.N + k],
+                        (int)(item - (int64_t)c * pieces));
+    });
+}
+
+// The demand event of layer f.l0 and its copies, the arena holding the union
+// (no rounds).  With one layer there is nothing to run side by side, and a
+// second launch for what is usually an empty copy list costs more than every
+// workgroup deciding the event again, however many streams' caches it reads.
+// Two launches against this one: 8.1 and 4.2 us at 64 streams of the 128-expert
+// shape; a token of given logits 12.0 and 9.3 us at 1 stream, 14.0 and 12.6 at
+// 256, 136 and 134.5 at 8192.
+template <class COPY>
+__global__ __launch_bounds__(kFillThreads) void fill_kernel(Layout lo, ResidencyArgs f) {
+    __shared__ ResLds sm;
+    __shared__ int32_t list[kMaxN];
+    __shared__ uint4 buf[COPY::kLds / sizeof(uint4)];
+    const int ncopies = layer_events<false>(lo, f, sm, 0, blockIdx.x == 0, list, nullptr).x;
+    const int pieces = COPY::pieces(lo);
+    const int64_t total = (int64_t)ncopies * pieces, bytes = expert_bytes(lo);
+    copy_pieces<COPY>(lo, total, buf, [&](int64_t item) {  // workgroup-uniform
+        if (item >= total) return Piece{nullptr, nullptr, -1};
+        const int c = (int)(item / pieces);
+        return piece_at(lo, bytes, f.l0, __builtin_amdgcn_readfirstlane(list[c]), (int)(item - (int64_t)c * pieces));
+    });
+}
+
+// launch(copy type, workgroups) for the type of the weights and the pool
+template <typename F>
+void with_copy(const Layout& lo, F&& launch) {
+    const dim3 blocks(lo.pool_host ? kCopyBlocksHost : kCopyBlocksDevice);
+    if (lo.dtype != 1)
+        launch(TransposeCopy{}, blocks);
+    else if (lo.pool_host)
+        launch(PackedCopy<8>{}, blocks);
+    else
+        launch(PackedCopy<4>{}, blocks);
+}
+
 }  // namespace
 
 hipError_t launch_residency(const Layout& lo, const ResidencyArgs& f, hipStream_t st, const Timing& tm) {
@@ -574,13 +641,16 @@ hipError_t launch_residency(const Layout& lo, const ResidencyArgs& f, hipStream_
 }
 
 hipError_t launch_copies(const Layout& lo, int l0, int nl, int kind, hipStream_t st, const Timing& tm) {
-    if (lo.dtype != 1)
-        launch_kernel(copy_kernel<TransposeCopy>, dim3(lo.pool_host ? kCopyBlocksHost : kCopyBlocksDevice),
-                      dim3(kFillThreads), st, tm, lo, l0, nl, kind);
-    else if (lo.pool_host)
-        launch_kernel(copy_kernel<PackedCopy<8>>, dim3(kCopyBlocksHost), dim3(kFillThreads), st, tm, lo, l0, nl, kind);
-    else
-        launch_kernel(copy_kernel<PackedCopy<4>>, dim3(kCopyBlocksDevice), dim3(kFillThreads), st, tm, lo, l0, nl, kind);
+    with_copy(lo, [&](auto copy, dim3 blocks) {
+        launch_kernel(copy_kernel<decltype(copy)>, blocks, dim3(kFillThreads), st, tm, lo, l0, nl, kind);
+    });
+    return hipGetLastError();
+}
+
+hipError_t launch_fill(const Layout& lo, const ResidencyArgs& f, hipStream_t st, const Timing& tm) {
+    with_copy(lo, [&](auto copy, dim3 blocks) {
+        launch_kernel(fill_kernel<decltype(copy)>, blocks, dim3(kFillThreads), st, tm, lo, f);
+    });
     return hipGetLastError();
 }
 
