@@ -16,8 +16,13 @@ constexpr int kMaxSplit = 4;         // router split-K partials per logit, at mo
 constexpr int kRouterWaves = 4;      // router: wavefronts per workgroup, one k sub-range each
 constexpr int kMaxBatch = 64;        // layers of one batch (one launch of each phase), at most
 // workgroups of a copy launch: out of an HBM pool (measured with the copy
-// kernel's pieces), and over the host link
-constexpr int kCopyBlocksDevice = 512, kCopyBlocksHost = 128;
+// kernel's pieces), and over the host link, which many readers slow down:
+// pieces of 32 KB with 128, 96, 64, 48 and 40 workgroups take 284, 281, 277, 276
+// and 275 us (one layer of the 128-expert shape at one stream, about one expert
+// of 9.4 MB, 280 with one 16-byte load per thread in source order before), 12.00,
+// -, 11.90, 11.88 and 11.94 ms (16 experts of 37.7 MB, 11.98 before); pieces of
+// 16 or 64 KB 11.84 or 12.11 ms and 313 or 297 us
+constexpr int kCopyBlocksDevice = 512, kCopyBlocksHost = 48;
 // FFN work unit: one pass over an expert's weights for up to this many of its
 // tokens: 64 with one wavefront per workgroup, 128 in the grouped launch
 // (whose workgroups stage the activations in LDS for the four row tiles)
