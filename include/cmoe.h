@@ -94,7 +94,8 @@ typedef enum {
  * FFN.  The proactive fills of a layer come before its demand fills: by default
  * in a launch on the main stream; with CMOE_FLAG_FILL_ON_SIDE (and a side
  * stream) they run on the side stream, overlapping the FFNs of the layers
- * before.  Both flags: CMOE_ERR_INVALID_ARG. */
+ * before in the same batch of layers (a batch of one layer has none: its
+ * proactive fills stay on the main stream).  Both flags: CMOE_ERR_INVALID_ARG. */
 #define CMOE_FLAG_FILL_ON_MAIN 0x1u /* proactive fills on the main stream (the default)      */
 #define CMOE_FLAG_FILL_ON_SIDE 0x8u /* proactive fills on the side stream                    */
 /* bf16 expert FFN launch shape.  Single: one wavefront per workgroup, each on
