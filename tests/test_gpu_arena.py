@@ -87,6 +87,8 @@ E2E = [
      "grouped"),
     ("heavy_buckets_single", "gptoss_20b", dict(L=2, N=16, K=4, C=8, R=2, S=200, d=128, F=128, arena_slots=5),
      "single"),
+    # 100 tokens per expert: big units in launches of their own, over two rounds
+    ("big_units_bf16", "gptoss_20b", dict(L=2, N=6, K=3, C=4, R=2, S=200, d=192, F=128, arena_slots=4), "grouped"),
 ]
 
 

@@ -79,8 +79,9 @@ def test_noalloc_with_a_capacity_limited_arena():
 
 
 def test_noalloc_and_step_interleaved_on_one_handle():
-    """A handle with a workspace may take either entry point token by token
-    (L = 3 is odd, so the bucket buffers change parity between tokens)."""
+    """A handle with a workspace may take either entry point token by token (one
+    batch of layers a token, so the prediction buffers change parity between
+    tokens)."""
     from paper_2609_04895_amd import cmoe as B
     from paper_2609_04895_amd.workload import engine_for
     w = small(20, True)
