@@ -80,6 +80,7 @@ enum KernelId { KID_ROUTER = 0, KID_CACHE = 1, KID_FILL = 2, KID_UP = 3, KID_DOW
 struct Derived {
     int NW, n_r, n_slots, nsplit, rdk;
     int rounds;        // FFN rounds per layer step: more than one only for an arena smaller than the union
+    bool union_fits;   // the arena always holds the union of the streams' caches
     int iT, iS;        // router slots of the Temporal / Spatio Router, -1 if not used
     int ffn_waves;     // wavefronts per bf16 FFN workgroup (1 or 4)
     int xcd_units;     // 1: each FFN work unit's workgroups on one XCD
@@ -166,7 +167,8 @@ cmoe_status validate(const cmoe_config* c, Derived* dv) {
     // the executed experts of a layer step (at most min(N, S K)) pass through a
     // smaller arena in rounds of n_slots
     const int64_t max_exec = std::min<int64_t>(c->N, (int64_t)c->S * c->K);
-    dv->rounds = dv->n_slots < max_slots ? (int)((max_exec + dv->n_slots - 1) / dv->n_slots) : 1;
+    dv->union_fits = dv->n_slots == max_slots;
+    dv->rounds = !dv->union_fits ? (int)((max_exec + dv->n_slots - 1) / dv->n_slots) : 1;
     dv->esz = c->dtype == CMOE_BF16 ? 2 : 4;
     dv->expert_bytes = (size_t)3 * c->d * c->F * dv->esz;
     dv->rdk = router_range(c, dv->n_r, cmoe::kMaxSplit);
@@ -411,9 +413,10 @@ cmoe_status run_token(cmoe_handle* hd, const void* h, float* y, const float* zR,
                    "router");
         StepArgs a{l0, nl, hd->R, (int)(hd->g & 1), 0, hd->t, 0, {zR, nullptr, nullptr}};
         a.flags = (inject ? cmoe::kFlagInject : 0u) | (refine ? cmoe::kFlagRefine : 0u) | (counted ? cmoe::kFlagCount : 0u);
-        // one layer with demand copies only: its residency event and copies
-        // share a launch
-        const bool one = nl == 1 && !refine && hd->dv.rounds == 1;
+        // one layer with demand copies only, into an arena that holds the union
+        // of the caches (one that does not may have to evict even in a single
+        // round): its residency event and copies share a launch
+        const bool one = nl == 1 && !refine && hd->dv.union_fits;
         a.snap = one ? 1 : 0;
         if (hd->dv.iT > 0) a.z[hd->dv.iT] = zT;
         if (hd->dv.iS > 0) a.z[hd->dv.iS] = zS;

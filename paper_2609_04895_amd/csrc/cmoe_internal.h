@@ -145,8 +145,8 @@ hipError_t launch_router(const Layout& lo, int l0, int nl, const void* h, bool d
                          const Timing& tm = {});
 hipError_t launch_cache_step(const Layout& lo, const StepArgs& a, hipStream_t st, const Timing& tm = {});
 hipError_t launch_residency(const Layout& lo, const ResidencyArgs& f, hipStream_t st, const Timing& tm = {});
-// the demand event of layer f.l0 (nl 1, not refined, the only round) and its
-// copies in one launch
+// the demand event of layer f.l0 (nl 1, not refined, n_slots enough for the union
+// of the caches) and its copies in one launch
 hipError_t launch_fill(const Layout& lo, const ResidencyArgs& f, hipStream_t st, const Timing& tm = {});
 // the copies the last residency launch listed for layers l0 .. l0 + nl - 1;
 // kind: 0 demand, 1 proactive

@@ -599,8 +599,8 @@ __global__ __launch_bounds__(kFillThreads) void copy_kernel(Layout lo, int l0, i
     });
 }
 
-// The demand event of layer f.l0 and its copies, the arena holding the union
-// (no rounds).  With one layer there is nothing to run side by side, and a
+// The demand event of layer f.l0 and its copies, the arena always holding the
+// union of the caches (so that the bucket sizes decide nothing).  With one layer there is nothing to run side by side, and a
 // second launch for what is usually an empty copy list costs more than every
 // workgroup deciding the event again, however many streams' caches it reads.
 // Two launches against this one: 8.1 and 4.2 us at 64 streams of the 128-expert

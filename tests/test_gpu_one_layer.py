@@ -3,7 +3,8 @@ event and copies its experts in one launch: cache decisions, slot maps, counters
 and copies against the oracle bit for bit, and every slot's contents, while the
 refinement budget moves tokens between that launch and the separate ones.  Sizes:
 cache words in less and more than one batch of loads per thread, three words per
-stream (N = 130), part-filled copy pieces, more copies than one."""
+stream (N = 130), part-filled copy pieces, more copies than one, and arenas that
+do not hold the union of the caches, in one FFN round and in several."""
 import numpy as np
 import pytest
 
@@ -18,18 +19,21 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-@pytest.mark.parametrize("N,K,C,S,d,F,dtype,pool_kind", [
-    (1, 1, 1, 1, 64, 64, "bf16", "device"),
-    (11, 2, 4, 2, 320, 192, "bf16", "device"),
-    (11, 2, 4, 2, 576, 64, "bf16", "host"),
-    (9, 3, 4, 3, 64, 192, "f32", "device"),
-    (130, 5, 20, 37, 64, 64, "bf16", "device"),
-    (256, 8, 40, 300, 64, 64, "f32", "host"),
-    (8, 2, 3, 1100, 64, 64, "bf16", "device"),
+@pytest.mark.parametrize("N,K,C,S,d,F,dtype,pool_kind,P", [
+    (1, 1, 1, 1, 64, 64, "bf16", "device", 0),
+    (11, 2, 4, 2, 320, 192, "bf16", "device", 0),
+    (11, 2, 4, 2, 576, 64, "bf16", "host", 0),
+    (9, 3, 4, 3, 64, 192, "f32", "device", 0),
+    (130, 5, 20, 37, 64, 64, "bf16", "device", 0),
+    (256, 8, 40, 300, 64, 64, "f32", "host", 0),
+    (8, 2, 3, 1100, 64, 64, "bf16", "device", 0),
+    (16, 2, 8, 1, 320, 192, "bf16", "device", 4),   # one round, eight cached experts
+    (40, 2, 12, 2, 128, 576, "bf16", "device", 5),
+    (64, 4, 16, 9, 64, 64, "bf16", "device", 10),   # rounds
 ])
-def test_one_layer(N, K, C, S, d, F, dtype, pool_kind):
+def test_one_layer(N, K, C, S, d, F, dtype, pool_kind, P):
     from paper_2609_04895_amd import cmoe as B
-    name = f"one_layer_{N}_{K}_{C}_{S}_{d}_{F}_{dtype}_{pool_kind}"
+    name = f"one_layer_{N}_{K}_{C}_{S}_{d}_{F}_{dtype}_{pool_kind}_{P}"
     say(name)
     bf, host = dtype == "bf16", pool_kind == "host"
     dt, raw = (torch.bfloat16, torch.int16) if bf else (torch.float32, torch.int32)
@@ -42,12 +46,12 @@ def test_one_layer(N, K, C, S, d, F, dtype, pool_kind):
     w = torch.zeros((1, N, d), dtype=dt, device=dev)
     R = min(3, N)
     cfg = B.make_config(1, N, K, d, F, C, 0, S, B.CMOE_MODE_SPATIO_TEMPORAL, B.CMOE_BF16 if bf else B.CMOE_F32,
-                        B.CMOE_POOL_HOST_PINNED if host else B.CMOE_POOL_DEVICE, warmup_tokens=1)
+                        B.CMOE_POOL_HOST_PINNED if host else B.CMOE_POOL_DEVICE, warmup_tokens=1, arena_slots=P)
     eng = B.Engine(cfg, w, w, w, None, pool)
-    run = oracle.Run(1, N, K, C, 0, S, 1, 1)
+    run = oracle.Run(1, N, K, C, 0, S, 1, 1, arena_slots=P)
     T = 8
     z = logits_sequence(np.random.default_rng(stable_seed(name)), T, S, 1, N, ties=True)
-    n_slots = min(N, S * C)
+    n_slots = P or min(N, S * C)
     for t in range(T):
         if t in (3, 5, 6):  # R = 0, 0, 0, R, R, 0, R, R
             budget = 0 if t == 5 else R
