@@ -271,9 +271,11 @@ Plan batch_plan(const cmoe_config* c, const Derived& dv, size_t limit) {
 }
 
 // What decides whether a configuration may run on the scratch array: the
-// per-step buffers of one layer at a time with two bucket buffers and 4 or 16
-// partial sums per logit.  The plan of one layer per batch needs no more than
-// this, so a configuration within the limit always has a plan that fits.
+// per-step buffers of one layer at a time with two bucket buffers, 4 or 16
+// partial sums per logit and N + S K / 64 work units, or what the plan of one
+// layer per batch takes should that ever be more (the second bucket buffer,
+// N S entries, covers the longer unit lists of today's plan): a configuration
+// within the limit always has a plan that fits.
 size_t scratch_need(const cmoe_config* c, const Derived& dv) {
     const size_t S = c->S, L = c->L, N = c->N, K = c->K;
     const size_t slots = router_splits(c, router_range(c, dv.n_r, 16)) <= 4 ? 4 : 16;
@@ -282,7 +284,7 @@ size_t scratch_need(const cmoe_config* c, const Derived& dv) {
                          L * S * 16, L * 8, 2 * N * 4, 2 * N * S * 4, S * K * (size_t)c->F * dv.esz,
                          S * K * (size_t)c->d * dv.esz, N * 4, (N + (S * K + cmoe::kUnitTokens - 1) / cmoe::kUnitTokens) * 16, N * 4})
         o += align256(bytes);
-    return o;
+    return std::max(o, make_plan(c, dv, 1).ws_total);
 }
 
 // Points the workspace members of lo into the buffer wb (nullptr: none).

@@ -2,6 +2,7 @@
 validates configurations on the host (no GPU needed for any of this)."""
 import ctypes
 import os
+import random
 import re
 
 import pytest
@@ -130,6 +131,38 @@ def test_full_mode_needs_spatio_router():
     st = B.lib().cmoe_init(ctypes.byref(c), ctypes.byref(w), ctypes.byref(bufs), None, None, ctypes.byref(h))
     assert st == B.CMOE_ERR_INVALID_ARG
     assert b"w_spatio" in B.lib().cmoe_last_error()
+
+
+def test_configs_accepted_on_the_scratch_array_fit_it():
+    """A handle without a workspace is refused as unsupported before anything
+    else looks at the device exactly when its per-step buffers may not run on
+    the 64 MiB scratch array; what is not refused must have a plan that fits
+    (one layer: cmoe_query's workspace is that plan).  Sizes around the limit,
+    with many tokens per expert (long work unit lists) and few."""
+    rng = random.Random(3)
+    limit, near = 64 << 20, [0, 0]
+    for _ in range(4000):
+        N = rng.randint(1, 256)
+        K = rng.randint(1, min(64, N))
+        d, F = 64 * rng.randint(1, 24), 64 * rng.randint(1, 24)
+        dtype = rng.randint(0, 1)
+        per_stream = K * (d + F) * (2 if dtype else 4) + N * 4
+        S = max(1, int(limit / per_stream * rng.uniform(0.3, 1.3)))
+        if S * K >= 1 << 23:
+            continue
+        c = cfg(L=1, N=N, K=K, C=N, S=S, d=d, F=F, dtype=dtype, flags=rng.choice((0, B.CMOE_FLAG_FFN_GROUPED)))
+        sizes = B.cmoe_sizes()
+        assert B.lib().cmoe_query(ctypes.byref(c), ctypes.byref(sizes)) == B.CMOE_OK
+        h = ctypes.c_void_p()
+        w = B.cmoe_weights(256, 512, None, None, 1024)
+        bufs = B.cmoe_buffers(256, 512, None)
+        st = B.lib().cmoe_init(ctypes.byref(c), ctypes.byref(w), ctypes.byref(bufs), None, None, ctypes.byref(h))
+        assert st != B.CMOE_OK and not h.value  # no such weights
+        refused = st == B.CMOE_ERR_UNSUPPORTED
+        if not refused:
+            assert sizes.workspace_bytes <= limit, (N, K, S, d, F, dtype)
+        near[refused] += 1
+    assert min(near) > 500
 
 
 def test_misaligned_buffers_rejected():
