@@ -318,7 +318,7 @@ cmoe_status cmoe_concentration(cmoe_handle* hd, int32_t top_m, double* out4);
 /* Measurement utility, not part of the decode path: the rate at which the
  * current device streams `bytes` of device memory at src with the access
  * pattern of the expert weight loads (16-byte nontemporal loads, one
- * contiguous kilobyte per wavefront instruction, eight in flight, each
+ * contiguous kilobyte per wavefront instruction, sixteen in flight, each
  * wavefront walking its own contiguous block).  It is the practical ceiling of
  * the FFN's weight stream, as opposed to the datasheet peak.  src: device
  * memory owned by the caller, only read (its contents do not matter);

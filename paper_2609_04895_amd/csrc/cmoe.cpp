@@ -905,8 +905,7 @@ cmoe_status cmoe_read_probe(const void* src, int64_t bytes, int32_t reps, double
     if (!src || !gbps) return fail(CMOE_ERR_INVALID_ARG, "read probe: src and gbps are required");
     if (reps < 1) return fail(CMOE_ERR_INVALID_ARG, "read probe: reps must be >= 1");
     if (bytes < ((int64_t)64 << 20)) return fail(CMOE_ERR_INVALID_ARG, "read probe: needs a buffer of at least 64 MiB");
-    int64_t read = 0;
-    const int64_t per_wave = cmoe::read_probe_units_per_wave(bytes, &read);
+    const int64_t read = cmoe::read_probe_bytes(bytes);
     cmoe_handle* hd = nullptr;  // no handle: errors do not mark one broken
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e = hipEventCreate(&e0);
@@ -916,7 +915,7 @@ cmoe_status cmoe_read_probe(const void* src, int64_t bytes, int32_t reps, double
         cmoe::Timing tm;
         tm.start = e0;
         tm.stop = e1;
-        e = cmoe::launch_read_probe(src, per_wave, nullptr, tm);
+        e = cmoe::launch_read_probe(src, read, nullptr, tm);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0.0f;
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);

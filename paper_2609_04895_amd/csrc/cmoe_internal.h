@@ -159,10 +159,9 @@ hipError_t launch_ffn_down(const Layout& lo, int l0, int b0, int nl, hipStream_t
                            const Timing& heavy = {});
 // the combine of layers l0 .. l0 + nl - 1
 hipError_t launch_combine(const Layout& lo, int l0, int nl, float* y, hipStream_t st, const Timing& tm = {});
-// streaming read of per_wave 16-byte units by each wavefront of the probe
-// grid; read_probe_units_per_wave gives the largest per_wave that fits in
-// `bytes` and the bytes the grid then reads
-int64_t read_probe_units_per_wave(int64_t bytes, int64_t* read_bytes);
-hipError_t launch_read_probe(const void* src, int64_t per_wave, hipStream_t st, const Timing& tm);
+// streaming read of the read_probe_bytes(bytes) bytes at src: the largest
+// multiple of the probe's block size within `bytes`
+int64_t read_probe_bytes(int64_t bytes);
+hipError_t launch_read_probe(const void* src, int64_t bytes, hipStream_t st, const Timing& tm);
 
 }  // namespace cmoe
