@@ -190,11 +190,14 @@ int unit_tokens(const Derived& dv) { return dv.ffn_waves > 1 ? cmoe::kUnitTokens
 
 // Big work units (more than kLightTokens tokens), at most, where they have
 // launches of their own: in the grouped bf16 shape from 64 tokens per expert on
-// average.  Measured per token on MI355X, with against without (means over
-// eight engines): 1557 against 1600 us at 64 tokens per expert (d = 2048,
-// F = 768, 6 layers), 1785 against 2030 us at 128 (d = F = 2880, 4 layers);
-// with fewer, the second launch's ramp costs more than the big units gain: 1443
-// against 1415 us at 44, 1697 to 1800 against 1600 to 1650 us at 24.
+// average.  Measured per token on MI355X, with against without, in us (means of
+// six engines each, which differ by 1% or less); with fewer tokens the second
+// launch's ramp costs more than the big units gain:
+//   tokens per expert            32         48         56         64         72         96         128
+//   d = 2048, F = 768  x4     947/931  1039/1016  1055/1067  1145/1166  1090/1101  1175/1198  1791/1850
+//   d = F = 2880       x3     941/838   924/880    918/921    946/971    957/985    915/938   1380/1553
+//   d = 4096, F = 1536 x2   1714/1679  1845/1782  1828/1858  1714/1733  1895/2019  1896/1991
+// (x4: 4 layers; 128, 32 and 128 experts).
 int max_heavy(const cmoe_config* c, const Derived& dv) {
     if (c->dtype != CMOE_BF16 || dv.ffn_waves == 1 || (int64_t)c->S * c->K < (int64_t)64 * c->N) return 0;
     return (int)((int64_t)c->S * c->K / (cmoe::kLightTokens + 1));
