@@ -320,8 +320,8 @@ def main():
     ap.add_argument("--arena-slots", type=int, default=None,
                     help="HBM expert slots per layer (default 0: min(N, S C), which holds the union of the caches)")
     ap.add_argument("--fills", choices=["auto", "main", "side"], default="auto",
-                    help="where proactive fills run (auto: the library's choice, one launch with the demand fill "
-                         "on the main stream)")
+                    help="where proactive fills run (auto: the library's choice, the main stream, before the "
+                         "demand fills)")
     ap.add_argument("--ffn-shape", choices=["auto", "single", "grouped"], default="auto",
                     help="bf16 FFN workgroups: one wavefront each, or four sharing big units' activations "
                          "(auto: the library's choice from the average tokens per expert)")

@@ -158,7 +158,12 @@ typedef struct {
 typedef struct {
     size_t arena_bytes;     /* HBM expert slots: L x arena_slots experts         */
     size_t state_bytes;     /* caches, scores, counters, slot maps               */
-    size_t workspace_bytes; /* per-step scratch and the inspectable outputs      */
+    size_t workspace_bytes; /* per-step scratch and the inspectable outputs: the
+                               buffers of as many layers, 64 at most, as stay
+                               within 192 MiB (each phase of a token is one launch
+                               for that many layers), and of one layer at least.
+                               A handle without a workspace runs on the library's
+                               64 MiB scratch array instead (cmoe_step_noalloc)  */
 } cmoe_sizes;
 
 typedef struct {
@@ -296,7 +301,7 @@ cmoe_status cmoe_read(cmoe_handle* hd, int32_t view, void* host_out, size_t byte
  * cmoe_profile_end synchronizes and returns, per kernel id, the summed
  * milliseconds and the number of layer steps the launches covered (a launch
  * that runs a batch of layers counts each of them), so that their quotient is
- * the time per layer step.  Kernel ids: 0 router GEMV, 1 cache step (routing,
+ * the time per layer step (for the combine: per token of all layers).  Kernel ids: 0 router GEMV, 1 cache step (routing,
  * refinement, retention, counters, expert grouping), 2 residency and fill
  * (proactive fills add their time to the layer step they belong to), 3 expert
  * gate/up, 4 expert down (both once per FFN round of a layer), 5 combine

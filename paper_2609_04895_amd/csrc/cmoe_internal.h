@@ -23,9 +23,10 @@ constexpr int kMaxBatch = 64;        // layers of one batch (one launch of each 
 // -, 11.90, 11.88 and 11.94 ms (16 experts of 37.7 MB, 11.98 before); pieces of
 // 16 or 64 KB 11.84 or 12.11 ms and 313 or 297 us
 constexpr int kCopyBlocksDevice = 512, kCopyBlocksHost = 48;
-// FFN work unit: one pass over an expert's weights for up to this many of its
-// tokens: 64 with one wavefront per workgroup, 128 in the grouped launch
-// (whose workgroups stage the activations in LDS for the four row tiles)
+// FFN work unit: up to this many of an expert's tokens: 64 with one wavefront
+// per workgroup, 128 in the grouped launch (whose workgroups stage the
+// activations in LDS for the four row tiles).  In bf16 a unit is one pass over
+// the expert's weights; in fp32 one for every 32 of its tokens
 constexpr int kUnitTokens = 64, kUnitTokensGrouped = 128;
 // grouped bf16 shape: units of more than this many tokens have launches of
 // their own, whose wavefronts take two row tiles
@@ -36,9 +37,11 @@ struct Layout {
     int32_t L, N, K, d, F, C, S, mode, dtype, NW, n_slots, n_r, nsplit, rdk, warmup;
     int32_t G;             // layers per batch: the per-batch buffers below hold G layers
     int32_t iT, iS;        // router slot of the Temporal / Spatio Router, -1 if not used
-    int32_t max_units;     // FFN work units per layer step, at most N + ceil(S K / kUnitTokens)
-    int32_t max_heavy;     // units of more than kLightTokens tokens per layer step, at most (grouped bf16
-                           // shape; else 0): the first max_heavy entries of units
+    int32_t max_units;     // entries of units per layer step: max_heavy, then min(N, S K); without
+                           // max_heavy min(N, S K) + S K / unit_tokens
+    int32_t max_heavy;     // units of more than kLightTokens tokens per layer step, at most
+                           // S K / (kLightTokens + 1) (grouped bf16 shape with many tokens per
+                           // expert; else 0): the first max_heavy entries of units
     int32_t unit_tokens;   // tokens per work unit: kUnitTokens, or kUnitTokensGrouped (grouped launch)
     int32_t ffn_waves;     // wavefronts per bf16 FFN workgroup: 1, or 4 (grouped: units of more
                            // than 16 tokens share their activations through LDS)

@@ -3,9 +3,10 @@
 //   a_e = silu(W_gate,e x) * (W_up,e x),  y_(s,k) = g_(s,k) W_down,e a_e,
 //   y_s = sum_k y_(s,k)  (k in ascending order).
 // Each expert's weights are read from its HBM slot once per work unit (a
-// pass over up to 64 or 128 of its tokens; nearly every expert needs one), so the
-// layer step streams about |union of selected experts| x expert_bytes: the
-// kernels are HBM-bound.
+// pass over up to 64 or 128 of its tokens; nearly every expert needs one; in
+// fp32 a unit of more than 32 tokens takes several passes), so the layer step
+// streams about |union of selected experts| x expert_bytes: the kernels are
+// HBM-bound.
 //
 // bf16: one wavefront per 16 rows of W_gate and of W_up (gate/up kernel) or
 // per 32 rows of W_down (down kernel), one wavefront per workgroup or four
@@ -18,16 +19,17 @@
 // loaded weights).  Per 64-wide k chunk, lane (r, g) of the A operand holds
 // W[row r][kc + 8 g .. + 8] and W[row r][kc + 32 + 8 g .. + 8]; the two MFMAs
 // of a chunk take k-slots kc + 8 g + {0..7} and kc + 32 + 8 g + {0..7}, the
-// same for both operands.  Each activation load thus reads one contiguous
-// 64-byte half of a token's 128-byte k chunk.
+// same for both operands.  Each activation load of a wavefront on its own
+// (units of up to 16 tokens) thus reads one contiguous 64-byte half of a
+// token's 128-byte k chunk; shared activations are loaded in whole chunks.
 // The weights come from the expert's HBM slot in packed order (the copy
 // kernel writes it so): each A operand load of a wavefront reads one
 // contiguous kilobyte and each wavefront streams one contiguous block.  The
 // SwiGLU intermediate is stored in bf16 (the input type of the down kernel's
 // matrix core).
 //
-// fp32: the same units on the fp32 matrix core, over transposed weights (the
-// copy kernel writes them so).
+// fp32: the same units on the fp32 matrix core, in passes of up to 32 tokens
+// one after another, over transposed weights (the copy kernel writes them so).
 #include "cmoe_internal.h"
 
 namespace cmoe {
@@ -92,8 +94,9 @@ __device__ inline void store_gated(const Layout& lo, int bl, int s, int k, int j
 // to the eight XCDs in turn.  With xcd_units, workgroup b takes unit
 // u = 8 (q / wgn) + b % 8 and part q % wgn of it, q = b / 8, so that all the
 // workgroups of a unit have the same b % 8: a unit runs on one XCD and its
-// tokens' activations are fetched into one L2 instead of eight.  Units come
-// heaviest first, and each XCD takes every eighth one.  That grid is rounded
+// tokens' activations are fetched into one L2 instead of eight.  Each XCD
+// takes every eighth unit of the list (heaviest first if some bucket takes
+// several units, else in expert order).  That grid is rounded
 // up to whole groups of eight units; u may exceed the last unit.  Without
 // it, workgroup b takes unit b / wgn, part b % wgn, and every unit is spread
 // over all XCDs: with few tokens per expert there is little to share, and
@@ -183,10 +186,11 @@ __device__ inline void mfma_pass(const uint4* __restrict__ tile, int nchunk, con
 // and read their B fragments from there.  NG token groups of 16, columns past
 // the bucket repeating its last token.
 //
-// What bounds it: the L1 caches, whose misses in flight were all in use 69% of
-// the time (128 experts d = 2048, F = 768, 64 tokens each; a third of the
-// lines are activations): more loads in flight per wavefront only made each
-// take longer, a second block of weights in flight included.  So fewer lines:
+// What bounds it: the L1 caches, whose misses in flight are all in use 66% of
+// the time (128 experts d = 2048, F = 768, 64 tokens each, T = 1; a third of the
+// lines are activations; with T = 2 71%, a fifth): more loads in flight per
+// wavefront only made each take longer, a second block of weights in flight
+// included.  So fewer lines:
 // a staging load takes whole 128-byte lines (8 tokens x one chunk; 16 tokens x
 // half a line fetched each line twice), and with many tokens per expert the
 // big units run in a launch of their own with T = 2, which halves the

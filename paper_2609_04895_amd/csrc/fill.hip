@@ -30,6 +30,7 @@ namespace {
 // Threads of a fill workgroup (four wavefronts), a compile-time constant so
 // that no loop bound has to be read from the dispatch packet.
 constexpr int kFillThreads = 256;
+static_assert(kFillThreads == kMaxN, "one expert, one slot and one ranking key per thread");
 
 // Block-wide exclusive prefix counts and sums over the 256 threads of the
 // block, each call with one barrier: the wavefront totals go to LDS slots
@@ -600,9 +601,10 @@ __global__ __launch_bounds__(kFillThreads) void copy_kernel(Layout lo, int l0, i
 }
 
 // The demand event of layer f.l0 and its copies, the arena always holding the
-// union of the caches (so that the bucket sizes decide nothing).  With one layer there is nothing to run side by side, and a
-// second launch for what is usually an empty copy list costs more than every
-// workgroup deciding the event again, however many streams' caches it reads.
+// union of the caches (so that the bucket sizes decide nothing).  With one layer
+// there is nothing to run side by side, and a second launch for what is usually
+// an empty copy list costs more than every workgroup deciding the event again,
+// however many streams' caches it reads.
 // Two launches against this one: 8.1 and 4.2 us at 64 streams of the 128-expert
 // shape; a token of given logits 12.0 and 9.3 us at 1 stream, 14.0 and 12.6 at
 // 256, 136 and 134.5 at 8192.

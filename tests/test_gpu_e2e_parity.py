@@ -217,12 +217,10 @@ def test_bf16_multi_pass_units_with_ragged_expert_count(shape):
 
 @pytest.mark.parametrize("base,N", [("qwen3_30b", 16), ("qwen3_30b_zipf", 64)])
 def test_bf16_combine_in_the_next_cache_step_ragged_tail(base, N):
-    # From the second layer on, the cache-step launch also combines the
-    # previous layer's gated outputs in workgroups after the streams': 37
-    # streams x d = 192 leave the last of them part-filled, K = 5 a part-filled
-    # batch of outputs.  N = 16: 11.6 tokens per expert, each FFN work unit on
-    # one XCD; N = 64 (full mode, with the refine-only launch of layer 0):
-    # 2.9, units spread over all XCDs.
+    # The combine's workgroups: 37 streams x d = 192 leave the last one of a
+    # layer part-filled, K = 5 a part-filled batch of outputs.  N = 16: 11.6
+    # tokens per expert, each FFN work unit on one XCD; N = 64 (full mode): 2.9,
+    # units spread over all XCDs.
     w = synth.WORKLOADS[base].replace(name=f"bf16_combine_tail_{base}_{N}", L=3, N=N, K=5, d=192, F=128, S=37,
                                       C=6, R=2)
     run_e2e(w, T=3, tol=2e-2)
